@@ -23,14 +23,12 @@ namespace kpsi {
 
 // ------------------------------------------------------------------ math helpers
 // rcp_, rsq_, fma_, the barrier polynomials and the d functions: kpsi_math.h
-// natural log from the hardware base-2 logarithm, for normal inputs only: the FP32 path counts
-// an event whose density is below the smallest normal float as a bad event (pos_floor)
-__device__ __forceinline__ float log_(float x) { return __builtin_amdgcn_logf(x) * 0.693147180559945309f; }
+// Smallest density a data event may have (exclusive): the FP32 path counts an event whose density
+// is below the smallest normal float as a bad event.
 template <typename T> __device__ __forceinline__ constexpr T pos_floor() {
   if constexpr (std::is_same_v<T, float>) return 1.17549435e-38f;
   else return T(0);
 }
-__device__ __forceinline__ double log_(double x) { return log(x); }
 
 template <typename T> __device__ __forceinline__ T ldnt(const T* p) { return __builtin_nontemporal_load(p); }
 // Load at a uniform base plus a 32-bit per-lane byte offset: this maps onto the
@@ -53,6 +51,11 @@ template <typename P> __device__ __forceinline__ kconst_ptr<P> kernarg_laundered
   asm volatile("" : "+s"(p));
   return p;
 }
+
+// FP64: x added to this thread's own LDS slot by an LDS add without a returned value, so nothing
+// waits for the slot.  (The FP32 kernel reads, adds and writes: the LDS add of a float runs at a
+// tenth of the rate here, 570 against 50 us for 3e6 events.)
+__device__ __forceinline__ void lds_add(lds_ptr<double> p, double x) { __builtin_amdgcn_ds_atomic_fadd_f64(p, x); }
 
 // ------------------------------------------------------------------ invariants
 // Columns written per event (type T, in groups of four at col_at(k, e, ld)):
@@ -282,25 +285,20 @@ template <typename T> __device__ __forceinline__ void cacc(T& gr, T& gi, const C
   gi = fma_(A.re, V.im, fma_(A.im, V.re, gi));
 }
 
-// Lineshape-parameter derivatives of one floating resonance.  B = 1/(M^2 - m^2 - i P g) is its
-// bare Breit-Wigner and Q = sum_lambda H'_lambda V'_lambda its adjoint weight, so X = B Q is
-// the resonance's share of dS/dA times A.  With A = K n B (K and P depending on M, P also on
-// Gamma0 = P/PoG):
-//   dS/dM      = Re[X (kappa - (2M - i P' g) B)],   kappa = d ln K/dM, P' = dP/dM
-//   dS/dGamma0 = Re[X i PoG g B] = -PoG g Im[X B]
-// The slot's 0/1 selectors f0, f1 route the two derivatives to floating slot 0 or 1.
-template <typename T, typename R>
-__device__ __forceinline__ void flt_deriv(const R& rc, const Cx<T>& B, const Cx<T>& Q, T g, T& gM0, T& gG0, T& gM1,
-                                          T& gG1) {
-  const T Xr = B.re * Q.re - B.im * Q.im, Xi = B.re * Q.im + B.im * Q.re;
-  const T pg = rc.dP * g;
-  const T Yr = fma_(rc.twoM, B.re, pg * B.im), Yi = fma_(rc.twoM, B.im, -pg * B.re);
-  const T dM = fma_(rc.kap, Xr, -fma_(Xr, Yr, -Xi * Yi));
-  const T dG = -rc.PoG * g * fma_(Xr, B.im, Xi * B.re);
-  gM0 = fma_(rc.f0, dM, gM0);
-  gG0 = fma_(rc.f0, dG, gG0);
-  gM1 = fma_(rc.f1, dM, gM1);
-  gG1 = fma_(rc.f1, dG, gG1);
+// Lineshape-parameter sums of one floating resonance.  B = 1/(M^2 - m^2 - i P g) is its bare
+// Breit-Wigner and Q = sum_lambda h_lambda V_lambda its adjoint weight, so X = B Q is the
+// resonance's share of dS/dA times A.  With A = K n B (K and P depending on M, P also on
+// Gamma0 = P/PoG) and Z = B X:
+//   dS/dM      = Re[X (kappa - (2M - i P' g) B)] = kappa Re X - 2M Re Z - P' g Im Z
+//   dS/dGamma0 = Re[X i PoG g B]                 = -PoG g Im Z
+// (kappa = d ln K/dM, P' = dP/dM).  The constants leave the event loop: the kernel sums Re Z and
+// g Im Z, and the host combines them with sum Re X, which follows from the coupling sums
+// (finish_record).  That is 9 instructions per event and floating resonance where the two
+// derivatives and their routing to the slots took 20.
+template <typename T> __device__ __forceinline__ void flt_sums(const Cx<T>& B, const Cx<T>& Q, T g, T& sR, T& sI) {
+  const T Xr = fma_(B.re, Q.re, -B.im * Q.im), Xi = fma_(B.re, Q.im, B.im * Q.re);
+  sR = fma_(Xr, B.re, fma_(-Xi, B.im, sR));
+  sI = fma_(g, fma_(Xr, B.im, Xi * B.re), sI);
 }
 
 template <class Sh> __host__ __device__ constexpr int acc_base(int J) {   // accumulator offset of spin J
@@ -314,9 +312,9 @@ template <class Sh> __host__ __device__ constexpr int acc_base(int J) {   // acc
 //          (data: sum ln S; norm: sum eps S).  Gradient mode, flavour tags with the Eq. 14
 //          mixture: data slot 0 is the whole sum and slot 1 the - flavour's sum of w S
 //   2    : number of data events with S <= 0 or non-finite
-//   then per K* slot (spin order) 2 (spin 0) or 6 (lambda = -1, 0, +1) values re/im of
-//   sum w * dS/dH' with H' = K H (before the factor 2), then per Z slot 4 values
-//   (lambda' = 0, +-1), then 2 per floating slot (d/dM, d/dGamma0).
+//   then per K* slot (spin order) 2 (spin 0) or 6 (h[0], h[1], h[2]) values re/im of
+//   sum w * dS/dh with h the kernel's couplings (before the factor 2), then per Z slot 4 values
+//   (h[0], h[1]), then 2 per floating slot (sum Re Z, sum g Im Z: flt_sums).
 
 // The gradient kernel of the large shape asks for 4 (FP32) or 2 (FP64) wavefronts per SIMD, at
 // most 128 or 256 registers; its spin-1..3 accumulators live in LDS to make room (36 values x
@@ -352,7 +350,10 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
   const int64_t e1 = (e0 + a.chunk < n) ? e0 + a.chunk : n;
 
   double ms = 0.0, mc = 0.0;   // Kahan pair
-  float nbad = 0.f;   // events with a non-positive or non-finite density (exact count)
+  double mprod = 1.0;          // data: product of the terms as mprod 2^mexp
+  int mexp = 0;
+  float nbad = 0.f;   // events with a non-positive or non-finite density (exact count; the call then
+                      // fails, so what they add to the sums does not matter)
   // Eq. 14 mixture on the data set: background weight k from the reduced normalisation total
   const bool mix = (set == 0) && a.bkg_data != nullptr;
   T kb = T(0), kb2 = T(0);   // background weight k (flavour tags: of the + and - flavours)
@@ -412,7 +413,7 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
   A_t gk[Sh::NKACC > 0 ? Sh::NKACC : 1];
   A_t gz[NZ > 0 ? 4 * Sh::NZ : 1];
   static_assert(NFL == 2, "floating accumulators are named registers for two slots");
-  A_t gM0 = 0, gG0 = 0, gM1 = 0, gG1 = 0;   // d/dM, d/dGamma0 of floating slots 0 and 1
+  A_t gM0 = 0, gG0 = 0, gM1 = 0, gG1 = 0;   // lineshape sums of floating slots 0 and 1 (flt_sums)
   if constexpr (GRAD) {
 #pragma unroll
     for (int i = 0; i < Sh::NKACC; ++i) gk[i] = 0;
@@ -423,43 +424,92 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
   using V4 = T __attribute__((ext_vector_type(4)));
   const V4* __restrict__ gb = (const V4*)col + e0;   // column group 0 at this block's first event
   const uint32_t n_blk = (uint32_t)(e1 > e0 ? e1 - e0 : 0);
+  // Column groups of this thread's event.  The FP64 gradient kernel (two wavefronts per SIMD)
+  // fetches the next event's as soon as the current ones are used up, before the accumulation
+  // (a clamped index past the last event: no branch); 108 against 111 us for 3e6 events.  The other
+  // kernels load them where the event begins: the live registers cost the FP32 gradient kernel
+  // more than the latency (51.5 against 50.5 us), and the likelihood-only one reads at the
+  // memory's rate either way (66 against 65 us).
+  constexpr int NG = NZ > 0 ? (ZF ? 5 : 4) : 3;
+  V4 grp[NG];
+  auto fetch = [&](uint32_t i) {
+    const uint32_t ob4 = i * (uint32_t)sizeof(V4);
+#pragma unroll
+    for (int k = 0; k < NG; ++k)
+      if (k < 3 || a.cnt[5] > 0) grp[k] = ldoff(gb + k * ld, ob4);
+  };
+  constexpr bool PRE = GRAD && std::is_same_v<T, double>;
+  if (PRE && threadIdx.x < n_blk) fetch(threadIdx.x);
   for (uint32_t i = threadIdx.x; i < n_blk; i += 256) {
     const int64_t e = e0 + i;
     const uint32_t ob = i * (uint32_t)sizeof(T);
-    const uint32_t ob4 = i * (uint32_t)sizeof(V4);
     const auto& ka = *kernarg_laundered<AmpArgs<T, Sh>>();
+    if constexpr (!PRE) fetch(i);
     // this thread's LDS accumulator column, re-derived opaquely each event so the compiler keeps
     // the accumulators in LDS instead of promoting them back into registers across the loop
     lds_ptr<A_t> accb = (lds_ptr<A_t>)&accl[0][threadIdx.x];
     if constexpr (LDSACC) asm volatile("" : "+v"(accb));
-    const V4 g0 = ldoff(gb, ob4), g1 = ldoff(gb + ld, ob4), g2 = ldoff(gb + 2 * ld, ob4);
-    const T m = g0.x, q = g0.y, pB = g0.z, cK = g0.w;
-    const T sK = g1.x, cJ = g1.y, sJ = g1.z, cph = g1.w;
-    const T sph = g2.x, qm = g2.z;   // q/m from the event columns
+    const T m = grp[0].x, q = grp[0].y, pB = grp[0].z, cK = grp[0].w;
+    const T sK = grp[1].x, cJ = grp[1].y, sJ = grp[1].z, cph = grp[1].w;
+    const T sph = grp[2].x, qm = grp[2].z;   // q/m from the event columns
 
-    const T m2 = m * m;
-    const T zR = (ka.rR * q) * (ka.rR * q);
-    const T zB = (ka.rB * pB) * (ka.rB * pB);
-    const T pbm = pB * ka.invMB;
     const T qq = q * q;
+    const T zR = ka.rR2 * qq;
+    const T zB = ka.rB2 * (pB * pB);
 
     // ---- K* lineshapes (Eq. 2-3) and coupling sums T_{J lambda}
     // Each resonance's amplitude is K n_J(m) B_R(m) with B_R = 1/(M^2 - m^2 - i P g_J(m)) the
     // bare Breit-Wigner, K the per-resonance constant and n_J the per-spin barrier and momentum
-    // factor.  K is folded into the couplings on the host (H' = K H) and n_J into the angular
+    // factor.  K is folded into the couplings on the host and n_J into the angular
     // factors of its spin, so each resonance costs one complex reciprocal: Amp holds B_R.
     Cx<T> Amp[NK > 0 ? NK : 1];
     T gJv[5] = {T(0), T(0), T(0), T(0), T(0)};   // g_J(m) per spin (width derivative)
-    T nJv[5] = {T(0), T(0), T(0), T(0), T(0)};   // n_J(m) per spin
+    T nJv[5] = {T(0), T(0), T(0), T(0), T(0)};   // n_J(m) per spin (without the 1/M_B of p_B: host)
     Cx<T> Tl[5][3];
 #pragma unroll
     for (int J = 0; J < 5; ++J)
 #pragma unroll
       for (int l = 0; l < 3; ++l) Tl[J][l] = Cx<T>{T(0), T(0)};
 
+    // The constants of a resonance are one scalar load (AC).  In FP64 (two wavefronts per SIMD)
+    // it is taken one resonance ahead: the load of the next one is issued when the current one's
+    // values have arrived (the empty asm is their first use), and the scheduling barrier, which
+    // only arithmetic may cross, keeps it there.  Scalar loads return out of order, so every wait
+    // is for all of them; loaded where they are used, each resonance waited for its own.  The four
+    // wavefronts of FP32 hide those waits, and the fixed order costs more than it gives there
+    // (tagged step 90 against 85 us).
+    using C8 = T __attribute__((ext_vector_type(8)));
+    const kconst_ptr<C8> cp = (kconst_ptr<C8>)&ka.cs[0];
+    constexpr bool AHEAD = std::is_same_v<T, double>;
+    C8 ahead{};
+    if constexpr (AHEAD) ahead = cp[0];
+    auto constants = [&](int k) -> C8 {
+      if constexpr (AHEAD) {
+        asm volatile("" : "+s"(ahead));
+        const C8 c = ahead;
+        if (k + 1 < NK + Sh::NZ) ahead = cp[k + 1];
+        __builtin_amdgcn_sched_barrier(1);
+        return c;
+      } else {
+        return cp[k];
+      }
+    };
     // Every K* slot of the shape is evaluated: the host gives the slots the model leaves empty
     // zero couplings and the constants M^2 = P = 0 (a finite 1/D = -1/m^2), so they add nothing
     // and need no per-event test (the Z slots keep theirs: models often use one of the two).
+    const int lass = ka.lass;
+    // LASS (Eq. 7-8): with u = q cot(delta_B) = 1/a + b q^2/2 (finite at threshold),
+    // (m/q) sin(delta_B) e^{i delta_B} = m (u + i q)/(u^2 + q^2) and
+    // e^{2 i delta_B} = (u + i q)^2/(u^2 + q^2); the resonant term is the
+    // Breit-Wigner B times P = M^2 Gamma0/q0 and e^{2 i delta_B}
+    auto lass_amp = [&](int k, T P, const Cx<T>& B) -> Cx<T> {
+      if (!(lass & (1 << k))) return B;
+      const T u = fma_(ka.lhb[k], qq, ka.lai[k]);
+      const T dn = rcp_(fma_(u, u, qq));
+      const T er = (u * u - qq) * dn, ei = T(2) * u * q * dn;
+      const T md = m * dn;
+      return Cx<T>{fma_(md, u, P * (er * B.re - ei * B.im)), fma_(md, q, P * (er * B.im + ei * B.re))};
+    };
     auto do_spin = [&](auto Jc) {
       constexpr int J = decltype(Jc)::value;
       if constexpr (Sh::N[J] > 0) {
@@ -467,7 +517,7 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
           constexpr int LB = LBof<J>::v;
           const T BR = bpoly<J>(zR), BB = bpoly<LB>(zB);
           const T rJ = rsq_(BR * BB);
-          const T nJ = ipow<T, LB>(pbm) * ipow<T, J>(qm) * rJ;
+          const T nJ = ipow<T, LB>(pB) * ipow<T, J>(qm) * rJ;
           // 1/B_J(z_R) = rJ^2 B_LB(z_B): no second reciprocal
           T gJ = qm;
           if constexpr (J > 0) gJ = qm * ipow<T, J>(qq) * (rJ * rJ * BB);
@@ -477,32 +527,20 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
 #pragma unroll
           for (int j = 0; j < Sh::N[J]; ++j) {
             {
-              const auto& rc = ka.ks[sb + j];
-              const T dre = pole_gap(rc, m2);
-              const T dim = rc.P * gJ;   // M Gamma(m)
+              const C8 rc = constants(sb + j);   // M2, P, h
+              const T dre = pole_gap_m(rc[0], ka.M2lo[sb + j], m);
+              const T dim = rc[1] * gJ;   // M Gamma(m)
               const T inv = rcp_(fma_(dre, dre, dim * dim));
-              const T br = dre * inv, bi = dim * inv;
-              T Ar = br, Ai = bi;
+              Cx<T> A{dre * inv, dim * inv};
               if constexpr (J == 0) {
-                if (rc.lass) {
-                  // LASS (Eq. 7-8): with u = q cot(delta_B) = 1/a + b q^2/2 (finite at threshold),
-                  // (m/q) sin(delta_B) e^{i delta_B} = m (u + i q)/(u^2 + q^2) and
-                  // e^{2 i delta_B} = (u + i q)^2/(u^2 + q^2); the resonant term is the
-                  // Breit-Wigner above times P = M^2 Gamma0/q0 and e^{2 i delta_B}
-                  const T u = fma_(rc.lhb, qq, rc.lai);
-                  const T dn = rcp_(fma_(u, u, qq));
-                  const T er = (u * u - qq) * dn, ei = T(2) * u * q * dn;
-                  const T md = m * dn;
-                  Ar = fma_(md, u, rc.P * (er * br - ei * bi));
-                  Ai = fma_(md, q, rc.P * (er * bi + ei * br));
-                }
+                if (lass) A = lass_amp(sb + j, rc[1], A);
               }
-              Amp[sb + j] = Cx<T>{Ar, Ai};
+              Amp[sb + j] = A;
               if constexpr (J == 0) {
-                cmac(Tl[0][1], rc.hr[1], rc.hi[1], Ar, Ai);
+                cmac(Tl[0][1], rc[4], rc[5], A.re, A.im);
               } else {
 #pragma unroll
-                for (int l = 0; l < 3; ++l) cmac(Tl[J][l], rc.hr[l], rc.hi[l], Ar, Ai);
+                for (int l = 0; l < 3; ++l) cmac(Tl[J][l], rc[2 + 2 * l], rc[3 + 2 * l], A.re, A.im);
               }
             }
           }
@@ -515,57 +553,71 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
     do_spin(std::integral_constant<int, 3>{});
     do_spin(std::integral_constant<int, 4>{});
 
-    // ---- angular sums (Eq. 4): U_lambda = sum_J d^J_{lambda 0}(theta_K) T_{J lambda}
-    // (n_J times the d functions; the n_J of spins absent from the model are zero)
+    // ---- angular sums (Eq. 4) in the transversity basis.  With the helicity sums U_+- and U_0 of
+    // Eq. 4, P = (U_+ + U_-)/sqrt2 and M = (U_+ - U_-)/sqrt2 come from the coupling combinations
+    // h[0], h[2] directly (d^J_{-10} = -d^J_{10}), and the muon amplitudes a_+-1 rotated to
+    // X = (a_+ + a_-)/sqrt2, Y = (a_+ - a_-)/sqrt2 (S = |X|^2 + |Y|^2) are
+    //   X = cos phi P + i sin phi M + Z terms
+    //   Y = cos th_J (cos phi M + i sin phi P) + sin th_J U_0 + Z terms:
+    // every factor is real or imaginary, so each step is half a complex product, in the adjoint
+    // too.  The helicity form took about 25% more instructions for this part and twice as many in
+    // the Z chain.
+    // (n_J times the angular functions; the n_J of spins absent from the model are zero)
     T dd0[5], dd1[5];
-    dd0[0] = nJv[0]; dd1[0] = T(0);
-    dd0[1] = nJv[1] * d00<1>(cK); dd1[1] = nJv[1] * d10<1>(cK, sK);
-    dd0[2] = nJv[2] * d00<2>(cK); dd1[2] = nJv[2] * d10<2>(cK, sK);
-    dd0[3] = nJv[3] * d00<3>(cK); dd1[3] = nJv[3] * d10<3>(cK, sK);
-    dd0[4] = nJv[4] * d00<4>(cK); dd1[4] = nJv[4] * d10<4>(cK, sK);
-    Cx<T> U0{T(0), T(0)}, Up{T(0), T(0)}, Um{T(0), T(0)};
+    auto do_ang = [&](auto Jc) {
+      constexpr int J = decltype(Jc)::value;
+      dd0[J] = nJv[J] * ang0<J>(cK);
+      dd1[J] = J > 0 ? nJv[J] * sK * ang1<J>(cK) : T(0);
+    };
+    do_ang(std::integral_constant<int, 0>{});
+    do_ang(std::integral_constant<int, 1>{});
+    do_ang(std::integral_constant<int, 2>{});
+    do_ang(std::integral_constant<int, 3>{});
+    do_ang(std::integral_constant<int, 4>{});
+    Cx<T> U0{T(0), T(0)}, UP{T(0), T(0)}, UM{T(0), T(0)};
 #pragma unroll
     for (int J = 0; J < 5; ++J) {
       if (Sh::N[J] == 0) continue;
       U0.re = fma_(dd0[J], Tl[J][1].re, U0.re);
       U0.im = fma_(dd0[J], Tl[J][1].im, U0.im);
       if (J > 0) {
-        Up.re = fma_(dd1[J], Tl[J][2].re, Up.re);
-        Up.im = fma_(dd1[J], Tl[J][2].im, Up.im);
-        Um.re = fma_(-dd1[J], Tl[J][0].re, Um.re);
-        Um.im = fma_(-dd1[J], Tl[J][0].im, Um.im);
+        UP.re = fma_(dd1[J], Tl[J][0].re, UP.re);
+        UP.im = fma_(dd1[J], Tl[J][0].im, UP.im);
+        UM.re = fma_(dd1[J], Tl[J][2].re, UM.re);
+        UM.im = fma_(dd1[J], Tl[J][2].im, UM.im);
       }
     }
-    // e^{i lambda phi} d^1_{lambda xi}(theta_J):  lambda=+1: (1+c)/2, (1-c)/2;  0: s/sqrt2, -s/sqrt2;
-    // lambda=-1: (1-c)/2, (1+c)/2   for xi = +1, -1
-    const T hp = T(0.5) * (T(1) + cJ), hm = T(0.5) * (T(1) - cJ), s0 = sJ * T(0.70710678118654752440);
-    // Amplitudes a_xi (Eq. 12) of the event read with phi -> f phi.  f = -1 is the
-    // charge-conjugate decay: e^{i lambda phi} becomes e^{-i lambda phi}, and the Z-chain azimuths
-    // phi~ and alpha reverse, which conjugates the Z angular factors.
-    auto kstar_at = [&](T f, Cx<T>& ap_, Cx<T>& am_) {
+    // Amplitudes X, Y of the event read with phi -> f phi.  f = -1 is the charge-conjugate decay:
+    // sin phi changes its sign, and the Z-chain azimuths phi~ and alpha reverse, which conjugates
+    // the Z angular factors.
+    auto kstar_at = [&](T f, Cx<T>& X_, Cx<T>& Y_) {
       const T sp = f * sph;
-      const Cx<T> eUp{cph * Up.re - sp * Up.im, cph * Up.im + sp * Up.re};
-      const Cx<T> eUm{cph * Um.re + sp * Um.im, cph * Um.im - sp * Um.re};
-      ap_ = Cx<T>{hp * eUp.re + s0 * U0.re + hm * eUm.re, hp * eUp.im + s0 * U0.im + hm * eUm.im};
-      am_ = Cx<T>{hm * eUp.re - s0 * U0.re + hp * eUm.re, hm * eUp.im - s0 * U0.im + hp * eUm.im};
+      X_ = Cx<T>{fma_(cph, UP.re, -sp * UM.im), fma_(cph, UP.im, sp * UM.re)};
+      const Cx<T> y{fma_(cph, UM.re, -sp * UP.im), fma_(cph, UM.im, sp * UP.re)};
+      Y_ = Cx<T>{fma_(cJ, y.re, sJ * U0.re), fma_(cJ, y.im, sJ * U0.im)};
     };
-    // Zang[l'][xi] as (re, im) pairs: l' = 0 (xi = +1, -1), l' = +-1 or +1, then (ZF) l' = -1
-    T za[ZF ? 12 : 8];
-    auto z_add = [&](T f, const Cx<T>& T0, const Cx<T>& T1, const Cx<T>& T2, Cx<T>& ap_, Cx<T>& am_) {
-      cmac(ap_, T0.re, T0.im, za[0], f * za[1]);
-      cmac(am_, T0.re, T0.im, za[2], f * za[3]);
-      cmac(ap_, T1.re, T1.im, za[4], f * za[5]);
-      cmac(am_, T1.re, T1.im, za[6], f * za[7]);
+    // Z chain: X += i z0i T0 + i z1i T1 (+ z2r T2), Y += z0r T0 + z1r T1 (+ i z2i T2), T2 with free
+    // helicities only; the imaginary parts carry f
+    T z0r = T(0), z0i = T(0), z1r = T(0), z1i = T(0), z2r = T(0), z2i = T(0);
+    auto z_add = [&](T f, const Cx<T>& T0, const Cx<T>& T1, const Cx<T>& T2, Cx<T>& X_, Cx<T>& Y_) {
+      const T a0 = f * z0i, a1 = f * z1i;
+      X_.re = fma_(-a0, T0.im, fma_(-a1, T1.im, X_.re));
+      X_.im = fma_(a0, T0.re, fma_(a1, T1.re, X_.im));
+      Y_.re = fma_(z0r, T0.re, fma_(z1r, T1.re, Y_.re));
+      Y_.im = fma_(z0r, T0.im, fma_(z1r, T1.im, Y_.im));
       if constexpr (ZF) {
-        cmac(ap_, T2.re, T2.im, za[8], f * za[9]);
-        cmac(am_, T2.re, T2.im, za[10], f * za[11]);
+        const T a2 = f * z2i;
+        X_.re = fma_(z2r, T2.re, X_.re);
+        X_.im = fma_(z2r, T2.im, X_.im);
+        Y_.re = fma_(-a2, T2.im, Y_.re);
+        Y_.im = fma_(a2, T2.re, Y_.im);
       }
     };
     // flavour of this reading: the tag of a data event, + / - for the two normalisation records
     T f1 = T(1);
     if constexpr (CC) f1 = set == 0 ? ldoff(a.tag + e0, ob) : (set == 1 ? T(1) : T(-1));
-    Cx<T> ap, am;
-    kstar_at(f1, ap, am);
+    Cx<T> X, Y;
+    kstar_at(f1, X, Y);
 
     // ---- Z chain (Eq. 10-12)
     // (AZ holds the bare Breit-Wigner; the Z barrier factor n_Z is in the angular columns)
@@ -574,34 +626,40 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
     Cx<T> T0k{T(0), T(0)}, T1k{T(0), T(0)}, T2k{T(0), T(0)};   // Z coupling sums, kept for a second reading
     if constexpr (NZ > 0) {
       if (a.cnt[5] > 0) {
-        const T mz2 = g2.y;
-        gzv = g2.w;
-        // Zang[l'][xi]: for l' = 0 and the combined l' = +-1, xi = -1 is (-Re, Im) of xi = +1
-        const V4 g3 = ldoff(gb + 3 * ld, ob4);
-        za[0] = g3.x; za[1] = g3.y; za[2] = -g3.x; za[3] = g3.y;
+        const T mz2 = grp[2].y;
+        gzv = grp[2].w;
+        // The xi = -1 factors are (-Re, Im) of the xi = +1 ones (columns 12-15), so Im enters X and
+        // Re enters Y
+        const V4 g3 = grp[3];
+        z0r = g3.x;
+        z0i = g3.y;
         if constexpr (ZF) {
-          // l' = +1: F++, F+-;  l' = -1: -conj(F+-), -conj(F++)
-          const V4 g4 = ldoff(gb + 4 * ld, ob4);
-          za[4] = g3.z; za[5] = g3.w; za[6] = g4.x; za[7] = g4.y;
-          za[8] = -g4.x; za[9] = g4.y; za[10] = -g3.z; za[11] = g3.w;
+          // F++ (14-15) and F+- (16-17): the sum and difference couplings take the real and
+          // imaginary parts of F++ +- F+-
+          const V4 g4 = grp[4];
+          z1r = g3.z - g4.x;
+          z1i = g3.w + g4.y;
+          z2r = g3.z + g4.x;
+          z2i = g3.w - g4.y;
         } else {
-          za[4] = g3.z; za[5] = g3.w; za[6] = -g3.z; za[7] = g3.w;
+          z1r = g3.z;
+          z1i = g3.w;
         }
         Cx<T> T0{T(0), T(0)}, T1{T(0), T(0)}, T2{T(0), T(0)};
 #pragma unroll
         for (int z = 0; z < NZ; ++z) {
           if (z < a.cnt[5]) {
-            const auto& rc = ka.zs[z];
-            const T dre = pole_gap(rc, mz2);
-            const T dim = rc.P * gzv;
+            const C8 rc = constants(NK + z);
+            const T dre = pole_gap(rc[0], ka.M2lo[NK + z], mz2);
+            const T dim = rc[1] * gzv;
             const T inv = rcp_(fma_(dre, dre, dim * dim));
             AZ[z] = Cx<T>{dre * inv, dim * inv};
-            cmac(T0, rc.hr[0], rc.hi[0], AZ[z].re, AZ[z].im);
-            cmac(T1, rc.hr[1], rc.hi[1], AZ[z].re, AZ[z].im);
-            if constexpr (ZF) cmac(T2, rc.hr[2], rc.hi[2], AZ[z].re, AZ[z].im);
+            cmac(T0, rc[2], rc[3], AZ[z].re, AZ[z].im);
+            cmac(T1, rc[4], rc[5], AZ[z].re, AZ[z].im);
+            if constexpr (ZF) cmac(T2, rc[6], rc[7], AZ[z].re, AZ[z].im);
           }
         }
-        z_add(f1, T0, T1, T2, ap, am);
+        z_add(f1, T0, T1, T2, X, Y);
         if constexpr (CC) {
           T0k = T0;
           T1k = T1;
@@ -610,7 +668,7 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
       }
     }
 
-    const T S = ap.re * ap.re + ap.im * ap.im + am.re * am.re + am.im * am.im;
+    const T S = fma_(X.re, X.re, X.im * X.im) + fma_(Y.re, Y.re, Y.im * Y.im);
 
     if constexpr (MODE == MODE_DENSITY) {
       a.s_out[set][e] = (double)S;
@@ -620,18 +678,18 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
     // ---- likelihood terms
     T w;
     T w2 = T(0);                  // mistag: adjoint weight of the other-flavour reading
-    Cx<T> ap2{T(0), T(0)}, am2{T(0), T(0)};
+    Cx<T> X2{T(0), T(0)}, Y2{T(0), T(0)};
     if (set == 0) {
       T arg = S;   // the quantity whose logarithm is summed
       if constexpr (CC) {
         T S2 = T(0);
         if (a.mistag > T(0)) {
           // t = (1 - w) S(q phi) + w S(-q phi)
-          kstar_at(-f1, ap2, am2);
+          kstar_at(-f1, X2, Y2);
           if constexpr (NZ > 0) {
-            if (a.cnt[5] > 0) z_add(-f1, T0k, T1k, T2k, ap2, am2);
+            if (a.cnt[5] > 0) z_add(-f1, T0k, T1k, T2k, X2, Y2);
           }
-          S2 = ap2.re * ap2.re + ap2.im * ap2.im + am2.re * am2.re + am2.im * am2.im;
+          S2 = fma_(X2.re, X2.re, X2.im * X2.im) + fma_(Y2.re, Y2.re, Y2.im * Y2.im);
           arg = fma_(a.keep, S, a.mistag * S2);
         }
         // Eq. 14 with tags: t = p eps [(1 - w) S(q phi) + w S(-q phi)] + k_q b, k_q of the
@@ -641,7 +699,7 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
           pe = a.purity * (a.eps_data ? ldoff(a.eps_data + e0, ob) : T(1));
           arg = fma_(pe, arg, (f1 > T(0) ? kb : kb2) * ldoff(a.bkg_data + e0, ob));
         }
-        if (!(arg > pos_floor<T>()) || !(arg < T(INFINITY))) { nbad += 1.f; continue; }
+        if (!(arg > pos_floor<T>()) || !(arg < T(INFINITY))) nbad += 1.f;
         const T r = pe * rcp_(arg);
         if (a.mistag > T(0)) {
           w = a.keep * r;
@@ -658,18 +716,19 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
         // Eq. 14: t = p eps S + k b; d ln t / dS = p eps / t
         const T pe = a.purity * (a.eps_data ? ldoff(a.eps_data + e0, ob) : T(1));
         arg = fma_(pe, S, kb * ldoff(a.bkg_data + e0, ob));
-        if (!(arg > pos_floor<T>()) || !(arg < T(INFINITY))) { nbad += 1.f; continue; }
+        if (!(arg > pos_floor<T>()) || !(arg < T(INFINITY))) nbad += 1.f;
         w = pe * rcp_(arg);
         ws += (A_t)(w * S);
       } else {
-        if (!(S > pos_floor<T>()) || !(S < T(INFINITY))) { nbad += 1.f; continue; }
+        if (!(S > pos_floor<T>()) || !(S < T(INFINITY))) nbad += 1.f;
         w = rcp_(S);
       }
-      const double x = (double)log_(arg);
-      const double y = x - mc;
-      const double t = ms + y;
-      mc = (t - ms) - y;
-      ms = t;
+      // ln of the product of the terms: mantissa product in [1/2, 1) and exponent sum; one
+      // logarithm per thread after the loop (a rounding of 2^-53 per event, below that of a
+      // logarithm per event and its sum; 4-5 instructions in place of 8 in FP32 and 100 in FP64)
+      const double pr = mprod * (double)arg;
+      mprod = __builtin_amdgcn_frexp_mant(pr);
+      mexp += __builtin_amdgcn_frexp_exp(pr);
     } else {
       const T eps = a.eps ? ldoff(a.eps + e0, ob) : T(1);
       const double x = (double)(eps * S);
@@ -681,84 +740,112 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
     }
 
     if constexpr (GRAD) {
-      // adjoint of S = sum_xi |a_xi|^2: b_xi = w conj(a_xi); W_lambda = sum_xi E_{lambda xi} b_xi,
-      // summed over the readings of the event
-      Cx<T> W0, Wp, Wm;
-      Cx<T> bp, bm, bp2{T(0), T(0)}, bm2{T(0), T(0)};
-      auto adj_w = [&](auto first, T wt, T f, const Cx<T>& ap_, const Cx<T>& am_, Cx<T>& bp_, Cx<T>& bm_) {
+      // adjoint of S = |X|^2 + |Y|^2: bX = w conj(X), bY = w conj(Y); the weights of P, M and U_0
+      // are W_P = cos phi bX + i sin phi cos th_J bY, W_M = i sin phi bX + cos phi cos th_J bY and
+      // W_0 = sin th_J bY, summed over the readings of the event
+      Cx<T> W0, WP, WM;
+      Cx<T> bX, bY, bX2{T(0), T(0)}, bY2{T(0), T(0)};
+      auto adj_w = [&](auto first, T wt, T f, const Cx<T>& X_, const Cx<T>& Y_, Cx<T>& bX_, Cx<T>& bY_) {
         constexpr bool F = decltype(first)::value;
-        bp_ = Cx<T>{wt * ap_.re, -wt * ap_.im};
-        bm_ = Cx<T>{wt * am_.re, -wt * am_.im};
+        bX_ = Cx<T>{wt * X_.re, -wt * X_.im};
+        bY_ = Cx<T>{wt * Y_.re, -wt * Y_.im};
         const T sp = f * sph;
-        const Cx<T> Wp0{hp * bp_.re + hm * bm_.re, hp * bp_.im + hm * bm_.im};
-        const Cx<T> wp{cph * Wp0.re - sp * Wp0.im, cph * Wp0.im + sp * Wp0.re};   // e^{+i f phi}
-        const Cx<T> w0{s0 * (bp_.re - bm_.re), s0 * (bp_.im - bm_.im)};
-        const Cx<T> Wm0{hm * bp_.re + hp * bm_.re, hm * bp_.im + hp * bm_.im};
-        const Cx<T> wm{cph * Wm0.re + sp * Wm0.im, cph * Wm0.im - sp * Wm0.re};   // e^{-i f phi}
+        const Cx<T> y{cJ * bY_.re, cJ * bY_.im};
         if constexpr (F) {
-          Wp = wp; W0 = w0; Wm = wm;
+          WP = Cx<T>{fma_(cph, bX_.re, -sp * y.im), fma_(cph, bX_.im, sp * y.re)};
+          WM = Cx<T>{fma_(cph, y.re, -sp * bX_.im), fma_(cph, y.im, sp * bX_.re)};
+          W0 = Cx<T>{sJ * bY_.re, sJ * bY_.im};
         } else {
-          Wp.re += wp.re; Wp.im += wp.im;
-          W0.re += w0.re; W0.im += w0.im;
-          Wm.re += wm.re; Wm.im += wm.im;
+          WP.re = fma_(cph, bX_.re, fma_(-sp, y.im, WP.re));
+          WP.im = fma_(cph, bX_.im, fma_(sp, y.re, WP.im));
+          WM.re = fma_(cph, y.re, fma_(-sp, bX_.im, WM.re));
+          WM.im = fma_(cph, y.im, fma_(sp, bX_.re, WM.im));
+          W0.re = fma_(sJ, bY_.re, W0.re);
+          W0.im = fma_(sJ, bY_.im, W0.im);
         }
       };
-      adj_w(std::true_type{}, w, f1, ap, am, bp, bm);
+      adj_w(std::true_type{}, w, f1, X, Y, bX, bY);
       const bool two = CC && set == 0 && a.mistag > T(0);
       if constexpr (CC) {
-        if (two) adj_w(std::false_type{}, w2, -f1, ap2, am2, bp2, bm2);
+        if (two) adj_w(std::false_type{}, w2, -f1, X2, Y2, bX2, bY2);
       }
-
+      // weights of the Z coupling sums over the readings: WZ0 = i z0i bX + z0r bY, WZ1 alike, and
+      // with free helicities WZ2 = z2r bX + i z2i bY
+      Cx<T> WZ0{T(0), T(0)}, WZ1{T(0), T(0)}, WZ2{T(0), T(0)};
+      auto wz = [&](auto first, T f, const Cx<T>& bX_, const Cx<T>& bY_) {
+        constexpr bool F = decltype(first)::value;
+        const T a0 = f * z0i, a1 = f * z1i;
+        Cx<T> y0{z0r * bY_.re, z0r * bY_.im}, y1{z1r * bY_.re, z1r * bY_.im};
+        if constexpr (!F) {
+          y0.re += WZ0.re; y0.im += WZ0.im;
+          y1.re += WZ1.re; y1.im += WZ1.im;
+        }
+        WZ0 = Cx<T>{fma_(-a0, bX_.im, y0.re), fma_(a0, bX_.re, y0.im)};
+        WZ1 = Cx<T>{fma_(-a1, bX_.im, y1.re), fma_(a1, bX_.re, y1.im)};
+        if constexpr (ZF) {
+          const T a2 = f * z2i;
+          WZ2.re = fma_(z2r, bX_.re, fma_(-a2, bY_.im, WZ2.re));
+          WZ2.im = fma_(z2r, bX_.im, fma_(a2, bY_.re, WZ2.im));
+        }
+      };
+      auto z_weights = [&]() {
+        wz(std::true_type{}, f1, bX, bY);
+        if constexpr (CC) {
+          if (two) wz(std::false_type{}, -f1, bX2, bY2);
+        }
+      };
+      // V_{J lambda}: the angular functions times the weights
+      auto V_of = [&](auto Jc, Cx<T>& VP, Cx<T>& V0, Cx<T>& VM) {
+        constexpr int J = decltype(Jc)::value;
+        V0 = Cx<T>{dd0[J] * W0.re, dd0[J] * W0.im};
+        if constexpr (J > 0) {
+          VP = Cx<T>{dd1[J] * WP.re, dd1[J] * WP.im};
+          VM = Cx<T>{dd1[J] * WM.re, dd1[J] * WM.im};
+        }
+      };
+      if constexpr (NZ > 0) {
+        if (a.cnt[5] > 0) z_weights();
+      }
+      if constexpr (PRE) fetch(i + 256 < n_blk ? i + 256 : i);
       auto grad_spin = [&](auto Jc) {
         constexpr int J = decltype(Jc)::value;
         if constexpr (Sh::N[J] > 0) {
-          {
-            constexpr int sb = slot_base<Sh>(J);
-            constexpr int ab = acc_base<Sh>(J) - 3;
-            // V_{J lambda} = d^J_{lambda 0} W_lambda
-            const Cx<T> V0{dd0[J] * W0.re, dd0[J] * W0.im};
-            const Cx<T> Vp{dd1[J] * Wp.re, dd1[J] * Wp.im};
-            const Cx<T> Vm{-dd1[J] * Wm.re, -dd1[J] * Wm.im};
+          constexpr int sb = slot_base<Sh>(J);
+          constexpr int ab = acc_base<Sh>(J) - 3;
+          Cx<T> VP, V0, VM;
+          V_of(Jc, VP, V0, VM);
 #pragma unroll
-            for (int j = 0; j < Sh::N[J]; ++j) {
-              {
-                const Cx<T> A = Amp[sb + j];
-                const auto& rc = ka.ks[sb + j];
-                Cx<T> Q{T(0), T(0)};
-                if constexpr (J == 0) {
-                  // accumulators += A V as two fused multiply-adds per component
-                  cacc(gk[ab + 2 * j], gk[ab + 2 * j + 1], A, V0);
-                  if (rc.flt >= 0) cmac(Q, rc.hr[1], rc.hi[1], V0.re, V0.im);
-                } else if constexpr (LDSACC && J >= 1 && J <= 3) {
-                  // ab + 6 j lies in [LO, HI): read-add-write this thread's own LDS slots (no other
-                  // lane touches them, so no atomics)
-                  lds_ptr<A_t> g = accb + 256 * (ab + 6 * j - LO);
-                  A_t v[6];
+          for (int j = 0; j < Sh::N[J]; ++j) {
+            const Cx<T> A = Amp[sb + j];
+            if constexpr (J == 0) {
+              // accumulators += A V as two fused multiply-adds per component
+              cacc(gk[ab + 2 * j], gk[ab + 2 * j + 1], A, V0);
+            } else if constexpr (LDSACC && J >= 1 && J <= 3) {
+              // ab + 6 j lies in [LO, HI): this thread's own LDS slots
+              lds_ptr<A_t> g = accb + 256 * (ab + 6 * j - LO);
+              if constexpr (std::is_same_v<A_t, double>) {
+                auto add = [&](int l, const Cx<T>& V) {
+                  lds_add(g + 512 * l, fma_(A.re, V.re, -A.im * V.im));
+                  lds_add(g + 512 * l + 256, fma_(A.re, V.im, A.im * V.re));
+                };
+                add(0, VP);
+                add(1, V0);
+                add(2, VM);
+              } else {
+                A_t v[6];
 #pragma unroll
-                  for (int q = 0; q < 6; ++q) v[q] = g[256 * q];
-                  cacc(v[0], v[1], A, Vm);
-                  cacc(v[2], v[3], A, V0);
-                  cacc(v[4], v[5], A, Vp);
+                for (int q = 0; q < 6; ++q) v[q] = g[256 * q];
+                cacc(v[0], v[1], A, VP);
+                cacc(v[2], v[3], A, V0);
+                cacc(v[4], v[5], A, VM);
 #pragma unroll
-                  for (int q = 0; q < 6; ++q) g[256 * q] = v[q];
-                  if (rc.flt >= 0) {
-                    cmac(Q, rc.hr[0], rc.hi[0], Vm.re, Vm.im);
-                    cmac(Q, rc.hr[1], rc.hi[1], V0.re, V0.im);
-                    cmac(Q, rc.hr[2], rc.hi[2], Vp.re, Vp.im);
-                  }
-                } else {
-                  A_t* g = gk + ab + 6 * j;
-                  cacc(g[0], g[1], A, Vm);
-                  cacc(g[2], g[3], A, V0);
-                  cacc(g[4], g[5], A, Vp);
-                  if (rc.flt >= 0) {
-                    cmac(Q, rc.hr[0], rc.hi[0], Vm.re, Vm.im);
-                    cmac(Q, rc.hr[1], rc.hi[1], V0.re, V0.im);
-                    cmac(Q, rc.hr[2], rc.hi[2], Vp.re, Vp.im);
-                  }
-                }
-                if (rc.flt >= 0) flt_deriv(rc, A, Q, gJv[J], gM0, gG0, gM1, gG1);
+                for (int q = 0; q < 6; ++q) g[256 * q] = v[q];
               }
+            } else {
+              A_t* g = gk + ab + 6 * j;
+              cacc(g[0], g[1], A, VP);
+              cacc(g[2], g[3], A, V0);
+              cacc(g[4], g[5], A, VM);
             }
           }
         }
@@ -771,36 +858,6 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
 
       if constexpr (NZ > 0) {
         if (a.cnt[5] > 0) {
-          // WZ_{l'} = sum_xi Zang_{l' xi} b_xi over the readings
-          auto wz = [&](T f, const Cx<T>& bp_, const Cx<T>& bm_, Cx<T>& WZ0, Cx<T>& WZ1) {
-            const T z1 = f * za[1], z3 = f * za[3], z5 = f * za[5], z7 = f * za[7];
-            WZ0 = Cx<T>{za[0] * bp_.re - z1 * bp_.im + za[2] * bm_.re - z3 * bm_.im,
-                        za[0] * bp_.im + z1 * bp_.re + za[2] * bm_.im + z3 * bm_.re};
-            WZ1 = Cx<T>{za[4] * bp_.re - z5 * bp_.im + za[6] * bm_.re - z7 * bm_.im,
-                        za[4] * bp_.im + z5 * bp_.re + za[6] * bm_.im + z7 * bm_.re};
-          };
-          // (free helicities) WZ_{-1} from the l' = -1 factors, same form; a generic lambda, so
-          // that its body exists only in the instantiations that call it (za has 12 entries there)
-          auto wz2 = [&](auto f, const auto& bp_, const auto& bm_) -> Cx<T> {
-            const T z9 = f * za[9], z11 = f * za[11];
-            return Cx<T>{za[8] * bp_.re - z9 * bp_.im + za[10] * bm_.re - z11 * bm_.im,
-                         za[8] * bp_.im + z9 * bp_.re + za[10] * bm_.im + z11 * bm_.re};
-          };
-          Cx<T> WZ0, WZ1, WZ2{T(0), T(0)};
-          wz(f1, bp, bm, WZ0, WZ1);
-          if constexpr (ZF) WZ2 = wz2(f1, bp, bm);
-          if constexpr (CC) {
-            if (two) {
-              Cx<T> X0, X1;
-              wz(-f1, bp2, bm2, X0, X1);
-              WZ0.re += X0.re; WZ0.im += X0.im;
-              WZ1.re += X1.re; WZ1.im += X1.im;
-              if constexpr (ZF) {
-                const Cx<T> X2 = wz2(-f1, bp2, bm2);
-                WZ2.re += X2.re; WZ2.im += X2.im;
-              }
-            }
-          }
 #pragma unroll
           for (int z = 0; z < NZ; ++z) {
             if (z < a.cnt[5]) {
@@ -809,23 +866,70 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
               cacc(g[0], g[1], A, WZ0);
               cacc(g[2], g[3], A, WZ1);
               if constexpr (ZF) cacc(g[4], g[5], A, WZ2);   // the second Z's lambda' = 0 slots
-              const auto& rc = ka.zs[z];
-              if (rc.flt >= 0) {
-                Cx<T> Q{T(0), T(0)};
-                cmac(Q, rc.hr[0], rc.hi[0], WZ0.re, WZ0.im);
-                cmac(Q, rc.hr[1], rc.hi[1], WZ1.re, WZ1.im);
-                if constexpr (ZF) cmac(Q, rc.hr[2], rc.hi[2], WZ2.re, WZ2.im);
-                flt_deriv(rc, A, Q, gzv, gM0, gG0, gM1, gG1);
-              }
             }
           }
         }
+      }
+
+      // Lineshape sums of the floating slots: the slot's Breit-Wigner, adjoint weight and width
+      // factor are picked by uniform branches (the slot numbers are re-read each event, so the
+      // comparisons are not hoisted into scalar registers the loop needs), then one piece of code
+      // sums them.
+      auto flt_slot = [&](int slot, T& sR, T& sI) {
+        Cx<T> B{T(0), T(0)}, Q{T(0), T(0)};
+        T g = T(0);
+        auto pick = [&](auto Jc) {
+          constexpr int J = decltype(Jc)::value;
+          constexpr int sb = slot_base<Sh>(J);
+#pragma unroll
+          for (int j = 0; j < Sh::N[J]; ++j) {
+            if (slot != sb + j) continue;
+            const auto& rc = ka.cs[sb + j];
+            Cx<T> VP, V0, VM;
+            V_of(Jc, VP, V0, VM);
+            if constexpr (J > 0) cmac(Q, rc.h[0][0], rc.h[0][1], VP.re, VP.im);
+            cmac(Q, rc.h[1][0], rc.h[1][1], V0.re, V0.im);
+            if constexpr (J > 0) cmac(Q, rc.h[2][0], rc.h[2][1], VM.re, VM.im);
+            B = Amp[sb + j];
+            g = gJv[J];
+          }
+        };
+        pick(std::integral_constant<int, 0>{});
+        pick(std::integral_constant<int, 1>{});
+        pick(std::integral_constant<int, 2>{});
+        pick(std::integral_constant<int, 3>{});
+        pick(std::integral_constant<int, 4>{});
+        if constexpr (NZ > 0) {
+#pragma unroll
+          for (int z = 0; z < NZ; ++z) {
+            if (slot != NK + z) continue;
+            const auto& rc = ka.cs[NK + z];
+            cmac(Q, rc.h[0][0], rc.h[0][1], WZ0.re, WZ0.im);
+            cmac(Q, rc.h[1][0], rc.h[1][1], WZ1.re, WZ1.im);
+            if constexpr (ZF) cmac(Q, rc.h[2][0], rc.h[2][1], WZ2.re, WZ2.im);
+            B = AZ[z];
+            g = gzv;
+          }
+        }
+        flt_sums(B, Q, g, sR, sI);
+      };
+      const int fs0 = ka.flt[0], fs1 = ka.flt[1];   // (the first is filled first)
+      if (fs0 >= 0) {
+        flt_slot(fs0, gM0, gG0);
+        if (fs1 >= 0) flt_slot(fs1, gM1, gG1);
       }
     }
   }
 
   if constexpr (MODE == MODE_DENSITY) return;
 
+  if (set == 0) {
+    // ln(mprod 2^mexp) as the pair ms - mc: mexp ln2 in two parts, the first exact (29 bits times
+    // at most 24) so that the pair carries the full product
+    constexpr double L2H = 0x1.62e42ff000000p-1, L2L = -0x1.718432a1b0e26p-35;
+    ms = (double)mexp * L2H;
+    mc = -((double)mexp * L2L + log(mprod));
+  }
   // ---- block reduction: wave transpose-butterfly, then the 4 waves in order
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   __shared__ double red[4][NACC];

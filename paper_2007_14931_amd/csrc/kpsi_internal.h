@@ -25,18 +25,29 @@ __host__ __device__ constexpr int64_t col_at(int k, int64_t e, int64_t ld) {
 
 enum { MODE_DENSITY = 0, MODE_NLL = 1, MODE_GRAD = 2 };
 
-// Per-resonance constants of one call (host-computed in double, stored as T).
+// Per-resonance constants of an interference-matrix build (host-computed in double, stored as T).
 //   den(m) = M2 - m^2 - i P g(m),  A(m) = K n(m) / den(m)
 template <typename T> struct RC {
   T M2, P, K;
   T M2lo;             // M^2 - M2 (FP32 constants: the rounding remainder of M^2; FP64: 0)
-  T hr[3], hi[3];     // K*: lambda = -1, 0, +1; Z: [0] lambda' = 0, [1] lambda' = +-1 (Eq. 11)
-                      // or, free helicities, [1] lambda' = +1 and [2] lambda' = -1
+  T pad0[6];          // (spacing for which the compiler keeps the constants out of spilled registers)
   T kap, twoM, dP, PoG;   // d ln K/dM, 2M, dP/dM, P/Gamma0
   int flt;            // floating slot or -1
-  T f0, f1;           // 1 where flt is 0 (1), else 0
+  T pad1[2];
   int lass;           // 1: LASS S-wave (spin-0 K* only), 0: Breit-Wigner
   T lai, lhb;         // LASS 1/a and b/2: q cot(delta_B) = lai + lhb q^2
+};
+
+// Per-resonance constants of the per-event kernel: eight values, so that one scalar load (32 bytes
+// in FP32, 64 in FP64) brings a resonance.  The couplings are those of the transversity basis the
+// kernel sums in (pack):
+//   K* of spin >= 1: h[0] ~ H_+ - H_-, h[1] ~ H_0, h[2] ~ H_+ + H_-;  spin 0: h[1] ~ H_0
+//   Z: h[0] ~ H'_0, h[1] ~ H'_{+-1} (Eq. 11), or, free helicities, h[1] ~ H'_+1 + H'_-1 and
+//   h[2] ~ H'_+1 - H'_-1
+// each times K and the constant factors of its angular and barrier functions (CoupScale).
+template <typename T> struct alignas(8 * sizeof(T)) AC {
+  T M2, P;
+  T h[3][2];
 };
 
 // Compile-time capacity of a kernel instantiation: K* slots per spin 0..4 and Z slots.
@@ -70,9 +81,12 @@ template <typename T, class Sh> struct AmpArgs {
   int nb_data;          // blocks of the data set; the rest cover the normalisation set
   int chunk;            // events per block
   int cnt[6];           // slots in use per spin 0..4 and Z
-  T rR, rB, invMB;
-  RC<T> ks[Sh::NK > 0 ? Sh::NK : 1];
-  RC<T> zs[Sh::NZ > 0 ? Sh::NZ : 1];
+  T rR2, rB2;           // squared barrier radii
+  AC<T> cs[Sh::NK + Sh::NZ];   // K* slots, then Z slots
+  T M2lo[Sh::NK + Sh::NZ];   // M^2 - M2 (FP32: the rounding remainder of M^2; FP64: 0)
+  T lai[Sh::NK], lhb[Sh::NK];   // LASS 1/a and b/2 of a spin-0 slot: q cot(delta_B) = lai + lhb q^2
+  int lass;             // bit k: K* slot k is a LASS S-wave (spin 0 only)
+  int flt[NFL];         // slot (K* slots, then NK + Z slot) of each floating lineshape, or -1
   // Signal + background mixture (Eq. 14) on the data set, active when bkg_data != null:
   // each data event contributes ln t with t = purity eps_i S_i + k b_i, where
   // k = bkg_coef * sum eps S over the normalisation events (bkg_coef = (1 - p) / (N_b N_MC)).

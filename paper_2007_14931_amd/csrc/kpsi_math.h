@@ -37,9 +37,9 @@ __device__ __forceinline__ double fma_(double a, double b, double c) { return __
 // carried as M2 plus its rounding remainder M2lo: near a narrow pole M^2 - s is far smaller than
 // M^2, and the rounding of M^2 alone would move the pole of every event by the same amount (a
 // shift of 0.5 ulp of M^2 is 1e-3 of the statistical error of a K*(892) mass at 3e6 events).
-template <typename T, typename R> __device__ __forceinline__ T pole_gap(const R& rc, T s) {
-  if constexpr (sizeof(T) == sizeof(float)) return (rc.M2 - s) + rc.M2lo;
-  else return rc.M2 - s;
+template <typename T> __device__ __forceinline__ T pole_gap(T M2, T M2lo, T s) {
+  if constexpr (sizeof(T) == sizeof(float)) return (M2 - s) + M2lo;
+  else return M2 - s;
 }
 
 // Blatt-Weisskopf polynomial B_L(z), z = (r p)^2, in Horner form: the barrier factor of
@@ -59,6 +59,34 @@ template <typename T, int n> __device__ __forceinline__ T ipow(T x) {
 #pragma unroll
   for (int i = 0; i < n; ++i) r *= x;
   return r;
+}
+
+// M^2 - m^2 of a K* from m itself: one fused step leaves only the rounding of the result.
+template <typename T> __device__ __forceinline__ T pole_gap_m(T M2, T M2lo, T m) {
+  if constexpr (sizeof(T) == sizeof(float)) return fma_(-m, m, M2) + M2lo;
+  else return fma_(-m, m, M2);
+}
+
+// The per-event kernel's angular functions: d^J_{00}(theta_K) = E0<J> ang0<J> and d^J_{10}(theta_K) =
+// E1<J> sin ang1<J>, with the constants folded into the couplings on the host.
+template <int J> struct AngScale;
+template <> struct AngScale<0> { static constexpr double E0 = 1.0, E1 = 0.0; };
+template <> struct AngScale<1> { static constexpr double E0 = 1.0, E1 = -0.70710678118654752440; };
+template <> struct AngScale<2> { static constexpr double E0 = 1.0, E1 = -1.22474487139158904910; };
+template <> struct AngScale<3> { static constexpr double E0 = 1.0, E1 = -0.43301270189221932338; };
+template <> struct AngScale<4> { static constexpr double E0 = 0.125, E1 = -0.55901699437494742410; };
+template <int J, typename T> __device__ __forceinline__ T ang0(T c) {
+  if constexpr (J == 0) return T(1);
+  else if constexpr (J == 1) return c;
+  else if constexpr (J == 2) return fma_(T(1.5) * c, c, T(-0.5));
+  else if constexpr (J == 3) return c * fma_(T(2.5) * c, c, T(-1.5));
+  else { const T c2 = c * c; return fma_(c2, fma_(T(35), c2, T(-30)), T(3)); }
+}
+template <int J, typename T> __device__ __forceinline__ T ang1(T c) {
+  if constexpr (J <= 1) return T(1);
+  else if constexpr (J == 2) return c;
+  else if constexpr (J == 3) return fma_(T(5) * c, c, T(-1));
+  else return c * fma_(T(7) * c, c, T(-3));
 }
 
 // d^J_{00}(theta_K) and d^J_{10}(theta_K) (d^J_{-1,0} = -d^J_{10}) as polynomials in cos and sin.

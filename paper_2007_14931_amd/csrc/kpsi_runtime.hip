@@ -19,6 +19,7 @@
 
 #include "kpsi.h"
 #include "kpsi_internal.h"
+#include "kpsi_math.h"
 
 using namespace kpsi;
 
@@ -243,61 +244,103 @@ LsConst lineshape_consts(const kpsi_kinematics& k, const kpsi_resonance& r, doub
   return c;
 }
 
-// The couplings are stored multiplied by the resonance constant K (H' = K H): the per-event
-// kernel evaluates the bare Breit-Wigner and leaves K to the couplings, so its coupling
-// accumulators come out divided by K (undone in kpsi_nll_and_grad).
-template <typename T> void fill_rc(RC<T>& rc, const LsConst& c, const double* hr, const double* hi, int nl, int flt) {
-  rc.M2 = (T)c.M2; rc.P = (T)c.P; rc.K = (T)c.K;
-  rc.M2lo = (T)(c.M2 - (double)rc.M2);
-  for (int l = 0; l < 3; ++l) {
-    rc.hr[l] = (T)(l < nl ? c.K * hr[l] : 0.0);
-    rc.hi[l] = (T)(l < nl ? c.K * hi[l] : 0.0);
-  }
-  rc.kap = (T)c.kap; rc.twoM = (T)c.twoM; rc.dP = (T)c.dP; rc.PoG = (T)c.PoG;
-  rc.flt = flt;
-  rc.f0 = (T)(flt == 0 ? 1 : 0);
-  rc.f1 = (T)(flt == 1 ? 1 : 0);
-  rc.lass = 0;
-  rc.lai = rc.lhb = T(0);
+// Constant factors between a resonance's physical couplings K H and the per-event kernel's
+// couplings h: e0 and e1 for its lambda = 0 and lambda = +-1 terms (the constants of the angular
+// functions and the 1/M_B of each power of p_B; Z: the sqrt2 of the rotated muon amplitudes, and
+// 1/sqrt2 more where two free helicity couplings combine).
+//   K*, spin >= 1: h[0] = e1 (H_+ - H_-)/sqrt2, h[1] = e0 H_0, h[2] = e1 (H_+ + H_-)/sqrt2
+//   K*, spin 0:    h[1] = e0 H_0
+//   Z:             h[0] = sqrt2 H'_0, h[1] = sqrt2 H'_{+-1}
+//   Z, free:       h[0] = sqrt2 H'_0, h[1] = (H'_+1 + H'_-1)/sqrt2, h[2] = (H'_+1 - H'_-1)/sqrt2
+struct CoupScale { double e0, e1; };
+CoupScale coup_scale(const kpsi_kinematics& k, const kpsi_resonance& r) {
+  if (r.chain == 1) return {M_SQRT2, M_SQRT2};
+  constexpr double E0[5] = {AngScale<0>::E0, AngScale<1>::E0, AngScale<2>::E0, AngScale<3>::E0, AngScale<4>::E0};
+  constexpr double E1[5] = {AngScale<0>::E1, AngScale<1>::E1, AngScale<2>::E1, AngScale<3>::E1, AngScale<4>::E1};
+  double f = 1.0;
+  for (int i = 0; i < lowest_lb(r); ++i) f /= k.m_b;
+  return {f * E0[r.spin], f * E1[r.spin] * M_SQRT1_2};
 }
 
-// Pack the canonical parameter vector into kernel arguments.
+// Complex couplings times K of table resonance r at the parameters p: K*, spin >= 1 lambda = -1, 0,
+// +1, spin 0 lambda = 0 at [1]; Z lambda' = 0, +1 (and -1).
+void physical_couplings(const kpsi_resonance& r, double K, const double* p, double* hr, double* hi) {
+  for (int l = 0; l < 3; ++l) hr[l] = hi[l] = 0.0;
+  const int nl = ncoup(r), l0 = r.chain == 0 && r.spin == 0 ? 1 : 0;
+  for (int l = 0; l < nl; ++l) {
+    hr[l0 + l] = K * p[2 * l] * std::cos(p[2 * l + 1]);
+    hi[l0 + l] = K * p[2 * l] * std::sin(p[2 * l + 1]);
+  }
+}
+
+// Per-event kernel constants of one resonance.
+template <typename T>
+void fill_ac(AC<T>& rc, const kpsi_kinematics& k, const kpsi_resonance& r, const LsConst& c, const double* p) {
+  rc.M2 = (T)c.M2;
+  rc.P = (T)c.P;
+  const CoupScale s = coup_scale(k, r);
+  double h[2][3], g[2][3];
+  physical_couplings(r, c.K, p, h[0], h[1]);
+  for (int i = 0; i < 2; ++i) {
+    if (r.chain == 0) {
+      g[i][0] = s.e1 * (h[i][2] - h[i][0]);
+      g[i][1] = s.e0 * h[i][1];
+      g[i][2] = s.e1 * (h[i][2] + h[i][0]);
+    } else {
+      g[i][0] = s.e0 * h[i][0];
+      g[i][1] = r.hel_free ? M_SQRT1_2 * (h[i][1] + h[i][2]) : s.e1 * h[i][1];
+      g[i][2] = r.hel_free ? M_SQRT1_2 * (h[i][1] - h[i][2]) : 0.0;
+    }
+  }
+  for (int l = 0; l < 3; ++l) {
+    rc.h[l][0] = (T)g[0][l];
+    rc.h[l][1] = (T)g[1][l];
+  }
+}
+
+// Pack the canonical parameter vector into the per-event kernel's arguments.
 template <typename T, class Sh> void pack(const kpsi_ctx* c, const double* par, AmpArgs<T, Sh>& a) {
   const int ncr = c->nparams - 2 * (int)c->res.size();
   // K* slots the model leaves empty are still evaluated by the kernel: zero couplings, M^2 = P = 0
-  // (a finite Breit-Wigner), not floating
-  for (int k = 0; k < Sh::NK; ++k) {
-    a.ks[k] = RC<T>{};
-    a.ks[k].flt = -1;
-  }
+  // (a finite Breit-Wigner)
+  for (AC<T>& x : a.cs) x = AC<T>{};
+  for (int k = 0; k < Sh::NK; ++k) a.lai[k] = a.lhb[k] = T(0);
+  for (T& x : a.M2lo) x = T(0);
+  a.lass = 0;
+  for (int& f : a.flt) f = -1;
   for (size_t i = 0; i < c->res.size(); ++i) {
     const kpsi_resonance& r = c->res[i];
-    const double M = par[ncr + 2 * i], G = par[ncr + 2 * i + 1];
-    LsConst lc = lineshape_consts(c->kin, r, M, G);
-    const double* p = par + c->coff[i];
-    double hr[3], hi[3];
-    int nl;
-    if (r.chain == 0) {
-      if (r.spin == 0) {   // only lambda = 0, stored in the middle slot
-        hr[0] = hi[0] = hr[2] = hi[2] = 0.0;
-        hr[1] = p[0] * std::cos(p[1]); hi[1] = p[0] * std::sin(p[1]);
-      } else {
-        for (int l = 0; l < 3; ++l) { hr[l] = p[2 * l] * std::cos(p[2 * l + 1]); hi[l] = p[2 * l] * std::sin(p[2 * l + 1]); }
-      }
-      nl = 3;
-      fill_rc(a.ks[c->slot[i]], lc, hr, hi, nl, c->fslot[i]);
-      if (r.shape == 1) {
-        RC<T>& rc = a.ks[c->slot[i]];
-        rc.lass = 1;
-        rc.lai = (T)(1.0 / r.lass_a);
-        rc.lhb = (T)(0.5 * r.lass_b);
-      }
-    } else {
-      // lambda' = 0, +1 (standing for +-1 through Eq. 11), and -1 when the helicities are free
-      nl = ncoup(r);
-      for (int l = 0; l < nl; ++l) { hr[l] = p[2 * l] * std::cos(p[2 * l + 1]); hi[l] = p[2 * l] * std::sin(p[2 * l + 1]); }
-      fill_rc(a.zs[c->slot[i]], lc, hr, hi, nl, c->fslot[i]);
+    const LsConst lc = lineshape_consts(c->kin, r, par[ncr + 2 * i], par[ncr + 2 * i + 1]);
+    const int slot = (r.chain == 0 ? 0 : Sh::NK) + c->slot[i];
+    fill_ac(a.cs[slot], c->kin, r, lc, par + c->coff[i]);
+    a.M2lo[slot] = (T)(lc.M2 - (double)a.cs[slot].M2);
+    if (r.shape == 1) {
+      a.lass |= 1 << slot;
+      a.lai[slot] = (T)(1.0 / r.lass_a);
+      a.lhb[slot] = (T)(0.5 * r.lass_b);
     }
+    if (c->fslot[i] >= 0) a.flt[c->fslot[i]] = slot;
+  }
+  a.zfree = c->zfree ? 1 : 0;
+  for (int j = 0; j < 6; ++j) a.cnt[j] = c->cnt[j];
+  a.rR2 = (T)(c->kin.r_r * c->kin.r_r);
+  a.rB2 = (T)(c->kin.r_b * c->kin.r_b);
+}
+
+// Constants of an interference-matrix build.
+template <typename T, class Sh> void pack_im(const kpsi_ctx* c, const double* par, ImArgs<T, Sh>& a) {
+  const int ncr = c->nparams - 2 * (int)c->res.size();
+  for (size_t i = 0; i < c->res.size(); ++i) {
+    const kpsi_resonance& r = c->res[i];
+    const LsConst lc = lineshape_consts(c->kin, r, par[ncr + 2 * i], par[ncr + 2 * i + 1]);
+    RC<T>& rc = r.chain == 0 ? a.ks[c->slot[i]] : a.zs[c->slot[i]];
+    rc.M2 = (T)lc.M2; rc.P = (T)lc.P; rc.K = (T)lc.K;
+    rc.M2lo = (T)(lc.M2 - (double)rc.M2);
+    rc.kap = (T)lc.kap; rc.twoM = (T)lc.twoM; rc.dP = (T)lc.dP; rc.PoG = (T)lc.PoG;
+    rc.flt = c->fslot[i];
+    rc.lass = r.shape == 1 ? 1 : 0;
+    rc.lai = r.shape == 1 ? (T)(1.0 / r.lass_a) : T(0);
+    rc.lhb = r.shape == 1 ? (T)(0.5 * r.lass_b) : T(0);
   }
   a.zfree = c->zfree ? 1 : 0;
   for (int j = 0; j < 6; ++j) a.cnt[j] = c->cnt[j];
@@ -321,6 +364,52 @@ int shape_counts(int shape, int* N, int* NZ) {
   if (shape == 0) { int n[5] = {0, 1, 0, 0, 0}; for (int j = 0; j < 5; ++j) N[j] = n[j]; *NZ = 0; }
   else { int n[5] = {3, 3, 2, 1, 1}; for (int j = 0; j < 5; ++j) N[j] = n[j]; *NZ = 2; }
   return 0;
+}
+
+// From the per-event kernel's gradient record (sums over its couplings h and the lineshape sums
+// of flt_sums) to the form the gradient is assembled from: d/dH' of the physical couplings
+// H' = K H in their helicity order, and d/dM, d/dGamma0 per floating slot, in place.
+void finish_record(const kpsi_ctx* c, const double* par, double* rec) {
+  int N[5], NZ;
+  shape_counts(c->shape, N, &NZ);
+  int nkacc = 0;
+  for (int j = 0; j < 5; ++j) nkacc += N[j] * (j == 0 ? 2 : 6);
+  const int ncr = c->nparams - 2 * (int)c->res.size();
+  for (size_t i = 0; i < c->res.size(); ++i) {
+    const kpsi_resonance& r = c->res[i];
+    double* v = rec + acc_offset(c, i, N);
+    const CoupScale s = coup_scale(c->kin, r);
+    const int nl = ncoup(r);
+    for (int q = 0; q < 2; ++q) {   // real and imaginary parts
+      if (r.chain == 0 && r.spin == 0) {
+        v[q] *= s.e0;
+      } else if (r.chain == 0) {
+        const double gp = s.e1 * v[q], gm = s.e1 * v[4 + q];
+        v[q] = gm - gp;        // lambda = -1
+        v[2 + q] *= s.e0;
+        v[4 + q] = gm + gp;    // lambda = +1
+      } else {
+        v[q] *= s.e0;
+        if (r.hel_free) {
+          const double gs = M_SQRT1_2 * v[2 + q], gd = M_SQRT1_2 * v[4 + q];
+          v[2 + q] = gs + gd;
+          v[4 + q] = gs - gd;
+        } else {
+          v[2 + q] *= s.e1;
+        }
+      }
+    }
+    if (c->fslot[i] < 0) continue;
+    const LsConst lc = lineshape_consts(c->kin, r, par[ncr + 2 * i], par[ncr + 2 * i + 1]);
+    const int l0 = r.chain == 0 && r.spin == 0 ? 1 : 0;
+    double hr[3], hi[3], sx = 0.0;   // sx = sum Re X = Re sum_lambda H'_lambda dS/dH'_lambda
+    physical_couplings(r, lc.K, par + c->coff[i], hr, hi);
+    for (int l = 0; l < nl; ++l) sx += hr[l0 + l] * v[2 * l] - hi[l0 + l] * v[2 * l + 1];
+    double* f = rec + 3 + nkacc + 4 * NZ + 2 * c->fslot[i];
+    const double sR = f[0], sI = f[1];
+    f[0] = lc.kap * sx - lc.twoM * sR - lc.dP * sI;
+    f[1] = -lc.PoG * sI;
+  }
 }
 
 kpsi_status ensure_partial(kpsi_ctx* c, size_t nblocks) {
@@ -540,24 +629,16 @@ kpsi_status gram_build_t(kpsi_ctx* c, const double* par, bool with_eps, bool wit
     if (hipMalloc(&c->cache_out, nv * sizeof(double)) != hipSuccess) return fail(c, KPSI_E_OOM, "cache output");
     c->cache_out_cap = nv;
   }
-  AmpArgs<T, Sh> pa{};
-  pack<T, Sh>(c, par, pa);
   ImArgs<T, Sh> a{};
+  pack_im<T, Sh>(c, par, a);
   a.cols = (const T*)d.cols;
   a.ld = d.ld;
   a.n = d.n;
   a.eps = with_eps ? (const T*)c->eps : (const T*)c->wcol;   // wcol: importance weights or null
   a.partial = c->cache_partial;
   a.ncols = ncols;
-  a.zfree = c->zfree ? 1 : 0;
   a.skip_last = (NT > 1 && 16 * (NT - 1) >= 2 * ncomp) ? 1 : 0;
-  for (int j = 0; j < 6; ++j) a.cnt[j] = pa.cnt[j];
   for (int f = 0; f < NFL; ++f) a.dcol[f] = dcol[f];
-  a.rR = pa.rR; a.rB = pa.rB; a.invMB = pa.invMB;
-  for (int k = 0; k < (Sh::NK > 0 ? Sh::NK : 1); ++k) a.ks[k] = pa.ks[k];
-  for (int k = 0; k < (Sh::NZ > 0 ? Sh::NZ : 1); ++k) {
-    a.zs[k] = pa.zs[k];
-  }
   if (!with_deriv) {   // no derivative columns: every lineshape counts as fixed in this matrix
     for (int k = 0; k < (Sh::NK > 0 ? Sh::NK : 1); ++k) a.ks[k].flt = -1;
     for (int k = 0; k < (Sh::NZ > 0 ? Sh::NZ : 1); ++k) a.zs[k].flt = -1;
@@ -1582,9 +1663,14 @@ kpsi_status kpsi_nll(kpsi_ctx* c, const double* params, double* nll) {
 // -2 ln L and its gradient from the reduced records of a gradient-mode pass (the normalisation
 // record from the interference matrix when `cached`).
 static kpsi_status assemble_grad(kpsi_ctx* c, const double* params, bool cached, double* nll, double* grad) {
-  const double* rd = c->red_host;
-  const double* rm = c->red_host + NACC;
-  const double* rm2 = c->red_host + 2 * NACC;
+  double* rd = c->red_host;
+  double* rm = c->red_host + NACC;
+  double* rm2 = c->red_host + 2 * NACC;
+  finish_record(c, params, rd);
+  if (!cached) {
+    finish_record(c, params, rm);
+    if (c->cc_on) finish_record(c, params, rm2);
+  }
   const double nd = (double)c->set[0].n;
   for (int i = 0; i < c->nparams; ++i) grad[i] = NAN;
   // combined complex sensitivity G = -2 G_data + c1 G_norm1 (+ c2 G_norm2 with flavour tags):
