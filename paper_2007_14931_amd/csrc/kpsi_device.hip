@@ -440,7 +440,18 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
   };
   constexpr bool PRE = GRAD && std::is_same_v<T, double>;
   if (PRE && threadIdx.x < n_blk) fetch(threadIdx.x);
+  // Wavefronts further from their block's end issue first.  Left to the hardware, the oldest ready
+  // wavefront issues first, so of the blocks sharing a compute unit (all with the same number of
+  // events) one ends early and the last runs with idle issue slots: on average 3.5 of 4 (FP32) and
+  // 1.7 of 2 (FP64) wavefronts per SIMD were left.  Lowering a wavefront's priority as it nears its end
+  // lets the others catch up.
+  __builtin_amdgcn_s_setprio(3);
+  uint32_t left = (n_blk + 255) / 256;   // passes of this block still to do
   for (uint32_t i = threadIdx.x; i < n_blk; i += 256) {
+    if (left == 6) __builtin_amdgcn_s_setprio(2);
+    else if (left == 3) __builtin_amdgcn_s_setprio(1);
+    else if (left == 1) __builtin_amdgcn_s_setprio(0);
+    --left;
     const int64_t e = e0 + i;
     const uint32_t ob = i * (uint32_t)sizeof(T);
     const auto& ka = *kernarg_laundered<AmpArgs<T, Sh>>();
