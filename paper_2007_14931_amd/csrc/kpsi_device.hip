@@ -346,8 +346,9 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
   const int64_t n = a.n[src];
   const T* __restrict__ col = a.cols[src];
   const int64_t ld = a.ld[src];
-  const int64_t e0 = blk * (int64_t)a.chunk;
-  const int64_t e1 = (e0 + a.chunk < n) ? e0 + a.chunk : n;
+  const int64_t e0 = (int64_t)(((uint64_t)blk * a.step[src]) >> 32) * 256;
+  const int64_t e2 = (int64_t)(((uint64_t)(blk + 1) * a.step[src]) >> 32) * 256;
+  const int64_t e1 = (blk + 1 < (src == 0 ? a.nb_data : a.nb_mc) && e2 < n) ? e2 : n;
 
   double ms = 0.0, mc = 0.0;   // Kahan pair
   double mprod = 1.0;          // data: product of the terms as mprod 2^mexp
