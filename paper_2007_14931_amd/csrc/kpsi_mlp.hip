@@ -37,6 +37,68 @@ __device__ __forceinline__ float dsilu(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
+// silu with a correctly rounded quotient.  With y the correctly rounded 1/d (the hardware's value,
+// one Newton step), one correction of q = z y gives the IEEE quotient: the steps of the division
+// without its scaling of extreme operands, which d >= 1 needs only where it is huge.  There it is
+// held at 2^100 (z < -69: the result is below 1e-28 in size either way).
+__device__ __forceinline__ float sig_den(float z) { return fminf(1.0f + __expf(-z), 0x1p100f); }
+__device__ __forceinline__ float silu_rn(float z) {
+  const float d = sig_den(z), y0 = __builtin_amdgcn_rcpf(d);
+  const float y = __builtin_fmaf(__builtin_fmaf(-d, y0, 1.0f), y0, y0);
+  const float q = z * y;
+  return __builtin_fmaf(__builtin_fmaf(-d, q, z), y, q);
+}
+// The same where the value is rounded to BF16 at once: without the Newton step the quotient is
+// correctly rounded but for about one value in 2^20, by one FP32 unit in the last place.
+__device__ __forceinline__ float silu_bf(float z) {
+  const float d = sig_den(z), y = __builtin_amdgcn_rcpf(d);
+  const float q = z * y;
+  return __builtin_fmaf(__builtin_fmaf(-d, q, z), y, q);
+}
+// Sum over the 16 lanes of a row, in every lane (quad permutations, then the mirrored half rows and
+// rows: their lanes hold equal values by then).
+template <int CTRL> __device__ __forceinline__ float dpp(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float row_sum(float x) {
+  x += dpp<0xB1>(x);
+  x += dpp<0x4E>(x);
+  x += dpp<0x141>(x);
+  return x + dpp<0x140>(x);
+}
+// Eight consecutive FP32 weights (16-byte aligned) as a BF16 operand.
+__device__ __forceinline__ bf8_t to_bf8(const float* p) {
+  const f4_t lo = *reinterpret_cast<const f4_t*>(p), hi = *reinterpret_cast<const f4_t*>(p + 4);
+  bf8_t v;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    v[j] = (__bf16)lo[j];
+    v[4 + j] = (__bf16)hi[j];
+  }
+  return v;
+}
+// Input layer in registers, for the features f(c) = 32 (c / 8) + 8 lg + c % 8 of a lane (the order
+// of the matrix cores' operands); W1 rounded to BF16 like W2.
+struct L1Weights {
+  float w[16][4], b[16];
+  __device__ __forceinline__ void load(const float* params, int lg) {
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      const int f = 32 * (c >> 3) + 8 * lg + (c & 7);
+      const f4_t v = *reinterpret_cast<const f4_t*>(params + P_W1 + 4 * f);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) w[c][k] = from_bf16(bf16(v[k]));
+      b[c] = params[P_B1 + f];
+    }
+  }
+  __device__ __forceinline__ float z(int c, const float* u) const {
+    float x = b[c];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x = __builtin_fmaf(w[c][k], u[k], x);
+    return x;
+  }
+};
+
 struct __align__(16) Smem {
   unsigned short W2[64 * 64];    // [o][i] bf16 (W2 and W2T adjacent: staged as one copy)
   unsigned short W2T[64 * 64];   // [i][o] bf16
@@ -67,8 +129,7 @@ __device__ __forceinline__ f4_t mm16x64(const unsigned short* a, const unsigned 
   return acc;
 }
 
-__device__ __forceinline__ float input_of(const MlpArgs& a, int k, int64_t e) {
-  const double x = a.obs[k][e];
+__device__ __forceinline__ float input_map(const MlpArgs& a, int k, double x) {
   if (k == 0) return (float)(2.0 * (x - a.lo) / (a.hi - a.lo) - 1.0);
   if (k == 3) return (float)(x * 0.31830988618379067154);
   return (float)x;
@@ -98,7 +159,7 @@ __device__ void forward_tile(const MlpArgs& a, Smem& s, int64_t e0, f4_t z2[4]) 
     const int64_t e = e0 + t;
     const bool ok = e < a.n;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) s.U[t * 4 + k] = ok ? input_of(a, k, e) : 0.0f;
+    for (int k = 0; k < 4; ++k) s.U[t * 4 + k] = ok ? input_map(a, k, a.obs[k][e]) : 0.0f;
     s.Y[t] = (ok && a.label) ? (float)a.label[e] : 0.0f;
   }
   __syncthreads();
@@ -327,35 +388,72 @@ __global__ __launch_bounds__(256) void adam_kernel(float* p, float* m, float* v,
 }
 
 // Probabilities of the network for n events.
-__global__ __launch_bounds__(256) void mlp_eval_kernel(MlpArgs a) {
+//
+// One wavefront takes 64 events at a time, with no LDS and no barrier: lane l evaluates the input
+// layer for event l % 16 of a group of 16 and the features 32 kk + 8 (l / 16) + j, which is the
+// layout in which the matrix cores read them as the A operand, and the weights of all layers stay
+// in registers over the events of the wavefront.  Bound by the vector instructions of the 128
+// sigmoids per event: 148 us per call for 2e6 events.  (335 us with the layers passed through LDS
+// by a workgroup per 64 events, a barrier between them, whole IEEE divisions and the double
+// exponential of four events per 16 lanes evaluated in each of them.)
+__global__ __launch_bounds__(256, 2) void mlp_eval_kernel(MlpArgs a) {
   using namespace nn;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  Smem& s = *reinterpret_cast<Smem*>(smem_raw);
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6, l16 = lane & 15, lg = lane >> 4;
-  stage_weights(a, s);
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
+  L1Weights w1;
+  w1.load(a.params, lg);
+  bf8_t w2[4][2];   // W2[16 nt + l16][32 kk + 8 lg + j]
+  float b2[4], w3[4];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    const int o = 16 * nt + l16;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) w2[nt][kk] = to_bf8(a.params + P_W2 + 64 * o + 32 * kk + 8 * lg);
+    b2[nt] = a.params[P_B2 + o];
+    w3[nt] = from_bf16(bf16(a.params[P_W3 + o]));
+  }
   const float b3 = a.params[P_B3];
-  __syncthreads();
-  const int64_t begin = (int64_t)blockIdx.x * a.per_block;
-  const int64_t end = begin + a.per_block < a.n ? begin + a.per_block : a.n;
-  for (int64_t e0 = begin; e0 < end; e0 += TE) {
-    f4_t z2[4];
-    forward_tile(a, s, e0, z2);
-    float z3p[4] = {0.f, 0.f, 0.f, 0.f};
+  const int64_t tiles = (a.n + 63) / 64, stride = (int64_t)gridDim.x * 4;
+  int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  double x[4] = {0.0, 0.0, 0.0, 0.0};   // observables of event 64 tile + lane
+  auto fetch = [&](int64_t t) {
+    const int64_t e = 64 * t + lane;
+    if (e < a.n) {
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const int o = 16 * nt + l16;
-      const float bb = s.B2[o], ww = s.W3[o];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) z3p[r] += ww * silu(z2[nt][r] + bb);
+      for (int k = 0; k < 4; ++k) x[k] = a.obs[k][e];
     }
+  };
+  if (tile < tiles) fetch(tile);
+  for (; tile < tiles; tile += stride) {
+    float u[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int k = 0; k < 4; ++k) u[k] = input_map(a, k, x[k]);
+    if (tile + stride < tiles) fetch(tile + stride);
+    float z3 = 0.f;   // of event 16 (l16 / 4) + 4 lg + l16 % 4
+#pragma unroll 1
+    for (int mt = 0; mt < 4; ++mt) {
+      float um[4];
 #pragma unroll
-      for (int off = 1; off < 16; off <<= 1) z3p[r] += __shfl_xor(z3p[r], off, 64);
-      const int64_t e = e0 + 16 * w + 4 * lg + r;
-      if (l16 == 0 && e < end) a.out[e] = 1.0 / (1.0 + exp(-(double)(z3p[r] + b3)));
+      for (int k = 0; k < 4; ++k) um[k] = __shfl(u[k], 16 * mt + l16, 64);
+      bf8_t h[2];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) h[c >> 3][c & 7] = (__bf16)silu_bf(w1.z(c, um));
+      float z3p[4] = {0.f, 0.f, 0.f, 0.f};   // events 4 lg + r of the group
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) {
+        f4_t z2 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) z2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h[kk], w2[nt][kk], z2, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z3p[r] += w3[nt] * silu_rn(z2[r] + b2[nt]);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) z3p[r] = row_sum(z3p[r]);
+      const float lo = (l16 & 1) ? z3p[1] : z3p[0], hi = (l16 & 1) ? z3p[3] : z3p[2];
+      const float v = (l16 & 2) ? hi : lo;
+      z3 = (l16 >> 2) == mt ? v : z3;
     }
-    __syncthreads();
+    const int64_t e = 64 * tile + 16 * (l16 >> 2) + 4 * lg + (l16 & 3);
+    if (e < a.n) a.out[e] = 1.0 / (1.0 + exp(-(double)(z3 + b3)));
   }
 }
 
@@ -447,7 +545,7 @@ hipError_t launch_adam(float* p, float* m, float* v, const double* g, int n, flo
   return hipGetLastError();
 }
 hipError_t launch_mlp_eval(const MlpArgs& a, int nb, hipStream_t st) {
-  hipLaunchKernelGGL(mlp_eval_kernel, dim3(nb), dim3(256), sizeof(nn::Smem), st, a);
+  hipLaunchKernelGGL(mlp_eval_kernel, dim3(nb), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 hipError_t launch_labels(const LabelArgs& a, hipStream_t st) {

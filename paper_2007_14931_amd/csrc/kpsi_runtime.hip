@@ -2256,11 +2256,9 @@ static hipError_t mlp_eval_device(kpsi_ctx* c, const float* dparams, int64_t n, 
   MlpArgs a = mlp_args(c, n, m, ck, cj, phi);
   a.params = dparams;
   a.out = out;
-  if (hipError_t e = prep_w2h(c, dparams)) return e;
-  a.w2h = c->mlp_w2h;
+  // one resident round: two blocks of four wavefronts per compute unit, 64 events a wavefront
   const int64_t tiles = (n + 63) / 64;
-  const int nb = (int)std::min<int64_t>(tiles, 2048);
-  a.per_block = (tiles + nb - 1) / nb * 64;
+  const int nb = (int)std::min<int64_t>((tiles + 3) / 4, 2 * (c->n_cu > 0 ? c->n_cu : 256));
   return launch_mlp_eval(a, nb, c->stream);
 }
 

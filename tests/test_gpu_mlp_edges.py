@@ -1,0 +1,57 @@
+"""Network evaluation at the edges of its tiles (64 events per wavefront, 256 per block, one resident
+round of blocks) and at saturated units, against the FP64 reference network with the same BF16
+rounding points."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2007_14931_amd import kpsi
+from paper_2007_14931_amd import workloads as W
+from parity_bars import check_probabilities
+
+pytestmark = pytest.mark.gpu
+
+
+def _engine():
+    e = kpsi.Engine(0, "fp32")
+    e.set_model(W.KIN, W.model("kstar892"))
+    return e
+
+
+def _cuda(ev):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(ev)).to("cuda:0")
+
+
+def _par(seed):
+    rng = np.random.default_rng(seed)
+    par = W.mlp_init(seed)
+    par[256:320] = rng.normal(0, 0.3, 64)
+    par[4416:4480] = rng.normal(0, 0.3, 64)
+    return par
+
+
+# 64 x 4 x 512 = 131072 events are one pass of every wavefront of 2 x 256 blocks
+@pytest.mark.parametrize("n", [1, 63, 65, 257, 131_072, 131_137])
+def test_evaluation_at_tile_edges(n):
+    ev = W.neutral_events(n, 77)
+    p = _engine().mlp_eval(_par(4), _cuda(ev)).cpu().numpy()
+    u = O.mlp_inputs(W.M_LO, W.M_HI, ev)
+    _, ref, _ = O.mlp(_par(4).astype(np.float64), u)
+    check_probabilities(p, ref, _par(4), u)
+
+
+def test_evaluation_with_saturated_units_and_a_nan_event():
+    par = _par(5)
+    # exp(-z) runs from underflow over the largest finite float (z = -88.7) to infinity
+    par[256:320] = np.linspace(-140.0, 140.0, 64)
+    par[4416:4480] = np.linspace(110.0, -110.0, 64)
+    par[4480:4544] *= 0.01
+    ev = W.neutral_events(200, 78)
+    p = _engine().mlp_eval(par, _cuda(ev)).cpu().numpy()
+    u = O.mlp_inputs(W.M_LO, W.M_HI, ev)
+    _, ref, _ = O.mlp(par.astype(np.float64), u)
+    check_probabilities(p, ref, par, u)
+    ev[1, 70] = np.nan
+    q = _engine().mlp_eval(par, _cuda(ev)).cpu().numpy()
+    assert np.isnan(q[70]) and np.array_equal(np.delete(q, 70), np.delete(p, 70))
