@@ -205,6 +205,15 @@ struct MlpArgs {
   int64_t n, per_block;
 };
 
+// One Adam step: parameters p and moments m, v (4545 each), the BF16 copies w2h of the 64x64 layer, and
+// where the batch's mean loss goes.
+struct AdamArgs {
+  float *p, *m, *v;
+  unsigned short* w2h;
+  double* loss;
+  float lr, b1, b2, eps, c1, c2;   // c1, c2: bias corrections of the moments
+};
+
 struct LabelArgs {
   const double* obs[4];
   uint64_t seed;
@@ -225,12 +234,11 @@ struct HistCountArgs {
   unsigned int* acc;
 };
 
-size_t mlp_smem_bytes();
 hipError_t launch_mlp_bf16(const float* params, unsigned short* w2h, hipStream_t st);
 hipError_t launch_mlp_grad(const MlpArgs& a, int nb, hipStream_t st);
-hipError_t launch_mlp_reduce(const float* partial, int nb, int nv, double scale, double* out, hipStream_t st);
-hipError_t launch_adam(float* p, float* m, float* v, const double* g, int n, float lr, float b1, float b2, float eps,
-                       float c1, float c2, unsigned short* w2h, hipStream_t st);
+// The summed block records times scale: into out, or, with ad, through an Adam step of the parameters.
+hipError_t launch_mlp_reduce(const float* partial, int nb, int nv, double scale, double* out, const AdamArgs* ad,
+                             hipStream_t st);
 hipError_t launch_mlp_eval(const MlpArgs& a, int nb, hipStream_t st);
 hipError_t launch_labels(const LabelArgs& a, hipStream_t st);
 hipError_t launch_hist_count(const HistCountArgs& a, hipStream_t st);

@@ -22,6 +22,7 @@ constexpr int P_W1 = 0, P_B1 = 256, P_W2 = 320, P_B2 = 4416, P_W3 = 4480, P_B3 =
 constexpr int TE = 64;   // events per tile
 
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf4_t __attribute__((ext_vector_type(4)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
 
 // float -> bf16 bits, round to nearest even (finite inputs)
@@ -30,13 +31,6 @@ __device__ __forceinline__ unsigned short bf16(float f) {
   u += 0x7fffu + ((u >> 16) & 1u);
   return (unsigned short)(u >> 16);
 }
-__device__ __forceinline__ float from_bf16(unsigned short h) { return __uint_as_float((uint32_t)h << 16); }
-__device__ __forceinline__ float silu(float z) { return z / (1.0f + __expf(-z)); }
-__device__ __forceinline__ float dsilu(float z) {
-  const float s = 1.0f / (1.0f + __expf(-z));
-  return s * (1.0f + z * (1.0f - s));
-}
-
 // silu with a correctly rounded quotient.  With y the correctly rounded 1/d (the hardware's value,
 // one Newton step), one correction of q = z y gives the IEEE quotient: the steps of the division
 // without its scaling of extreme operands, which d >= 1 needs only where it is huge.  There it is
@@ -48,7 +42,16 @@ __device__ __forceinline__ float silu_rn(float z) {
   const float q = z * y;
   return __builtin_fmaf(__builtin_fmaf(-d, q, z), y, q);
 }
-// The same where the value is rounded to BF16 at once: without the Newton step the quotient is
+// silu and silu' = s (1 + z (1 - s)) with the correctly rounded sigmoid s = 1/d
+__device__ __forceinline__ void silu_both(float z, float& sl, float& ds) {
+  const float d = sig_den(z), y0 = __builtin_amdgcn_rcpf(d);
+  const float y = __builtin_fmaf(__builtin_fmaf(-d, y0, 1.0f), y0, y0);
+  const float s = __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
+  const float q = z * s;
+  sl = __builtin_fmaf(__builtin_fmaf(-d, q, z), s, q);
+  ds = s * __builtin_fmaf(z, 1.0f - s, 1.0f);
+}
+// silu where the value is rounded to BF16 at once: without the Newton step the quotient is
 // correctly rounded but for about one value in 2^20, by one FP32 unit in the last place.
 __device__ __forceinline__ float silu_bf(float z) {
   const float d = sig_den(z), y = __builtin_amdgcn_rcpf(d);
@@ -87,7 +90,7 @@ struct L1Weights {
       const int f = 32 * (c >> 3) + 8 * lg + (c & 7);
       const f4_t v = *reinterpret_cast<const f4_t*>(params + P_W1 + 4 * f);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) w[c][k] = from_bf16(bf16(v[k]));
+      for (int k = 0; k < 4; ++k) w[c][k] = (float)(__bf16)v[k];
       b[c] = params[P_B1 + f];
     }
   }
@@ -99,34 +102,50 @@ struct L1Weights {
   }
 };
 
+// Row strides of the LDS tiles: 16-byte rows for the vector accesses, and rows 4 and 8 apart start
+// in other banks.
+constexpr int SF = 68, SH = 72;
 struct __align__(16) Smem {
-  unsigned short W2[64 * 64];    // [o][i] bf16 (W2 and W2T adjacent: staged as one copy)
-  unsigned short W2T[64 * 64];   // [i][o] bf16
-  unsigned short H1[TE * 64];    // [e][i]
-  unsigned short H1T[64 * TE];   // [i][e]
-  unsigned short DZ[TE * 64];    // [e][o]
-  unsigned short DZT[64 * TE];   // [o][e]
-  float U[TE * 4];
-  float Y[TE];
-  float W1[256], B1[64], B2[64], W3[64];
-  float red[256];
+  float D1[TE * SF];                // silu'(z1) [event][feature]
+  unsigned short H1[2][TE * SH];    // h1 [event][feature]
+  unsigned short DZT[2][64 * SH];   // dz2 [output][event]
+  f4_t U[TE];                       // network inputs
+  float red[4][28 * 16];            // per-wavefront sums of the thin layers
+  float sc[4][2];                   // and of b3 and the loss
 };
 
 // eight consecutive bf16 of an LDS row (16-byte aligned) as an MFMA operand: one 16-byte read
 __device__ __forceinline__ bf8_t ld8(const unsigned short* p) { return *reinterpret_cast<const bf8_t*>(p); }
 
-// One 64 x 64 x (64 deep) product tile row for the wave: acc += A[16 rows][64] B[64][16 cols], with
-// A's rows at a + 64 * (lane % 16) and B's columns at b + 64 * (lane % 16) (both row-major in k).
-// Lane l supplies A[l % 16][8 (l / 16) + j] and B[8 (l / 16) + j][l % 16] for each 32-deep half.
-__device__ __forceinline__ f4_t mm16x64(const unsigned short* a, const unsigned short* b, int l16, int lg) {
-  f4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
-    const bf8_t av = ld8(a + 64 * l16 + 32 * kk + 8 * lg);
-    const bf8_t bv = ld8(b + 64 * l16 + 32 * kk + 8 * lg);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc, 0, 0, 0);
-  }
-  return acc;
+// Four values down the column (lane % 16) of the 4 x 16 block of 16-bit values whose rows start at p
+// in steps of `stride`, for each group of 16 lanes its own block: the transposing LDS read, for which
+// lane t of a group passes row t / 4, columns 4 (t % 4) on.
+typedef short s4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ s4_t ld4t(const unsigned short* p, int stride, int l16) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) s4_t*)(p + stride * (l16 >> 2) + 4 * (l16 & 3)));
+}
+// Operand whose eight k values are the rows 0..7 of such a block.
+__device__ __forceinline__ bf8_t ld8t(const unsigned short* p, int stride, int l16) {
+  const s4_t lo = ld4t(p, stride, l16), hi = ld4t(p + 4 * stride, stride, l16);
+  return __builtin_bit_cast(bf8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+// Orders the LDS accesses of one wavefront's lanes (they execute in order; this holds the compiler).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// a and b, c and d summed over the four 16-lane rows as (row 0 + row 1) + (row 2 + row 3): row k of
+// the result holds the sum of the k-th value.
+__device__ __forceinline__ float rows_sum4(float a, float b, float c, float d) {
+  auto pair = [](float x, float y, auto f) {
+    const auto r = f(__float_as_uint(x), __float_as_uint(y));
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  };
+  auto s16 = [](unsigned x, unsigned y) { return __builtin_amdgcn_permlane16_swap(x, y, false, false); };
+  auto s32 = [](unsigned x, unsigned y) { return __builtin_amdgcn_permlane32_swap(x, y, false, false); };
+  return pair(pair(a, b, s16), pair(c, d, s16), s32);
 }
 
 __device__ __forceinline__ float input_map(const MlpArgs& a, int k, double x) {
@@ -135,65 +154,54 @@ __device__ __forceinline__ float input_map(const MlpArgs& a, int k, double x) {
   return (float)x;
 }
 
-// Stage weights into LDS: the BF16 copies of W2 in both layouts (8192 values, from w2h), and the
-// FP32 small layers (W1 and w3 rounded to BF16 like W2).
-__device__ void stage_weights(const MlpArgs& a, Smem& s) {
-  const uint4* src = reinterpret_cast<const uint4*>(a.w2h);
-  uint4* dst = reinterpret_cast<uint4*>(s.W2);
-  for (int i = threadIdx.x; i < 2 * 4096 * 2 / 16; i += 256) dst[i] = src[i];
-  for (int i = threadIdx.x; i < 256; i += 256) s.W1[i] = from_bf16(bf16(a.params[P_W1 + i]));
-  if (threadIdx.x < 64) {
-    s.B1[threadIdx.x] = a.params[P_B1 + threadIdx.x];
-    s.B2[threadIdx.x] = a.params[P_B2 + threadIdx.x];
-    s.W3[threadIdx.x] = from_bf16(bf16(a.params[P_W3 + threadIdx.x]));
-  }
-}
-
-// Forward over one tile of 64 events starting at e0 (rows past n are zero-filled).
-// Leaves the inputs and h1 (both layouts) in LDS, returns in z2[nt][r] this lane's 16 values of
-// z2 for events 16 w + 4 (lane/16) + r and outputs 16 nt + lane % 16.
-__device__ void forward_tile(const MlpArgs& a, Smem& s, int64_t e0, f4_t z2[4]) {
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  // inputs and labels
-  if (t < TE) {
-    const int64_t e = e0 + t;
-    const bool ok = e < a.n;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) s.U[t * 4 + k] = ok ? input_map(a, k, a.obs[k][e]) : 0.0f;
-    s.Y[t] = (ok && a.label) ? (float)a.label[e] : 0.0f;
-  }
-  __syncthreads();
-  // layer 1 (VALU): thread t -> event t % 64, features 16 (t / 64) .. + 15
-  {
-    const int e = t & 63, j0 = (t >> 6) * 16;
-    const float u0 = s.U[e * 4], u1 = s.U[e * 4 + 1], u2 = s.U[e * 4 + 2], u3 = s.U[e * 4 + 3];
-#pragma unroll
-    for (int j = j0; j < j0 + 16; ++j) {
-      const float z = s.B1[j] + s.W1[4 * j] * u0 + s.W1[4 * j + 1] * u1 + s.W1[4 * j + 2] * u2 + s.W1[4 * j + 3] * u3;
-      const unsigned short h = bf16(silu(z));
-      s.H1[e * 64 + j] = h;
-      s.H1T[j * TE + e] = h;
-    }
-  }
-  __syncthreads();
-  // layer 2 (MFMA): wave w computes events 16 w .. 16 w + 15 for all 64 outputs:
-  // A[m = event][k = input] = h1 (rows of H1), B[k = input][n = output] = W2[output][input]
-  const int l16 = lane & 15, lg = lane >> 4;
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) z2[nt] = mm16x64(&s.H1[(16 * w) * 64], &s.W2[(16 * nt) * 64], l16, lg);
-}
-
 }  // namespace nn
 
 // Per-block gradient of the summed BCE (no 1/n) over the events [blk*per, (blk+1)*per),
 // written block-major to partial[block * 4546 + v] (one contiguous record per block, so the
 // writes are coalesced); v = 4545 is the loss.
-__global__ __launch_bounds__(256) void mlp_grad_kernel(MlpArgs a) {
+//
+// A block takes 64 events at a time, wavefront w the events 16 w .. 16 w + 15 of them.  The input
+// layer is computed in the operand layout of the matrix cores (as in mlp_eval_kernel), the weights
+// stay in registers, and each sigmoid is evaluated once for both silu and silu'.  LDS carries what
+// changes hands: silu' of the first layer within the wavefront, and h1 and dz2, between the
+// wavefronts, for the weight gradient, which contracts over all 64 events; these are read back
+// transposed.  One barrier per 64 events (two buffers).  Bound by the latency of a step that has
+// 128 events per compute unit (the weights, the chain of layers, the records): 24.9 -> GRAD_NOW us
+// for 32768 events (the weights staged through LDS by every block, 128-byte LDS rows, three
+// barriers per 64 events and 60 at the end, each sigmoid evaluated three times).
+__global__ __launch_bounds__(256, 1) void mlp_grad_kernel(MlpArgs a) {
   using namespace nn;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  Smem& s = *reinterpret_cast<Smem*>(smem_raw);
+  __shared__ Smem s;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, l16 = lane & 15, lg = lane >> 4;
-  stage_weights(a, s);
+  const int64_t begin = (int64_t)blockIdx.x * a.per_block;
+  const int64_t end = begin + a.per_block < a.n ? begin + a.per_block : a.n;
+  // observables of event 16 w + l16 and label of event 16 w + 4 lg + l16 % 4 of a tile
+  double x[4] = {0.0, 0.0, 0.0, 0.0};
+  float y = 0.f;
+  auto fetch = [&](int64_t e0) {
+    const int64_t e = e0 + 16 * w + l16, ey = e0 + 16 * w + 4 * lg + (l16 & 3);
+    if (e < end) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = a.obs[k][e];
+    }
+    if (ey < end) y = (float)a.label[ey];
+  };
+  fetch(begin);
+  L1Weights w1;
+  w1.load(a.params, lg);
+  bf8_t w2[4][2], w2t[4][2];   // W2[16 nt + l16][k] and W2[k][16 nt + l16], k = 32 kk + 8 lg + j
+  float b2[4], w3[4];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    const int o = 16 * nt + l16;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      w2[nt][kk] = ld8(a.w2h + 64 * o + 32 * kk + 8 * lg);
+      w2t[nt][kk] = ld8(a.w2h + 4096 + 64 * o + 32 * kk + 8 * lg);
+    }
+    b2[nt] = a.params[P_B2 + o];
+    w3[nt] = (float)(__bf16)a.params[P_W3 + o];
+  }
   const float b3 = a.params[P_B3];
   float gW2[4][4];        // dW2[o = 16 w + 4 lg + r][i = 16 nt + l16]
   float gb2[4], gw3[4];   // outputs 16 nt + l16 (this lane's events)
@@ -205,185 +213,212 @@ __global__ __launch_bounds__(256) void mlp_grad_kernel(MlpArgs a) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) { gW2[i][k] = 0.f; gW1[i][k] = 0.f; }
   }
-  __syncthreads();
-  const int64_t begin = (int64_t)blockIdx.x * a.per_block;
-  const int64_t end = begin + a.per_block < a.n ? begin + a.per_block : a.n;
-  for (int64_t e0 = begin; e0 < end; e0 += TE) {
-    f4_t z2[4];
-    forward_tile(a, s, e0, z2);
-    // output layer: z3 for events 16 w + 4 lg + r
-    float z3p[4] = {0.f, 0.f, 0.f, 0.f};
+  int buf = 0;
+  for (int64_t e0 = begin; e0 < end; e0 += TE, buf ^= 1) {
+    unsigned short* H1 = s.H1[buf];
+    unsigned short* DZT = s.DZT[buf];
+    // ---- input layer: event 16 w + l16, features 32 kk + 8 lg + j
+    f4_t u;
+    const bool in = e0 + 16 * w + l16 < end;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) u[k] = in ? input_map(a, k, x[k]) : 0.0f;
+    const float yl = y;
+    const bool ok = e0 + 16 * w + 4 * lg + (l16 & 3) < end;   // the event of yl
+    if (e0 + TE < end) fetch(e0 + TE);
+    if (lg == 0) s.U[16 * w + l16] = u;
+    const float uf[4] = {u[0], u[1], u[2], u[3]};
+    bf8_t h[2];
+#pragma unroll
+    for (int c4 = 0; c4 < 4; ++c4) {
+      f4_t d1;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int c = 4 * c4 + j;
+        float sl, ds;
+        silu_both(w1.z(c, uf), sl, ds);
+        d1[j] = ds;
+        h[c >> 3][c & 7] = (__bf16)sl;
+      }
+      *reinterpret_cast<f4_t*>(&s.D1[(16 * w + l16) * SF + 32 * (c4 >> 1) + 8 * lg + 4 * (c4 & 1)]) = d1;
+    }
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) *reinterpret_cast<bf8_t*>(&H1[(16 * w + l16) * SH + 32 * kk + 8 * lg]) = h[kk];
+    // ---- 64x64 layer: z2 of events 16 w + 4 lg + r, outputs 16 nt + l16
+    float sl2[4][4], ds2[4][4], z3p[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
-      const int o = 16 * nt + l16;
-      const float bb = s.B2[o], ww = s.W3[o];
+      f4_t z2 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) z2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h[kk], w2[nt][kk], z2, 0, 0, 0);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        z2[nt][r] += bb;
-        z3p[r] += ww * silu(z2[nt][r]);
+        silu_both(z2[r] + b2[nt], sl2[nt][r], ds2[nt][r]);
+        z3p[r] = __builtin_fmaf(w3[nt], sl2[nt][r], z3p[r]);
       }
     }
+    // ---- output layer: each lane takes the event 4 lg + l16 % 4, then hands it to its quad
+#pragma unroll
+    for (int r = 0; r < 4; ++r) z3p[r] = row_sum(z3p[r]);
+    const float zlo = (l16 & 1) ? z3p[1] : z3p[0], zhi = (l16 & 1) ? z3p[3] : z3p[2];
+    const float p = 1.0f / (1.0f + __expf(-(((l16 & 2) ? zhi : zlo) + b3)));
+    const float pc = fminf(fmaxf(p, 1e-12f), 1.0f - 1e-12f);
+    const float dz = ok ? p - yl : 0.0f;
+    const float term = ok ? -(yl * __logf(pc) + (1.0f - yl) * __logf(1.0f - pc)) : 0.0f;
+    const float dz3[4] = {dpp<0x00>(dz), dpp<0x55>(dz), dpp<0xAA>(dz), dpp<0xFF>(dz)};
+    const float tr[4] = {dpp<0x00>(term), dpp<0x55>(term), dpp<0xAA>(term), dpp<0xFF>(term)};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-#pragma unroll
-      for (int off = 1; off < 16; off <<= 1) z3p[r] += __shfl_xor(z3p[r], off, 64);
+      loss += tr[r];
+      gb3 += dz3[r];
     }
-    float dz3[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int e = 16 * w + 4 * lg + r;
-      const bool ok = e0 + e < end;
-      const float p = 1.0f / (1.0f + __expf(-(z3p[r] + b3)));
-      const float y = s.Y[e];
-      dz3[r] = ok ? p - y : 0.0f;
-      if (ok && l16 == 0) {
-        const float pc = fminf(fmaxf(p, 1e-12f), 1.0f - 1e-12f);
-        loss += -(y * __logf(pc) + (1.0f - y) * __logf(1.0f - pc));
-        gb3 += dz3[r];
-      }
-    }
-    // back-propagate to z2: dz2 = dz3 w3 silu'(z2); bias and w3 gradients
+    // ---- back to z2: dz2 = dz3 w3 silu'(z2); bias and w3 gradients
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
-      const int o = 16 * nt + l16;
-      const float ww = s.W3[o];
+      bf4_t dq;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int e = 16 * w + 4 * lg + r;
-        const float z = z2[nt][r];
-        gw3[nt] += dz3[r] * silu(z);
-        const float d = dz3[r] * ww * dsilu(z);
-        gb2[nt] += d;
-        const unsigned short h = bf16(d);
-        s.DZ[e * 64 + o] = h;
-        s.DZT[o * TE + e] = h;
+        gw3[nt] = __builtin_fmaf(dz3[r], sl2[nt][r], gw3[nt]);
+        const float dw = dz3[r] * w3[nt];
+        gb2[nt] = __builtin_fmaf(dw, ds2[nt][r], gb2[nt]);
+        dq[r] = (__bf16)(dw * ds2[nt][r]);
+      }
+      *reinterpret_cast<bf4_t*>(&DZT[(16 * nt + l16) * SH + 16 * w + 4 * lg]) = dq;
+    }
+    wave_sync();
+    // ---- dh1[e][i] = sum_o dz2[e][o] W2[o][i] for the wavefront's events, then the input layer
+    bf8_t dz2[2];   // event l16, outputs 32 kk + 8 lg + j
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) dz2[kk] = ld8t(&DZT[(32 * kk + 8 * lg) * SH + 16 * w], SH, l16);
+    f4_t ur[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) ur[r] = s.U[16 * w + 4 * lg + r];
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+      f4_t dh = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) dh = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dz2[kk], w2t[nt][kk], dh, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float d1 = s.D1[(16 * w + 4 * lg + r) * SF + 16 * nt + l16];
+        gb1[nt] = __builtin_fmaf(dh[r], d1, gb1[nt]);
+        const float dz1 = dh[r] * d1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) gW1[nt][k] = __builtin_fmaf(dz1, ur[r][k], gW1[nt][k]);
       }
     }
     __syncthreads();
-    // dW2[o][i] += sum_e dz2[e][o] h1[e][i]: wave w owns o-tile w;
-    // A[m = o][k = e] = dz2[e][o] (rows of DZT), B[k = e][n = i] = h1[e][i] (rows of H1T)
-    static_assert(TE == 64, "tile rows are 64 deep");
+    // ---- dW2[o][i] += sum_e dz2[e][o] h1[e][i]: wavefront w owns the outputs 16 w ..
+    bf8_t dv[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) dv[kk] = ld8(&DZT[(16 * w + l16) * SH + 32 * kk + 8 * lg]);
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
-      const f4_t acc = nn::mm16x64(&s.DZT[(16 * w) * TE], &s.H1T[(16 * nt) * TE], l16, lg);
+      f4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        const bf8_t hv = ld8t(&H1[(32 * kk + 8 * lg) * SH + 16 * nt], SH, l16);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dv[kk], hv, acc, 0, 0, 0);
+      }
 #pragma unroll
       for (int r = 0; r < 4; ++r) gW2[nt][r] += acc[r];
     }
-    // dh1[e][i] = sum_o dz2[e][o] W2[o][i]: wave w owns events 16 w ..;
-    // A[m = e][k = o] = dz2 (rows of DZ), B[k = o][n = i] = W2[o][i] (rows of W2T)
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const f4_t acc = nn::mm16x64(&s.DZ[(16 * w) * 64], &s.W2T[(16 * nt) * 64], l16, lg);
-      const int i = 16 * nt + l16;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int e = 16 * w + 4 * lg + r;
-        const float z1 = s.B1[i] + s.W1[4 * i] * s.U[e * 4] + s.W1[4 * i + 1] * s.U[e * 4 + 1] +
-                         s.W1[4 * i + 2] * s.U[e * 4 + 2] + s.W1[4 * i + 3] * s.U[e * 4 + 3];
-        const float dz1 = acc[r] * nn::dsilu(z1);
-        gb1[nt] += dz1;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) gW1[nt][k] += dz1 * s.U[e * 4 + k];
-      }
-    }
-    __syncthreads();
   }
-  // ---- block partials (value-major).  dW2 entries have a unique owner lane.
-  float* rec = a.partial + (int64_t)blockIdx.x * (MLP_NV);
-  auto put = [&](int v, float x) { rec[v] = x; };
+  // ---- block record.  dW2 entries have a unique owner lane; the others are summed over the rows of
+  // the wavefront, then the four wavefronts in order.
+  float* rec = a.partial + (int64_t)blockIdx.x * MLP_NV;
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) put(P_W2 + (16 * w + 4 * lg + r) * 64 + 16 * nt + l16, gW2[nt][r]);
-  // per-output sums: combine the 4 lane groups of a wave, then the 4 waves, in fixed order
-  auto reduce_out = [&](float x, int v) {
-    x += __shfl_xor(x, 16, 64);
-    x += __shfl_xor(x, 32, 64);
-    if (lg == 0) s.red[w * 64 + l16 + 0] = x;   // 16 values per wave at [w*64 + l16]
-    __syncthreads();
-    if (t < 16) put(v + t, ((s.red[t] + s.red[64 + t]) + s.red[128 + t]) + s.red[192 + t]);
-    __syncthreads();
-  };
+    for (int r = 0; r < 4; ++r) rec[P_W2 + (16 * w + 4 * lg + r) * 64 + 16 * nt + l16] = gW2[nt][r];
+  auto put4 = [&](int g, const float* v) { s.red[w][64 * g + lane] = rows_sum4(v[0], v[1], v[2], v[3]); };
+  put4(0, gb2);
+  put4(1, gw3);
+  put4(2, gb1);
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    reduce_out(gb2[nt], P_B2 + 16 * nt);
-    reduce_out(gw3[nt], P_W3 + 16 * nt);
-    reduce_out(gb1[nt], P_B1 + 16 * nt);
+  for (int nt = 0; nt < 4; ++nt) put4(3 + nt, gW1[nt]);
+  // b3 and loss: every lane of a row holds the row's sum
+  gb3 += __shfl_xor(gb3, 32, 64);
+  gb3 += __shfl_xor(gb3, 16, 64);
+  loss += __shfl_xor(loss, 32, 64);
+  loss += __shfl_xor(loss, 16, 64);
+  if (lane == 0) {
+    s.sc[w][0] = gb3;
+    s.sc[w][1] = loss;
   }
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      float x = gW1[nt][k];
-      x += __shfl_xor(x, 16, 64);
-      x += __shfl_xor(x, 32, 64);
-      if (lg == 0) s.red[w * 64 + l16] = x;
-      __syncthreads();
-      if (t < 16) put(P_W1 + 4 * (16 * nt + t) + k, ((s.red[t] + s.red[64 + t]) + s.red[128 + t]) + s.red[192 + t]);
-      __syncthreads();
-    }
-  // b3 and loss: a butterfly in each wavefront, then the four wavefronts in order
-  auto block_sum = [&](float x) -> float {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-    if (lane == 0) s.red[w] = x;
-    __syncthreads();
-    const float r = ((s.red[0] + s.red[1]) + s.red[2]) + s.red[3];
-    __syncthreads();
-    return r;
-  };
-  const float sb3 = block_sum(gb3), sloss = block_sum(loss);
-  if (t == 0) {
-    put(P_B3, sb3);
-    put(4545, sloss);
-  }
-}
-
-// Sum of block-major partials in FP64, fixed order: out[v] = scale * sum_b partial[b * nv + v].
-// A workgroup takes 64 consecutive values; its four wavefronts take the blocks b = s mod 4
-// (s = 0..3), each lane keeping four sums (blocks 16 k + s, + 4, + 8, + 12) so four reads are in
-// flight, and the 4 x 4 sums are combined in a fixed order.  A wavefront reads 64 consecutive
-// values of one block record: every read is coalesced.
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict__ partial, int nb, int nv,
-                                                         double scale, double* __restrict__ out) {
-  __shared__ double red[4][64];
-  const int vl = threadIdx.x & 63, seg = threadIdx.x >> 6;
-  const int v = blockIdx.x * 64 + vl;
-  double x0 = 0.0, x1 = 0.0, x2 = 0.0, x3 = 0.0;
-  if (v < nv) {
-    int b = seg;
-    for (; b + 12 < nb; b += 16) {
-      x0 += (double)partial[(int64_t)b * nv + v];
-      x1 += (double)partial[(int64_t)(b + 4) * nv + v];
-      x2 += (double)partial[(int64_t)(b + 8) * nv + v];
-      x3 += (double)partial[(int64_t)(b + 12) * nv + v];
-    }
-    for (; b < nb; b += 4) x0 += (double)partial[(int64_t)b * nv + v];
-  }
-  red[seg][vl] = (x0 + x1) + (x2 + x3);
   __syncthreads();
-  if (seg == 0 && v < nv) out[v] = scale * (((red[0][vl] + red[1][vl]) + red[2][vl]) + red[3][vl]);
+  for (int i = t; i < 28 * 16; i += 256) {
+    const int j = i >> 4, f = i & 15;   // value j of unit f
+    const int v = j < 4    ? P_B2 + 16 * j + f
+                  : j < 8  ? P_W3 + 16 * (j - 4) + f
+                  : j < 12 ? P_B1 + 16 * (j - 8) + f
+                           : P_W1 + 4 * (16 * ((j - 12) >> 2) + f) + (j & 3);
+    rec[v] = ((s.red[0][i] + s.red[1][i]) + s.red[2][i]) + s.red[3][i];
+  }
+  if (t < 2) rec[t == 0 ? P_B3 : 4545] = ((s.sc[0][t] + s.sc[1][t]) + s.sc[2][t]) + s.sc[3][t];
 }
 
-// Adam step on the FP32 master parameters; with w2h, also the BF16 copies of the updated 64x64
-// layer in both layouts (as launch_mlp_bf16 writes them).
-__global__ __launch_bounds__(256) void adam_kernel(float* p, float* m, float* v, const double* g, int n, float lr,
-                                                   float b1, float b2, float eps, float c1, float c2,
-                                                   unsigned short* w2h) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = (float)g[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * gi;
-  const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float pi = p[i] - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-  p[i] = pi;
+// Adam step of parameter i at the gradient g, on the FP32 master parameters; also the BF16 copies of
+// the updated 64x64 layer in both layouts (as launch_mlp_bf16 writes them).
+__device__ __forceinline__ void adam_step(const AdamArgs& a, int i, double g) {
+  const float gi = (float)g;
+  const float mi = __builtin_fmaf(a.b1, a.m[i], (1.0f - a.b1) * gi);
+  const float vi = __builtin_fmaf(a.b2, a.v[i], (1.0f - a.b2) * gi * gi);
+  a.m[i] = mi;
+  a.v[i] = vi;
+  const float pi = a.p[i] - a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + a.eps);
+  a.p[i] = pi;
   const int k = i - nn::P_W2;
-  if (w2h && k >= 0 && k < 4096) {
+  if (k >= 0 && k < 4096) {
     const unsigned short h = nn::bf16(pi);
-    w2h[k] = h;
-    w2h[4096 + (k & 63) * 64 + (k >> 6)] = h;
+    a.w2h[k] = h;
+    a.w2h[4096 + (k & 63) * 64 + (k >> 6)] = h;
+  }
+}
+
+// Sum of block-major partials in FP64, fixed order: value v = scale * sum_b partial[b * nv + v].
+// A workgroup takes 16 consecutive values and 16 chains of blocks: chain 4 s + q sums the blocks
+// s + 4 q + 16 k (s, q = 0..3; of an incomplete last 16, chain 4 s takes the blocks s mod 4), eight
+// reads in flight, and the chains are combined in a fixed order.  The values go to out, or, while
+// training (ADAM), each parameter's update follows at once and the loss goes to loss: 7.0 us and a
+// launch of 4.8 us for 256 records in one of RED_NOW us (64 values a workgroup and four reads in
+// flight before).
+template <bool ADAM>
+__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict__ partial, int nb, int nv,
+                                                         double scale, double* __restrict__ out, AdamArgs ad) {
+  __shared__ double red[16][16];
+  const int vl = threadIdx.x & 15, chain = threadIdx.x >> 4, sg = chain >> 2, q = chain & 3;
+  const int v = blockIdx.x * 16 + vl;
+  double x = 0.0;
+  if (v < nv) {
+    const int K = nb > sg + 12 ? (nb - sg - 13) / 16 + 1 : 0;   // whole sixteens of this s
+    const float* p = partial + (int64_t)(sg + 4 * q) * nv + v;
+    const int64_t step = (int64_t)16 * nv;
+    int k = 0;
+    for (; k + 8 <= K; k += 8) {
+      float f[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) f[i] = p[(k + i) * step];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x += (double)f[i];
+    }
+    for (; k < K; ++k) x += (double)p[k * step];
+    if (q == 0)
+      for (int b = sg + 16 * K; b < nb; b += 4) x += (double)partial[(int64_t)b * nv + v];
+  }
+  red[chain][vl] = x;
+  __syncthreads();
+  if (chain == 0 && v < nv) {
+    double y[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      y[g] = (red[4 * g][vl] + red[4 * g + 1][vl]) + (red[4 * g + 2][vl] + red[4 * g + 3][vl]);
+    const double r = scale * (((y[0] + y[1]) + y[2]) + y[3]);
+    if constexpr (ADAM) {
+      if (v == nv - 1) *ad.loss = r;
+      else adam_step(ad, v, r);
+    } else {
+      out[v] = r;
+    }
   }
 }
 
@@ -409,7 +444,7 @@ __global__ __launch_bounds__(256, 2) void mlp_eval_kernel(MlpArgs a) {
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) w2[nt][kk] = to_bf8(a.params + P_W2 + 64 * o + 32 * kk + 8 * lg);
     b2[nt] = a.params[P_B2 + o];
-    w3[nt] = from_bf16(bf16(a.params[P_W3 + o]));
+    w3[nt] = (float)(__bf16)a.params[P_W3 + o];
   }
   const float b3 = a.params[P_B3];
   const int64_t tiles = (a.n + 63) / 64, stride = (int64_t)gridDim.x * 4;
@@ -522,26 +557,21 @@ __global__ __launch_bounds__(256) void mlp_bf16_kernel(const float* __restrict__
   w2h[4096 + (i & 63) * 64 + (i >> 6)] = h;
 }
 
-size_t mlp_smem_bytes() { return sizeof(nn::Smem); }
-
 hipError_t launch_mlp_bf16(const float* params, unsigned short* w2h, hipStream_t st) {
   hipLaunchKernelGGL(mlp_bf16_kernel, dim3(16), dim3(256), 0, st, params, w2h);
   return hipGetLastError();
 }
 
 hipError_t launch_mlp_grad(const MlpArgs& a, int nb, hipStream_t st) {
-  hipLaunchKernelGGL(mlp_grad_kernel, dim3(nb), dim3(256), sizeof(nn::Smem), st, a);
+  hipLaunchKernelGGL(mlp_grad_kernel, dim3(nb), dim3(256), 0, st, a);
   return hipGetLastError();
 }
-hipError_t launch_mlp_reduce(const float* partial, int nb, int nv, double scale, double* out, hipStream_t st) {
+hipError_t launch_mlp_reduce(const float* partial, int nb, int nv, double scale, double* out, const AdamArgs* ad,
+                             hipStream_t st) {
   if (nv != MLP_NV) return hipErrorInvalidValue;   // the block records are MLP_NV values long
-  hipLaunchKernelGGL(mlp_reduce_kernel, dim3((nv + 63) / 64), dim3(256), 0, st, partial, nb, nv, scale, out);
-  return hipGetLastError();
-}
-hipError_t launch_adam(float* p, float* m, float* v, const double* g, int n, float lr, float b1, float b2, float eps,
-                       float c1, float c2, unsigned short* w2h, hipStream_t st) {
-  hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, m, v, g, n, lr, b1, b2, eps, c1, c2,
-                     w2h);
+  const dim3 grid((nv + 15) / 16);
+  if (ad) hipLaunchKernelGGL(mlp_reduce_kernel<true>, grid, dim3(256), 0, st, partial, nb, nv, scale, out, *ad);
+  else hipLaunchKernelGGL(mlp_reduce_kernel<false>, grid, dim3(256), 0, st, partial, nb, nv, scale, out, AdamArgs{});
   return hipGetLastError();
 }
 hipError_t launch_mlp_eval(const MlpArgs& a, int nb, hipStream_t st) {

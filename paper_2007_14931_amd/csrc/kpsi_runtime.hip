@@ -2147,23 +2147,25 @@ static hipError_t prep_w2h(kpsi_ctx* c, const float* dparams) {
   return launch_mlp_bf16(dparams, c->mlp_w2h, c->stream);
 }
 
-// w2h_current: the BF16 copies already match dparams (the Adam kernel of the previous step wrote them)
+// Mean gradient and loss of the n events into g (4546 doubles), or, with ad, through an Adam step.
+// w2h_current: the BF16 copies already match dparams (the Adam step of the previous batch wrote them)
 static hipError_t mlp_grad_device(kpsi_ctx* c, const float* dparams, int64_t n, const double* m, const double* ck,
                                   const double* cj, const double* phi, const uint8_t* label, float* partial,
-                                  int nbmax, double* g, bool w2h_current = false) {
+                                  int nbmax, double* g, AdamArgs* ad = nullptr, bool w2h_current = false) {
   MlpArgs a = mlp_args(c, n, m, ck, cj, phi);
   a.label = label;
   a.params = dparams;
   if (!w2h_current || !c->mlp_w2h)
     if (hipError_t e = prep_w2h(c, dparams)) return e;
   a.w2h = c->mlp_w2h;
+  if (ad) ad->w2h = c->mlp_w2h;
   a.partial = partial;
   const int64_t tiles = (n + 63) / 64;
   const int nb = (int)std::min<int64_t>(tiles, nbmax);
   a.per_block = (tiles + nb - 1) / nb * 64;
   hipError_t e = launch_mlp_grad(a, nb, c->stream);
   if (e != hipSuccess) return e;
-  return launch_mlp_reduce(partial, nb, MLP_NV, 1.0 / (double)n, g, c->stream);
+  return launch_mlp_reduce(partial, nb, MLP_NV, 1.0 / (double)n, g, ad, c->stream);
 }
 
 kpsi_status kpsi_mlp_grad(kpsi_ctx* c, const float* params, int64_t n, const double* m, const double* ck,
@@ -2202,52 +2204,51 @@ kpsi_status kpsi_mlp_train(kpsi_ctx* c, float* params, int64_t n, const double* 
   if (!c->has_model) return fail(c, KPSI_E_STATE, "no model set (kinematics needed)");
   hipSetDevice(c->device);
   // at most one block per compute unit: a batch of 32768 events then runs two 64-event tiles per
-  // block, which halves the weight staging and the block records against one tile per block
-  // (38.4 against 42.8 us per training step; four tiles per block, on half the units: 47.5 us)
+  // block (the kernel's sums follow these block and tile bounds)
   const int nbmax = c->n_cu > 0 ? c->n_cu : 256;
+  const int64_t B = o->batch;
+  const int64_t nbatch = (n + B - 1) / B;
   float *dp = nullptr, *mm = nullptr, *vv = nullptr, *part = nullptr;
-  double* g = nullptr;
+  double* dloss = nullptr;   // mean loss of each batch
   auto cleanup = [&]() {
-    for (void* p : {(void*)dp, (void*)mm, (void*)vv, (void*)part, (void*)g}) if (p) hipFree(p);
+    for (void* p : {(void*)dp, (void*)mm, (void*)vv, (void*)part, (void*)dloss}) if (p) hipFree(p);
   };
   if (hipMalloc(&dp, MLP_NP * sizeof(float)) || hipMalloc(&mm, MLP_NP * sizeof(float)) ||
       hipMalloc(&vv, MLP_NP * sizeof(float)) || hipMalloc(&part, (size_t)(MLP_NP + 1) * nbmax * sizeof(float)) ||
-      hipMalloc(&g, (MLP_NP + 1) * sizeof(double))) {
+      hipMalloc(&dloss, nbatch * sizeof(double))) {
     cleanup();
     return fail(c, KPSI_E_OOM, "network buffers");
   }
   hipError_t e = hipMemcpyAsync(dp, params, MLP_NP * sizeof(float), hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(mm, 0, MLP_NP * sizeof(float), c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(vv, 0, MLP_NP * sizeof(float), c->stream);
-  const int64_t B = o->batch;
-  const int64_t nbatch = (n + B - 1) / B;
+  AdamArgs ad{};
+  ad.p = dp; ad.m = mm; ad.v = vv;
+  ad.lr = (float)o->lr; ad.b1 = (float)o->beta1; ad.b2 = (float)o->beta2; ad.eps = (float)o->eps;
   int64_t step = 0;
-  double last_loss = 0.0;
   for (int ep = 0; ep < o->epochs && e == hipSuccess; ++ep) {
-    double eloss = 0.0;
     for (int64_t b = 0; b < nbatch && e == hipSuccess; ++b) {
       const int64_t off = b * B, cnt = std::min(B, n - off);
-      e = mlp_grad_device(c, dp, cnt, m + off, ck + off, cj + off, phi + off, label + off, part, nbmax, g, step > 0);
+      const bool current = step > 0;
       ++step;
-      const float c1 = (float)(1.0 / (1.0 - std::pow(o->beta1, (double)step)));
-      const float c2 = (float)(1.0 / (1.0 - std::pow(o->beta2, (double)step)));
-      if (e == hipSuccess)
-        e = launch_adam(dp, mm, vv, g, MLP_NP, (float)o->lr, (float)o->beta1, (float)o->beta2, (float)o->eps, c1, c2,
-                        c->mlp_w2h, c->stream);
-      if (ep == o->epochs - 1 && e == hipSuccess) {
-        double lb = 0.0;
-        e = hipMemcpyAsync(&lb, g + MLP_NP, sizeof(double), hipMemcpyDeviceToHost, c->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        eloss += lb * (double)cnt;
-      }
+      ad.c1 = (float)(1.0 / (1.0 - std::pow(o->beta1, (double)step)));
+      ad.c2 = (float)(1.0 / (1.0 - std::pow(o->beta2, (double)step)));
+      ad.loss = dloss + b;
+      e = mlp_grad_device(c, dp, cnt, m + off, ck + off, cj + off, phi + off, label + off, part, nbmax, nullptr, &ad,
+                          current);
     }
-    if (ep == o->epochs - 1) last_loss = eloss / (double)n;
   }
+  // the losses of the last epoch's batches
+  std::vector<double> hl(o->epochs > 0 ? nbatch : 0);
+  if (e == hipSuccess && !hl.empty())
+    e = hipMemcpyAsync(hl.data(), dloss, hl.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(params, dp, MLP_NP * sizeof(float), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   cleanup();
   if (e != hipSuccess) return fail(c, KPSI_E_HIP, "network training: %s", hipGetErrorString(e));
-  if (loss) *loss = last_loss;
+  double sum = 0.0;
+  for (size_t b = 0; b < hl.size(); ++b) sum += hl[b] * (double)std::min<int64_t>(B, n - (int64_t)b * B);
+  if (loss) *loss = sum / (double)n;
   return KPSI_OK;
 }
 
