@@ -7,7 +7,7 @@
 //                       the adjoint of S with respect to every coupling and the
 //                       floating masses/widths, reduced per block
 //   reduce_final        fixed-order compensated sum of the block partials
-//   phsp/accept kernels Philox4x32-10 phase-space and accept-reject generators
+//   generators          Philox4x32-10 phase space, and accept-reject samples of the model (toys)
 //
 // Wavefronts are 64 lanes.  Every reduction is atomic-free and in a fixed order,
 // so results are bitwise reproducible run to run.
@@ -69,16 +69,13 @@ __device__ __forceinline__ void lds_add(lds_ptr<double> p, double x) { __builtin
 //               With free Z helicities (zfree), columns 14-15 hold F++ = Zang[+1][+1] and
 //               16-17 F+- = Zang[+1][-1]; the l' = -1 factors are Zang[-1][+1] = -conj(F+-)
 //               and Zang[-1][-1] = -conj(F++).
-// All arithmetic in double; stored in T.
-template <typename T>
-__global__ __launch_bounds__(256) void invariants_kernel(InvArgs<T> a) {
+// All arithmetic in double.
+__device__ __forceinline__ void invariants(const Kin& k, double m, double cK, double cJ, double ph, bool with_z,
+                                           bool zfree, double* c, double* diag) {
   // One-time kinematics without contraction: at the threshold and end point of m_Kpi the
   // breakup momenta then round to exactly zero, as the plain double-precision definition does.
 #pragma clang fp contract(off)
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= a.n) return;
-  const double mB = a.mB, mJ = a.mJ, mK = a.mK, mP = a.mPi;
-  double m = a.obs[0][e], cK = a.obs[1][e], cJ = a.obs[2][e], ph = a.obs[3][e];
+  const double mB = k.mB, mJ = k.mJ, mK = k.mK, mP = k.mPi;
   // two-body momenta in the K pi frame and in the B frame
   const double s = m * m;
   const double q2 = (s - (mK + mP) * (mK + mP)) * (s - (mK - mP) * (mK - mP));
@@ -90,19 +87,17 @@ __global__ __launch_bounds__(256) void invariants_kernel(InvArgs<T> a) {
   const double sJ = sqrt(fmax(0.0, (1.0 - cJ) * (1.0 + cJ)));
   double sph, cph;
   sincos(ph, &sph, &cph);
-  T* c = a.cols;
-  const int64_t ld = a.ld;
-  c[col_at(0, e, ld)] = (T)m;
-  c[col_at(1, e, ld)] = (T)q;
-  c[col_at(2, e, ld)] = (T)pB;
-  c[col_at(3, e, ld)] = (T)cK;
-  c[col_at(4, e, ld)] = (T)sK;
-  c[col_at(5, e, ld)] = (T)cJ;
-  c[col_at(6, e, ld)] = (T)sJ;
-  c[col_at(7, e, ld)] = (T)cph;
-  c[col_at(8, e, ld)] = (T)sph;
-  c[col_at(10, e, ld)] = (T)(q / m);
-  if (!a.with_z && !a.diag) return;
+  c[0] = m;
+  c[1] = q;
+  c[2] = pB;
+  c[3] = cK;
+  c[4] = sK;
+  c[5] = cJ;
+  c[6] = sJ;
+  c[7] = cph;
+  c[8] = sph;
+  c[10] = (q / m);
+  if (!with_z && !diag) return;
 
   // J/psi rest frame, reached by a boost along z from the B frame, in which the K pi
   // system moves along +z and the J/psi along -z.  The K pi system moves along +z in
@@ -160,45 +155,145 @@ __global__ __launch_bounds__(256) void invariants_kernel(InvArgs<T> a) {
   const double ca = xb_x * xa_x + xb_y * xa_y + xb_z * xa_z;
   const double crx = xb_y * xa_z - xb_z * xa_y, cry = xb_z * xa_x - xb_x * xa_z, crz = xb_x * xa_y - xb_y * xa_x;
   const double sa = crx * ux + cry * uy + crz * uz;
-  if (a.diag) {
-    double* o = a.diag + 5 * e;
-    o[0] = mz; o[1] = cZ; o[2] = ct; o[3] = atan2(spt, cpt); o[4] = atan2(sa, ca);
+  if (diag) {
+    diag[0] = mz; diag[1] = cZ; diag[2] = ct; diag[3] = atan2(spt, cpt); diag[4] = atan2(sa, ca);
   }
-  if (!a.with_z) return;
+  if (!with_z) return;
   // Z lineshape factors (B -> Z K with L_B = 1, Z -> J/psi pi with L_R = 0)
   const double qz2 = (mz2 - (mJ + mP) * (mJ + mP)) * (mz2 - (mJ - mP) * (mJ - mP));
   const double qz = qz2 > 0.0 ? sqrt(qz2) / (2.0 * mz) : 0.0;
   const double pbz2 = (mB2 - (mz + mK) * (mz + mK)) * (mB2 - (mz - mK) * (mz - mK));
   const double pbz = pbz2 > 0.0 ? sqrt(pbz2) / (2.0 * mB) : 0.0;
-  const double zb = a.rB * pbz * a.rB * pbz;
+  const double zb = k.rB * pbz * k.rB * pbz;
   const double nZ = (pbz / mB) / sqrt(1.0 + zb);
-  c[col_at(9, e, ld)] = (T)mz2;
-  c[col_at(11, e, ld)] = (T)(qz / mz);
+  c[9] = mz2;
+  c[11] = (qz / mz);
   // Angular factors of Eq. (10): d^1_{0l'}(theta_Z) e^{i l' phi~} d^1_{l' xi}(theta~) e^{i xi alpha},
   // times nZ
   const double r2 = 0.7071067811865475244 * nZ;
   //  l' = 0:  xi = +1: cZ st/sqrt2 e^{i alpha};  xi = -1: -cZ st/sqrt2 e^{-i alpha}
   //  (xi = -1 is -z0 ca + i z0 sa: minus the real part, the same imaginary part)
   const double z0 = cZ * st * r2;
-  c[col_at(12, e, ld)] = (T)(z0 * ca);
-  c[col_at(13, e, ld)] = (T)(z0 * sa);
+  c[12] = (z0 * ca);
+  c[13] = (z0 * sa);
   //  l' = +-1 (H'_{-1} = H'_{+1}):  xi = +1: sZ/sqrt2 (ct cpt + i spt) e^{i alpha}
   //                                 xi = -1: sZ/sqrt2 (-ct cpt + i spt) e^{-i alpha}, again
   //                                 (-Re, Im) of the xi = +1 factor
   const double z1 = sZ * r2;
-  if (a.zfree) {
+  if (zfree) {
     // l' = +1 alone: d^1_{0,1}(theta_Z) = sZ/sqrt2, d^1_{1,xi}(theta~) = (1 + xi ct)/2, phases
     // e^{i (phi~ + xi alpha)}
     const double up = 0.5 * z1 * (1.0 + ct), dn = 0.5 * z1 * (1.0 - ct);
-    c[col_at(14, e, ld)] = (T)(up * (cpt * ca - spt * sa));
-    c[col_at(15, e, ld)] = (T)(up * (spt * ca + cpt * sa));
-    c[col_at(16, e, ld)] = (T)(dn * (cpt * ca + spt * sa));
-    c[col_at(17, e, ld)] = (T)(dn * (spt * ca - cpt * sa));
+    c[14] = (up * (cpt * ca - spt * sa));
+    c[15] = (up * (spt * ca + cpt * sa));
+    c[16] = (dn * (cpt * ca + spt * sa));
+    c[17] = (dn * (spt * ca - cpt * sa));
     return;
   }
   const double pr = ct * cpt, pi_ = spt;
-  c[col_at(14, e, ld)] = (T)(z1 * (pr * ca - pi_ * sa));
-  c[col_at(15, e, ld)] = (T)(z1 * (pr * sa + pi_ * ca));
+  c[14] = (z1 * (pr * ca - pi_ * sa));
+  c[15] = (z1 * (pr * sa + pi_ * ca));
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void invariants_kernel(InvArgs<T> a) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= a.n) return;
+  double c[18];
+  invariants(a.kin, a.obs[0][e], a.obs[1][e], a.obs[2][e], a.obs[3][e], a.with_z, a.zfree, c,
+             a.diag ? a.diag + 5 * e : nullptr);
+#pragma unroll
+  for (int k = 0; k < 18; ++k) {
+    const bool z = k == 9 || k > 10;   // a Z column
+    if (!z || (a.with_z && (k < 16 || a.zfree))) a.cols[col_at(k, e, a.ld)] = (T)c[k];
+  }
+}
+
+// ------------------------------------------------------------------ generators
+// Philox4x32-10 from its published definition (Salmon et al., SC'11).
+__device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
+#pragma unroll
+  for (int r = 0; r < 10; ++r) {
+    if (r > 0) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
+    const uint64_t p0 = (uint64_t)0xD2511F53u * c[0];
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c[2];
+    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c[1] ^ k0;
+    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c[3] ^ k1;
+    c[1] = (uint32_t)p1;
+    c[3] = (uint32_t)p0;
+    c[0] = n0;
+    c[2] = n2;
+  }
+}
+__device__ __forceinline__ void u2(uint64_t e, uint32_t w2, uint32_t w3, uint64_t seed, double& ua, double& ub) {
+  uint32_t c[4] = {(uint32_t)e, (uint32_t)(e >> 32), w2, w3};
+  philox4x32_10(c, (uint32_t)seed, (uint32_t)(seed >> 32));
+  ua = (double)(((uint64_t)(c[0] >> 5) << 26) | (uint64_t)(c[1] >> 6)) * (1.0 / 9007199254740992.0);
+  ub = (double)(((uint64_t)(c[2] >> 5) << 26) | (uint64_t)(c[3] >> 6)) * (1.0 / 9007199254740992.0);
+}
+
+// Trial t of the phase-space proposal e: m_Kpi flat in the mass range, accepted if u wmax < p_B(m)
+// q(m).  The test is evaluated without contraction so it is bit-identical to a plain FP64 host; the
+// squares decide it without roots and quotients where they differ by more than 1e-10 of either,
+// which is far more than both forms' roundings.
+__device__ __forceinline__ bool phsp_trial(const Kin& k, uint64_t seed, double wmax, uint64_t e, uint32_t t,
+                                           double& m) {
+#pragma clang fp contract(off)
+  const double lo = k.mK + k.mPi, hi = k.mB - k.mJ;
+  const double c1 = (k.mK + k.mPi) * (k.mK + k.mPi), c2 = (k.mK - k.mPi) * (k.mK - k.mPi);
+  double ua, ub;
+  u2(e, t, 0u, seed, ua, ub);
+  m = lo + (hi - lo) * ua;
+  // p_B(m) = sqrt((mB^2 - (mJ+m)^2)(mB^2 - (mJ-m)^2)) / (2 mB);  q(m) analogous
+  const double s = k.mB * k.mB;
+  const double pa = s - (k.mJ + m) * (k.mJ + m);
+  const double pb = s - (k.mJ - m) * (k.mJ - m);
+  const double px = pa * pb;
+  const double mm = m * m;
+  const double qa = mm - c1;
+  const double qb = mm - c2;
+  const double qx = qa * qb;
+  if (px > 0.0 && qx > 0.0) {
+    const double w = ub * wmax, l = w * w * (16.0 * s * mm), r = px * qx;
+    if (l < r * (1.0 - 1e-10)) return true;
+    if (l > r * (1.0 + 1e-10)) return false;
+  }
+  const double pB = px <= 0.0 ? 0.0 : sqrt(px) / (2.0 * k.mB);
+  const double q = qx <= 0.0 ? 0.0 : sqrt(qx) / (2.0 * m);
+  return ub * wmax < pB * q;
+}
+constexpr uint32_t kTrials = 4096;   // trials of a proposal before it counts as failed
+// Angles of the proposal e from counters (e, 0, 1) and (e, 0, 2), and the number kept for the
+// accept-reject test.
+__device__ __forceinline__ void phsp_angles(uint64_t e, uint64_t seed, double& ck, double& cj, double& phi,
+                                            double& spare) {
+#pragma clang fp contract(off)
+  double ua, ub;
+  u2(e, 0u, 1u, seed, ua, ub);
+  ck = 2.0 * ua - 1.0;
+  cj = 2.0 * ub - 1.0;
+  u2(e, 0u, 2u, seed, ua, spare);
+  phi = 3.14159265358979323846 * (2.0 * ua - 1.0);
+}
+
+// Seeded analytic acceptance (same definition as the generator's truth efficiency):
+// eps = 0.9 prod_d (1 - delta (1 - t_d)/2), t_d = sum_l a_dl P_l(u_d) / sum_l |a_dl|.
+// (t_d is in [-1, 1] and delta in (0, 1): eps is at most 0.9.)
+__device__ __forceinline__ double acceptance(const double* co, double delta, double lo, double hi, double m, double cK,
+                                             double cJ, double ph) {
+#pragma clang fp contract(off)
+  const double u[4] = {2.0 * (m - lo) / (hi - lo) - 1.0, cK, cJ, ph / 3.14159265358979323846};
+  double eps = 0.9;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const double x = u[d];
+    const double P1 = x, P2 = 0.5 * (3.0 * x * x - 1.0), P3 = 0.5 * (5.0 * x * x * x - 3.0 * x);
+    const double num = co[3 * d] * P1 + co[3 * d + 1] * P2 + co[3 * d + 2] * P3;
+    const double den = fabs(co[3 * d]) + fabs(co[3 * d + 1]) + fabs(co[3 * d + 2]);
+    const double t = den > 0.0 ? num / den : 0.0;
+    eps *= 1.0 - delta * (1.0 - t) / 2.0;
+  }
+  return eps;
 }
 
 // ------------------------------------------------------------------ cross-lane exchange
@@ -323,7 +418,7 @@ template <class Sh> __host__ __device__ constexpr int acc_base(int J) {   // acc
 template <typename T, class Sh, int MODE> struct AmpWaves {
   static constexpr bool lds = MODE == MODE_GRAD && Sh::LDS_HI > Sh::LDS_LO;
   static constexpr bool f32 = std::is_same<T, float>::value;
-  static constexpr int v = lds ? (f32 ? 4 : 2) : (!f32 && Sh::NK > 1 ? 4 : 1);
+  static constexpr int v = MODE == MODE_TOYS ? 2 : (lds ? (f32 ? 4 : 2) : (!f32 && Sh::NK > 1 ? 4 : 1));
 };
 // CC: flavour-tagged events (text after Eq. 12).  Data events carry a tag q = +-1 and are read
 // with phi -> q phi, plus the other flavour with the mistag weight; the normalisation events run
@@ -336,6 +431,7 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
   static_assert(!ZF || Sh::NZ >= 2, "free Z helicities use the second Z's record slots");
   constexpr int NZ = ZF ? 1 : Sh::NZ;   // Z slots evaluated
   constexpr bool GRAD = (MODE == MODE_GRAD);
+  constexpr bool TOYS = (MODE == MODE_TOYS);   // the listed proposals of a ToyArgs chunk
   using A_t = typename AccType<T>::type;   // per-thread gradient accumulator type
 
   const int set = (blockIdx.x < (unsigned)a.nb_data)
@@ -343,11 +439,12 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
                       : ((!CC || blockIdx.x < (unsigned)(a.nb_data + a.nb_mc)) ? 1 : 2);
   const int src = set == 0 ? 0 : 1;   // event set read by this block
   const int64_t blk = (int64_t)blockIdx.x - (set == 0 ? 0 : (set == 1 ? a.nb_data : a.nb_data + a.nb_mc));
-  const int64_t n = a.n[src];
+  const uint32_t tl = TOYS ? blockIdx.x % kToyLists : 0;   // toys: this block's list
+  const int64_t n = TOYS ? (int64_t)a.toys.stat[kToyListed + 16 * tl] : a.n[src];
   const T* __restrict__ col = a.cols[src];
   const int64_t ld = a.ld[src];
-  const int64_t e0 = (int64_t)(((uint64_t)blk * a.step[src]) >> 32) * 256;
-  const int64_t e2 = (int64_t)(((uint64_t)(blk + 1) * a.step[src]) >> 32) * 256;
+  const int64_t e0 = TOYS ? 0 : (int64_t)(((uint64_t)blk * a.step[src]) >> 32) * 256;
+  const int64_t e2 = TOYS ? n : (int64_t)(((uint64_t)(blk + 1) * a.step[src]) >> 32) * 256;
   const int64_t e1 = (blk + 1 < (src == 0 ? a.nb_data : a.nb_mc) && e2 < n) ? e2 : n;
 
   double ms = 0.0, mc = 0.0;   // Kahan pair
@@ -433,7 +530,23 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
   // memory's rate either way (66 against 65 us).
   constexpr int NG = NZ > 0 ? (ZF ? 5 : 4) : 3;
   V4 grp[NG];
+  uint32_t prop = 0;       // toys: this thread's proposal and the number of its accept-reject test
+  double spare = 0.0, eps_true = 1.0;
   auto fetch = [&](uint32_t i) {
+    if constexpr (TOYS) {
+      const ToyArgs& ty = a.toys;
+      prop = ty.list[tl * (((uint32_t)ty.rounds << kRoundBits) / kToyLists) + i];
+      const double m = ty.m[prop];
+      double ck, cj, phi, c[20];
+      phsp_angles((uint64_t)ty.e0 + prop, ty.seed, ck, cj, phi, spare);
+      invariants(ty.kin, m, ck, cj, phi, a.cnt[5] > 0, ZF, c, nullptr);
+      if (ty.acc_on)
+        eps_true = acceptance(ty.coef, ty.delta, ty.kin.mK + ty.kin.mPi, ty.kin.mB - ty.kin.mJ, m, ck, cj, phi);
+#pragma unroll
+      for (int k = 0; k < NG; ++k)
+        if (k < 3 || a.cnt[5] > 0) grp[k] = V4{(T)c[4 * k], (T)c[4 * k + 1], (T)c[4 * k + 2], (T)c[4 * k + 3]};
+      return;
+    }
     const uint32_t ob4 = i * (uint32_t)sizeof(V4);
 #pragma unroll
     for (int k = 0; k < NG; ++k)
@@ -448,7 +561,8 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
   // lets the others catch up.
   __builtin_amdgcn_s_setprio(3);
   uint32_t left = (n_blk + 255) / 256;   // passes of this block still to do
-  for (uint32_t i = threadIdx.x; i < n_blk; i += 256) {
+  for (uint32_t i = TOYS ? blockIdx.x / kToyLists * 256 + threadIdx.x : threadIdx.x; i < n_blk;
+       i += TOYS ? gridDim.x / kToyLists * 256 : 256) {
     if (left == 6) __builtin_amdgcn_s_setprio(2);
     else if (left == 3) __builtin_amdgcn_s_setprio(1);
     else if (left == 1) __builtin_amdgcn_s_setprio(0);
@@ -684,6 +798,13 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
 
     if constexpr (MODE == MODE_DENSITY) {
       a.s_out[set][e] = (double)S;
+      continue;
+    }
+    if constexpr (TOYS) {
+      const ToyArgs& ty = a.toys;
+      const double s = ty.acc_on ? (double)S * eps_true : (double)S;
+      if (s > ty.smax) atomicAdd(&ty.stat[kToyOver + (prop >> kRoundBits)], 1u);
+      if (spare * ty.smax < s) atomicOr(&ty.mask[prop >> 6], 1ull << (prop & 63));
       continue;
     }
 
@@ -933,7 +1054,7 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
     }
   }
 
-  if constexpr (MODE == MODE_DENSITY) return;
+  if constexpr (MODE == MODE_DENSITY || TOYS) return;
 
   if (set == 0) {
     // ln(mprod 2^mexp) as the pair ms - mc: mexp ln2 in two parts, the first exact (29 bits times
@@ -1117,118 +1238,252 @@ __global__ __launch_bounds__(256) void template_kernel(TplArgs a) {
 }
 
 // ------------------------------------------------------------------ generators
-// Philox4x32-10 from its published definition (Salmon et al., SC'11).
-__device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    if (r > 0) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
-    const uint64_t p0 = (uint64_t)0xD2511F53u * c[0];
-    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c[2];
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c[1] ^ k0;
-    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c[3] ^ k1;
-    c[1] = (uint32_t)p1;
-    c[3] = (uint32_t)p0;
-    c[0] = n0;
-    c[2] = n2;
-  }
-}
-__device__ __forceinline__ void u2(uint64_t e, uint32_t w2, uint32_t w3, uint64_t seed, double& ua, double& ub) {
-  uint32_t c[4] = {(uint32_t)e, (uint32_t)(e >> 32), w2, w3};
-  philox4x32_10(c, (uint32_t)seed, (uint32_t)(seed >> 32));
-  ua = (double)(((uint64_t)(c[0] >> 5) << 26) | (uint64_t)(c[1] >> 6)) * (1.0 / 9007199254740992.0);
-  ub = (double)(((uint64_t)(c[2] >> 5) << 26) | (uint64_t)(c[3] >> 6)) * (1.0 / 9007199254740992.0);
-}
-
-#pragma clang fp contract(off)
-// Phase-space event e: m_Kpi by accept-reject on p_B(m) q(m) < u * wmax with trial t drawn
-// from counter (e, t, 0); angles from counters (e, 0, 1) and (e, 0, 2).  The acceptance
-// test is evaluated without contraction so it is bit-identical to a plain FP64 host.
-__device__ int phsp_event(const GenArgs& a, uint64_t e, double* ev, double* spare) {
-  const double lo = a.mK + a.mPi, hi = a.mB - a.mJ;
-  const double c1 = (a.mK + a.mPi) * (a.mK + a.mPi), c2 = (a.mK - a.mPi) * (a.mK - a.mPi);
-  double ua, ub;
-  for (int t = 0; t < 4096; ++t) {
-    u2(e, (uint32_t)t, 0u, a.seed, ua, ub);
-    const double m = lo + (hi - lo) * ua;
-    // p_B(m) = sqrt((mB^2 - (mJ+m)^2)(mB^2 - (mJ-m)^2)) / (2 mB);  q(m) analogous
-    const double s = a.mB * a.mB;
-    const double pa = s - (a.mJ + m) * (a.mJ + m);
-    const double pb = s - (a.mJ - m) * (a.mJ - m);
-    const double px = pa * pb;
-    const double pB = px <= 0.0 ? 0.0 : sqrt(px) / (2.0 * a.mB);
-    const double mm = m * m;
-    const double qa = mm - c1;
-    const double qb = mm - c2;
-    const double qx = qa * qb;
-    const double q = qx <= 0.0 ? 0.0 : sqrt(qx) / (2.0 * m);
-    if (ub * a.wmax < pB * q) {
-      ev[0] = m;
-      u2(e, 0u, 1u, a.seed, ua, ub);
-      ev[1] = 2.0 * ua - 1.0;
-      ev[2] = 2.0 * ub - 1.0;
-      u2(e, 0u, 2u, a.seed, ua, ub);
-      ev[3] = 3.14159265358979323846 * (2.0 * ua - 1.0);
-      *spare = ub;
-      return t + 1;
-    }
-  }
-  return -1;
-}
-
 __global__ __launch_bounds__(256) void phsp_kernel(GenArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
-  double ev[4], sp;
-  const int t = phsp_event(a, (uint64_t)(a.e0 + i), ev, &sp);
-  if (t < 0) { a.flag[i] = 0; a.out[0][i] = NAN; return; }
-  a.out[0][i] = ev[0];
-  a.out[1][i] = ev[1];
-  a.out[2][i] = ev[2];
-  a.out[3][i] = ev[3];
-  if (a.spare) a.spare[i] = sp;
+  const uint64_t e = (uint64_t)(a.e0 + i);
+  double m, ck, cj, phi, spare;
+  uint32_t t = 0;
+  while (t < kTrials && !phsp_trial(a.kin, a.seed, a.wmax, e, t, m)) ++t;
+  if (t == kTrials) { a.flag[i] = 0; a.out[0][i] = NAN; return; }
+  phsp_angles(e, a.seed, ck, cj, phi, spare);
+  a.out[0][i] = m;
+  a.out[1][i] = ck;
+  a.out[2][i] = cj;
+  a.out[3][i] = phi;
   a.flag[i] = 1;
 }
 
-// Seeded analytic acceptance (same definition as the generator's truth efficiency):
-// eps = 0.9 prod_d (1 - delta (1 - t_d)/2), t_d = sum_l a_dl P_l(u_d) / sum_l |a_dl|.
-__device__ double acceptance(const double* co, double delta, double lo, double hi, double m, double cK, double cJ,
-                             double ph) {
-  const double u[4] = {2.0 * (m - lo) / (hi - lo) - 1.0, cK, cJ, ph / 3.14159265358979323846};
-  double eps = 0.9;
-  for (int d = 0; d < 4; ++d) {
-    const double x = u[d];
-    const double P1 = x, P2 = 0.5 * (3.0 * x * x - 1.0), P3 = 0.5 * (5.0 * x * x * x - 3.0 * x);
-    const double num = co[3 * d] * P1 + co[3 * d + 1] * P2 + co[3 * d + 2] * P3;
-    const double den = fabs(co[3 * d]) + fabs(co[3 * d + 1]) + fabs(co[3 * d + 2]);
-    const double t = den > 0.0 ? num / den : 0.0;
-    eps *= 1.0 - delta * (1.0 - t) / 2.0;
-  }
-  return eps;
-}
-#pragma clang fp contract(on)
+// Accept-reject toys.  Of the proposals flat in phase space about one in 200 is kept, so the density
+// is evaluated only where it can matter:
+//   bound_kernel    once per call: an upper bound of eps S in each of kBins mass bins
+//   propose_kernel  the masses of the proposals, and the list of those whose accept-reject number
+//                   lies below the bound of their bin (the others are rejected whatever their angles)
+//   amp_kernel      (MODE_TOYS) angles, density, acceptance and the accept bits of the listed ones
+//   count_kernel, collect_kernel   the accepted ones in the order of the proposals
+// Every step is a pure function of the proposal's number, so the sample does not depend on how the
+// proposals are split.  All columns, flags and densities of every proposal went through memory
+// before (phase space, invariants, density, acceptance, two scans and a copy: 205 us per 2^20
+// proposals, now 18 us).
 
-// Accept flags of proposals: flag = spare * smax < eps * S (S from the density kernel).
-__global__ __launch_bounds__(256) void accept_kernel(AcceptArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.n) return;
-  if (!a.valid[i]) { a.flag[i] = 0; return; }
-  double s = a.S[i];
-  if (a.acc_on) {
-    s *= acceptance(a.coef, a.delta, a.lo, a.hi, a.obs[0][i], a.obs[1][i], a.obs[2][i], a.obs[3][i]);
+// Upper bound of eps S for m_Kpi in bin b.  With the sums of kernel amplitudes P, M, U_0 of the
+// angular part of amp_kernel, the K* chain alone gives S <= |P|^2 + |M|^2 + |U_0|^2 (the rotations
+// by phi and theta_J are unitary), and the Z chain adds at most zmax to sqrt(S).  Each sum is at most
+// the sum of its terms' magnitudes, and over an interval of the mass
+//   |1/D|  <= 1 / sqrt(dist(M^2, [s1, s2])^2 + (P g(s1))^2)        (g grows with the mass)
+//   n_J    <= p_B(m1)^L_B (q/m)(m2)^J / sqrt(B_J(q1) B_LB(p_B2))   (p_B falls, q and q/m grow)
+//   |ang0| <= ang0(1),   |sin ang1| <= 2 ang1(1) / (J + 1)         (Legendre; Bernstein's inequality)
+// The Z angular factors are at most n_Z / sqrt2 in size.  The intervals overlap by 1e-9 of the range
+// and the bound is raised by 1e-6, which covers every rounding.
+template <class Sh> __global__ __launch_bounds__(kBins) void bound_kernel(const AmpArgs<double, Sh> a) {
+  const ToyArgs& ty = a.toys;
+  const Kin& k = ty.kin;
+  auto span = [&](double lo, double hi, double& x1, double& x2) {
+    x1 = fmax(lo, lo + (hi - lo) * ((double)threadIdx.x / kBins - 1e-9));
+    x2 = fmin(hi, lo + (hi - lo) * ((threadIdx.x + 1.0) / kBins + 1e-9));
+  };
+  // breakup momentum of mass M into m1 and m2
+  auto mom = [](double M, double m1, double m2) {
+    return sqrt(fmax(0.0, (M * M - (m1 + m2) * (m1 + m2)) * (M * M - (m1 - m2) * (m1 - m2)))) / (2.0 * M);
+  };
+  auto prop = [](double M2, double P, double s1, double s2, double g1) {
+    const double d = fmax(0.0, fmax(M2 - s2, s1 - M2)), w = P * g1;
+    return 1.0 / sqrt(d * d + w * w);
+  };
+  auto mag = [](const double* h) { return sqrt(h[0] * h[0] + h[1] * h[1]); };
+  // ---- Z chain: the bound over bin threadIdx.x of m_Jpsi pi, then the largest of the block
+  __shared__ double zred[kBins / 64];
+  double z = 0.0;
+  if (Sh::NZ > 0 && a.cnt[5] > 0) {
+    double m1, m2;
+    span(k.mJ + k.mPi, k.mB - k.mK, m1, m2);
+    const double g1 = mom(m1, k.mJ, k.mPi) / m1, pz = mom(k.mB, m1, k.mK);
+    const double nZ = (pz / k.mB) / sqrt(1.0 + k.rB * pz * k.rB * pz);
+    for (int i = 0; i < a.cnt[5]; ++i) {
+      const AC<double>& rc = a.cs[Sh::NK + i];
+      const double h = mag(rc.h[0]) + mag(rc.h[1]) + (a.zfree ? mag(rc.h[2]) : 0.0);
+      if (h > 0.0) z += h * prop(rc.M2, rc.P, m1 * m1, m2 * m2, g1) * nZ * 0.70710678118654752440;
+    }
   }
-  a.over[i] = (s > a.smax) ? 1 : 0;
-  a.flag[i] = (a.spare[i] * a.smax < s) ? 1 : 0;
+  for (int off = 32; off >= 1; off >>= 1) {
+    const double o = __shfl_xor(z, off, 64);
+    z = o > z || o != o ? o : z;   // (a NaN stays: the bound then rejects nothing)
+  }
+  if ((threadIdx.x & 63) == 0) zred[threadIdx.x >> 6] = z;
+  __syncthreads();
+  for (int w = 0; w < kBins / 64; ++w) z = zred[w] > z || zred[w] != zred[w] ? zred[w] : z;
+  // ---- K* chain
+  double m1, m2;
+  span(k.mK + k.mPi, k.mB - k.mJ, m1, m2);
+  const double q1 = mom(m1, k.mK, k.mPi), q2 = mom(m2, k.mK, k.mPi), pB1 = mom(k.mB, m1, k.mJ), pB2 = mom(k.mB, m2, k.mJ);
+  double p = 0.0, mm = 0.0, u0 = 0.0;
+  auto spin = [&](auto Jc) {
+    constexpr int J = decltype(Jc)::value, LB = LBof<J>::v;
+    const double BR = bpoly<J>(a.rR2 * q1 * q1);
+    const double nJ = ipow<double, LB>(pB1) * ipow<double, J>(q2 / m2) / sqrt(BR * bpoly<LB>(a.rB2 * pB2 * pB2));
+    const double gJ = q1 / m1 * ipow<double, J>(q1 * q1) / BR;
+    const double e0 = nJ * ang0<J>(1.0), e1 = J > 0 ? nJ * ang1<J>(1.0) * (2.0 / (J + 1)) : 0.0;
+    for (int j = 0; j < Sh::N[J]; ++j) {
+      const int sl = slot_base<Sh>(J) + j;
+      const AC<double>& rc = a.cs[sl];
+      const double h0 = J > 0 ? mag(rc.h[0]) : 0.0, h1 = mag(rc.h[1]), h2 = J > 0 ? mag(rc.h[2]) : 0.0;
+      if (h0 == 0.0 && h1 == 0.0 && h2 == 0.0) continue;
+      double A = prop(rc.M2, rc.P, m1 * m1, m2 * m2, gJ);
+      if (J == 0 && (a.lass & (1 << sl))) {
+        // m / |u + i q| + P |B|, u = 1/a + b q^2/2
+        const double ua = a.lai[sl] + a.lhb[sl] * q1 * q1, ub = a.lai[sl] + a.lhb[sl] * q2 * q2;
+        const double u = ua * ub > 0.0 ? fmin(fabs(ua), fabs(ub)) : 0.0;
+        A = m2 / sqrt(u * u + q1 * q1) + fabs(rc.P) * A;
+      }
+      p += e1 * h0 * A;
+      mm += e1 * h2 * A;
+      u0 += e0 * h1 * A;
+    }
+  };
+  spin(std::integral_constant<int, 0>{});
+  spin(std::integral_constant<int, 1>{});
+  spin(std::integral_constant<int, 2>{});
+  spin(std::integral_constant<int, 3>{});
+  spin(std::integral_constant<int, 4>{});
+  const double r = sqrt(p * p + mm * mm + u0 * u0) + z;
+  ty.bound[threadIdx.x] = (ty.acc_on ? 0.9 : 1.0) * (r * r * (1.0 + 1e-6));
 }
 
-// Stable compaction of accepted proposals: pos = exclusive prefix sum of flags (computed by
-// the caller), write accepted events to out[base + pos] while pos < limit.
-__global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.n || !a.flag[i]) return;
-  const int64_t p = a.base + a.pos[i];
-  if (p >= a.limit) return;
+// Masses of the proposals and the list of those to evaluate.  A wavefront takes per_wave proposals
+// (a multiple of 64, at most kPerWave); a lane whose proposal has found its mass takes the next one,
+// so a wavefront runs for the mean number of trials (about 2) and not for the longest of 64 (about
+// 7).  Bound by the integer multiplications of Philox, 11 us per 2^20 proposals in a chunk of
+// four of these (44 us for the masses and angles with one proposal per lane).
+constexpr int kPerWave = 1024;
+// Events accepted before this chunk; true if the sample is already complete (the chunk has nothing to do).
+__device__ __forceinline__ bool toys_done(const ToyArgs& a, int64_t& before) {
+  before = a.kept + *reinterpret_cast<const int64_t*>(a.stat - kToyStat + kToySum);
+  return before >= a.limit;
+}
+__global__ __launch_bounds__(256) void propose_kernel(ToyArgs a) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int64_t before;
+  if (toys_done(a, before)) return;
+  __shared__ double mass[4][kPerWave];
+  __shared__ unsigned long long sel[4][kPerWave / 64];
+  const int W = a.per_wave;
+  const uint32_t base = ((uint32_t)blockIdx.x * 4 + wave) * (uint32_t)W;   // (the grid covers the chunk)
+  const uint64_t first = (uint64_t)a.e0 + base;
+  if (lane < W / 64) a.mask[base / 64 + lane] = 0ull;
+  int idx = lane, next = 64;
+  uint32_t t = 0;
+  while (__ballot(idx < W)) {
+    double m = 0.0;
+    bool done = false;
+    if (idx < W) {
+      done = phsp_trial(a.kin, a.seed, a.wmax, first + idx, t, m);
+      if (!done && ++t == kTrials) {
+        m = NAN;   // failed: never listed
+        done = true;
+      }
+    }
+    const unsigned long long b = __ballot(done);
+    if (done) {
+      mass[wave][idx] = m;
+      idx = next + __popcll(b & ((1ull << lane) - 1));
+      t = 0;
+    }
+    next += __popcll(b);
+  }
+  __syncthreads();
+  const double lo = a.kin.mK + a.kin.mPi, hi = a.kin.mB - a.kin.mJ;
+  uint32_t cnt = 0;
+  for (int g = 0; g < W / 64; ++g) {
+    const int j = 64 * g + lane;
+    const double m = mass[wave][j];
+    double ua, spare;
+    u2(first + j, 0u, 2u, a.seed, ua, spare);
+    int bin = (int)((m - lo) / (hi - lo) * kBins);
+    bin = bin < 0 ? 0 : (bin >= kBins ? kBins - 1 : bin);
+    const bool s = m == m && !(spare * a.smax >= a.bound[bin]);
+    const unsigned long long b = __ballot(s);
+    if (lane == 0) sel[wave][g] = b;
+    cnt += __popcll(b);
+  }
+  // room in the block's list: one addition per block, to one of kToyLists lengths (additions to one
+  // address pass one after the other, 13 ns each: with one per wavefront to a single list they took
+  // all of the kernel's time)
+  __shared__ uint32_t wcnt[4], room;
+  if (lane == 0) wcnt[wave] = cnt;
+  __syncthreads();
+  const uint32_t list = blockIdx.x % kToyLists;
+  if (threadIdx.x == 0) room = atomicAdd(&a.stat[kToyListed + 16 * list], (wcnt[0] + wcnt[1]) + (wcnt[2] + wcnt[3]));
+  __syncthreads();
+  uint32_t at = list * (((uint32_t)a.rounds << kRoundBits) / kToyLists) + room;
+  for (int v = 0; v < wave; ++v) at += wcnt[v];
+  for (int g = 0; g < W / 64; ++g) {
+    const unsigned long long b = sel[wave][g];
+    if (b >> lane & 1) {
+      const uint32_t j = 64 * g + lane;
+      a.m[base + j] = mass[wave][j];
+      a.list[at + __popcll(b & ((1ull << lane) - 1))] = base + j;
+    }
+    at += __popcll(b);
+  }
+}
+
+// Accepted proposals of each group.  (Counted as they are found, the 5000 atomic additions per round
+// cost 7 us of the density kernel's 11; this takes one.)
+__global__ __launch_bounds__(256) void count_kernel(ToyArgs a) {
+  int64_t before;
+  if (toys_done(a, before)) return;
+  uint32_t n = __popcll(a.mask[(int64_t)blockIdx.x * 256 + threadIdx.x]);
 #pragma unroll
-  for (int d = 0; d < 4; ++d) a.out[d][p] = a.obs[d][i];
+  for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off, 64);
+  __shared__ uint32_t r[4];
+  if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = n;
+  __syncthreads();
+  if (threadIdx.x == 0) a.stat[kToyCounts + blockIdx.x] = (r[0] + r[1]) + (r[2] + r[3]);
+}
+
+// The accepted proposals of group blockIdx.x (one word of accept bits per thread), written behind those
+// of all earlier ones while there is room; the one that completes the sample leaves its number, and
+// the last group the sum so far.
+__global__ __launch_bounds__(256) void collect_kernel(ToyArgs a) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int64_t before;
+  const bool full = toys_done(a, before);
+  const unsigned* cnt = a.stat + kToyCounts;
+  static_assert((kMaxRounds << (kRoundBits - kGroupBits)) <= 256 && kGroupBits == 14, "one count and one word per thread");
+  __shared__ uint32_t r[4], q[4];
+  const unsigned long long w = full ? 0ull : a.mask[(int64_t)blockIdx.x * 256 + threadIdx.x];
+  uint32_t n = threadIdx.x < blockIdx.x ? cnt[threadIdx.x] : 0;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off, 64);
+  const uint32_t mine = __popcll(w);
+  uint32_t incl = mine;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t o = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += o;
+  }
+  if (lane == 63) {
+    r[wave] = n;
+    q[wave] = incl;
+  }
+  __syncthreads();
+  const int64_t earlier = before + ((r[0] + r[1]) + (r[2] + r[3]));
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+    *reinterpret_cast<int64_t*>(a.stat + kToySum) = earlier - a.kept + ((q[0] + q[1]) + (q[2] + q[3]));
+  int64_t pos = earlier + (incl - mine);
+  for (int v = 0; v < wave; ++v) pos += q[v];
+  for (unsigned long long b = w; b; b &= b - 1, ++pos) {
+    if (pos >= a.limit) return;
+    const uint32_t j = 64 * (256 * blockIdx.x + threadIdx.x) + (uint32_t)__builtin_ctzll(b);
+    const uint64_t e = (uint64_t)a.e0 + j;
+    double ck, cj, phi, spare;
+    phsp_angles(e, a.seed, ck, cj, phi, spare);
+    a.out[0][pos] = a.m[j];
+    a.out[1][pos] = ck;
+    a.out[2][pos] = cj;
+    a.out[3][pos] = phi;
+    if (pos == a.limit - 1) *reinterpret_cast<uint64_t*>(a.stat + kToyLast) = e;
+  }
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1323,15 +1578,38 @@ hipError_t launch_phsp(const GenArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(phsp_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
-hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {
-  if (a.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(accept_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, st, a);
+// One chunk of toys: the proposals, the densities of the listed ones, and the accepted events.
+template <class Sh> hipError_t launch_toys(const AmpArgs<double, Sh>& a, int n_cu, hipStream_t st) {
+  const ToyArgs& t = a.toys;
+  const int64_t n = (int64_t)t.rounds << kRoundBits;
+  const int groups = (int)(n >> kGroupBits);
+  if (t.rounds < 1 || t.rounds > kMaxRounds || t.per_wave < 64 || t.per_wave > kPerWave || n % (4 * kToyLists * t.per_wave))
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(propose_kernel, dim3((unsigned)(n / (4 * t.per_wave))), dim3(256), 0, st, t);
+  AmpArgs<double, Sh> b = a;
+  b.nb_data = (2 * n_cu + kToyLists - 1) / kToyLists * kToyLists;   // whole blocks per list
+  if constexpr (Sh::NZ >= 2) {
+    if (a.zfree) {
+      if (a.cnt[5] != 1) return hipErrorInvalidValue;   // refused by the host API
+      hipLaunchKernelGGL((amp_kernel<double, Sh, MODE_TOYS, false, true>), dim3(b.nb_data), dim3(256), 0, st, b);
+    } else {
+      hipLaunchKernelGGL((amp_kernel<double, Sh, MODE_TOYS, false, false>), dim3(b.nb_data), dim3(256), 0, st, b);
+    }
+  } else {
+    if (a.zfree) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((amp_kernel<double, Sh, MODE_TOYS, false, false>), dim3(b.nb_data), dim3(256), 0, st, b);
+  }
+  hipLaunchKernelGGL(count_kernel, dim3(groups), dim3(256), 0, st, t);
+  hipLaunchKernelGGL(collect_kernel, dim3(groups), dim3(256), 0, st, t);
   return hipGetLastError();
 }
-hipError_t launch_compact(const CompactArgs& a, hipStream_t st) {
-  if (a.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(compact_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, st, a);
+template <class Sh> hipError_t launch_toy_bound(const AmpArgs<double, Sh>& a, hipStream_t st) {
+  hipLaunchKernelGGL(bound_kernel<Sh>, dim3(1), dim3(kBins), 0, st, a);
   return hipGetLastError();
 }
+template hipError_t launch_toys<ShapeSmall>(const AmpArgs<double, ShapeSmall>&, int, hipStream_t);
+template hipError_t launch_toys<ShapeFull>(const AmpArgs<double, ShapeFull>&, int, hipStream_t);
+template hipError_t launch_toy_bound<ShapeSmall>(const AmpArgs<double, ShapeSmall>&, hipStream_t);
+template hipError_t launch_toy_bound<ShapeFull>(const AmpArgs<double, ShapeFull>&, hipStream_t);
 
 }  // namespace kpsi

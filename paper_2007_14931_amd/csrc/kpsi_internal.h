@@ -23,7 +23,7 @@ __host__ __device__ constexpr int64_t col_at(int k, int64_t e, int64_t ld) {
   return ((int64_t)(k >> 2) * ld + e) * 4 + (k & 3);
 }
 
-enum { MODE_DENSITY = 0, MODE_NLL = 1, MODE_GRAD = 2 };
+enum { MODE_DENSITY = 0, MODE_NLL = 1, MODE_GRAD = 2, MODE_TOYS = 3 };
 
 // Per-resonance constants of an interference-matrix build (host-computed in double, stored as T).
 //   den(m) = M2 - m^2 - i P g(m),  A(m) = K n(m) / den(m)
@@ -69,6 +69,39 @@ using ShapeFull = Shape<3, 3, 2, 1, 1, 2>;    // the ten K* of the paper and two
 
 template <typename T> struct AccType { using type = T; };
 
+// Masses of the decay and the barrier radius of the B vertex.
+struct Kin {
+  double mB, mJ, mK, mPi, rB;
+};
+
+// A chunk of accept-reject proposals, `rounds` times 2^kRoundBits of them from number e0 on.  Chunks are
+// enqueued one behind the other; each leaves a record of counters, and reads that of the one before.
+constexpr int kRoundBits = 20, kMaxRounds = 4;
+constexpr int kGroupBits = 14;    // accepted proposals are counted per group of 2^14
+constexpr int kBins = 1024;       // mass bins of the bound
+constexpr int kToyOver = 0;       // record: [r] densities above smax in round r,
+constexpr int kToySum = 6;        //   [6, 7] events accepted by this chunk and those before it,
+constexpr int kToyLast = 8;       //   [8, 9] number of the proposal that completed the sample,
+constexpr int kToyCounts = 10;    //   [10 + g] accepted proposals of group g
+constexpr int kToyListed = kToyCounts + (kMaxRounds << (kRoundBits - kGroupBits));
+constexpr int kToyLists = 16;     //   [kToyListed + 16 s] length of list s (of the blocks s mod 16; lines of their own)
+constexpr int kToyStat = kToyListed + 16 * kToyLists;
+constexpr int kToyChunks = 16;    // chunks enqueued between two synchronisations, at most
+struct ToyArgs {
+  uint64_t seed;
+  int64_t e0, kept, limit;        // kept: events before the first of these chunks; limit: events wanted
+  double wmax, smax;
+  Kin kin;
+  double coef[12], delta;         // analytic acceptance
+  int acc_on, rounds, per_wave;
+  double* bound;                  // kBins upper bounds of the density times the acceptance
+  double* m;                      // mass of each listed proposal, by number in the chunk
+  unsigned* list;                 // listed proposals, in any order: kToyLists lists of equal room
+  unsigned long long* mask;       // accept bits
+  unsigned* stat;                 // this chunk's record, behind that of the chunk before it
+  double* out[4];
+};
+
 template <typename T, class Sh> struct AmpArgs {
   const T* cols[2];     // data, normalisation column bases
   int64_t ld[2];        // column strides (elements)
@@ -112,6 +145,7 @@ template <typename T, class Sh> struct AmpArgs {
   // instantiation that reads the extra angular columns; its lambda' = -1 accumulators take the
   // record slots of the (then unused) second Z.
   int zfree;
+  ToyArgs toys;         // MODE_TOYS only
 };
 // Record slot of sum_i w_i S_i over the data events of the mixture (gradient mode).
 template <class Sh> constexpr int ws_slot() { return 3 + Sh::NKACC + 4 * Sh::NZ + 2 * NFL; }
@@ -120,7 +154,7 @@ template <typename T> struct InvArgs {
   const double* obs[4];   // m_Kpi, cos theta_K*, cos theta_J/psi, phi
   T* cols;
   int64_t ld, n;
-  double mB, mJ, mK, mPi, rB, rR;
+  Kin kin;
   int with_z;
   int zfree;              // with_z and free Z helicities: columns 14-17 hold the separate factors
   double* diag;           // optional (n, 5) output: m_Jpsi pi, cos theta_Z, cos theta~, phi~, alpha
@@ -150,31 +184,10 @@ struct TplArgs {
 struct GenArgs {
   uint64_t seed;
   int64_t e0, n;
-  double wmax, mB, mJ, mK, mPi;
+  double wmax;
+  Kin kin;
   double* out[4];
-  double* spare;
   int* flag;
-};
-
-struct AcceptArgs {
-  const double* obs[4];
-  const double* S;
-  const double* spare;
-  const int* valid;
-  int acc_on;
-  double coef[12];
-  double delta, lo, hi, smax;
-  int64_t n;
-  int* flag;
-  int* over;
-};
-
-struct CompactArgs {
-  const double* obs[4];
-  const int* flag;
-  const int* pos;
-  int64_t n, base, limit;
-  double* out[4];
 };
 
 // Interference-matrix build: per-event component amplitudes of the normalisation set.
@@ -257,8 +270,8 @@ hipError_t launch_reduce_final(const double* partial, int nb_data, int nb_mc, in
 hipError_t launch_hist_lookup(const HistArgs& a, hipStream_t st);
 hipError_t launch_template(const TplArgs& a, hipStream_t st);
 hipError_t launch_phsp(const GenArgs& a, hipStream_t st);
-hipError_t launch_accept(const AcceptArgs& a, hipStream_t st);
-hipError_t launch_compact(const CompactArgs& a, hipStream_t st);
+template <class Sh> hipError_t launch_toy_bound(const AmpArgs<double, Sh>& a, hipStream_t st);
+template <class Sh> hipError_t launch_toys(const AmpArgs<double, Sh>& a, int n_cu, hipStream_t st);
 hipError_t exclusive_scan_int(const int* in, int* out, int64_t n, void* tmp, size_t* tmp_bytes, hipStream_t st);
 
 // Record an error message on a context (the host runtime's kpsi_last_error) and return s.

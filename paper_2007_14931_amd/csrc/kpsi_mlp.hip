@@ -166,7 +166,7 @@ __device__ __forceinline__ float input_map(const MlpArgs& a, int k, double x) {
 // changes hands: silu' of the first layer within the wavefront, and h1 and dz2, between the
 // wavefronts, for the weight gradient, which contracts over all 64 events; these are read back
 // transposed.  One barrier per 64 events (two buffers).  Bound by the latency of a step that has
-// 128 events per compute unit (the weights, the chain of layers, the records): 24.9 -> GRAD_NOW us
+// 128 events per compute unit (the weights, the chain of layers, the records): 24.9 -> 14.0 us
 // for 32768 events (the weights staged through LDS by every block, 128-byte LDS rows, three
 // barriers per 64 events and 60 at the end, each sigmoid evaluated three times).
 __global__ __launch_bounds__(256, 1) void mlp_grad_kernel(MlpArgs a) {
@@ -380,7 +380,7 @@ __device__ __forceinline__ void adam_step(const AdamArgs& a, int i, double g) {
 // s + 4 q + 16 k (s, q = 0..3; of an incomplete last 16, chain 4 s takes the blocks s mod 4), eight
 // reads in flight, and the chains are combined in a fixed order.  The values go to out, or, while
 // training (ADAM), each parameter's update follows at once and the loss goes to loss: 7.0 us and a
-// launch of 4.8 us for 256 records in one of RED_NOW us (64 values a workgroup and four reads in
+// launch of 4.8 us for 256 records in one of 4.5 us (64 values a workgroup and four reads in
 // flight before).
 template <bool ADAM>
 __global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict__ partial, int nb, int nv,

@@ -129,6 +129,8 @@ struct kpsi_ctx {
   int64_t t_n = 0;
   std::vector<float> t_samples;  // the first kTimingSamples timed durations since the last reset
   int64_t t_dropped = 0;         // timed calls whose duration could not be read
+  void* toy_buf = nullptr;             // accept-reject generator buffers (toy_buffers)
+  int64_t toy_rounds = 0;              // rounds they hold
   unsigned short* mlp_w2h = nullptr;   // BF16 copies of the network's 64x64 layer (8192 values)
   int bench_reps = 0;             // kpsi_time_kernel: back-to-back launches of the per-event work
   double bench_ms = 0.0;          // their duration per launch
@@ -472,6 +474,10 @@ Grid pick_grid(kpsi_ctx* c, int mode, int64_t nd, int64_t nm, int nrec, int64_t 
   return g;
 }
 
+Kin kin_of(const kpsi_ctx* c) {
+  return Kin{c->kin.m_b, c->kin.m_jpsi, c->kin.m_k, c->kin.m_pi, c->kin.r_b};
+}
+
 kpsi_status derive_columns(kpsi_ctx* c, int s) {
   DevSet& d = c->set[s];
   if (d.n == 0 || !c->has_model) return KPSI_OK;
@@ -493,8 +499,7 @@ kpsi_status derive_columns(kpsi_ctx* c, int s) {
     a.cols = (T*)d.cols;
     a.ld = ld;
     a.n = d.n;
-    a.mB = c->kin.m_b; a.mJ = c->kin.m_jpsi; a.mK = c->kin.m_k; a.mPi = c->kin.m_pi;
-    a.rB = c->kin.r_b; a.rR = c->kin.r_r;
+    a.kin = kin_of(c);
     a.with_z = c->has_z ? 1 : 0;
     a.zfree = c->zfree ? 1 : 0;
     a.diag = nullptr;
@@ -1084,6 +1089,111 @@ kpsi_status check_ready(kpsi_ctx* c, const double* params) {
   return KPSI_OK;
 }
 
+// Buffers of the accept-reject generator for chunks of r rounds, kept with the context (14 MB for one
+// round, 55 MB for kMaxRounds): bounds, records, masses, accept bits and list.
+kpsi_status toy_buffers(kpsi_ctx* c, int64_t r, ToyArgs& t) {
+  const int64_t p = r << kRoundBits;
+  if (r > c->toy_rounds) {
+    if (c->toy_buf) hipFree(c->toy_buf);
+    c->toy_buf = nullptr;
+    c->toy_rounds = 0;
+    if (hipMalloc(&c->toy_buf, kBins * 8 + (1 + kToyChunks) * kToyStat * 4 + p * 8 + p / 8 + p * 4) != hipSuccess) {
+      c->toy_buf = nullptr;
+      return fail(c, KPSI_E_OOM, "generator buffers");
+    }
+    c->toy_rounds = r;
+  }
+  t.bound = reinterpret_cast<double*>(c->toy_buf);
+  t.stat = reinterpret_cast<unsigned*>(t.bound + kBins);
+  static_assert(kToyStat % 2 == 0 && kToySum % 2 == 0 && kToyLast % 2 == 0, "64-bit entries are aligned");
+  t.m = reinterpret_cast<double*>(t.stat + (1 + kToyChunks) * kToyStat);
+  t.mask = reinterpret_cast<unsigned long long*>(t.m + p);
+  t.list = reinterpret_cast<unsigned*>(t.mask + p / 64);
+  return KPSI_OK;
+}
+
+// Accept-reject toys: proposals in rounds of 2^20.  The first round's yield tells how many rounds the
+// sample needs; these follow in chunks of up to kMaxRounds, enqueued without waiting in between (a
+// chunk behind the one that completes the sample returns at once).  Densities above smax are
+// counted over the whole rounds up to the one that completes the sample.
+template <class Sh>
+kpsi_status generate_toys(kpsi_ctx* c, const double* params, uint64_t seed, int64_t n, double wmax, double smax,
+                          const double* acc_coef, double* m, double* ck, double* cj, double* phi, int64_t* n_prop,
+                          int64_t* n_over) {
+  constexpr int64_t B = (int64_t)1 << kRoundBits, budget = (int64_t)1 << 40;
+  const int n_cu = c->n_cu > 0 ? c->n_cu : 256;
+  AmpArgs<double, Sh> a{};
+  pack<double, Sh>(c, params, a);
+  ToyArgs& t = a.toys;
+  t.seed = seed;
+  t.limit = n;
+  t.wmax = wmax;
+  t.smax = smax;
+  t.kin = kin_of(c);
+  t.acc_on = acc_coef ? 1 : 0;
+  for (int j = 0; j < 12; ++j) t.coef[j] = acc_coef ? acc_coef[j] : 0.0;
+  t.delta = 1.0 - std::pow(3.0, -0.25);
+  t.out[0] = m; t.out[1] = ck; t.out[2] = cj; t.out[3] = phi;
+  int64_t kept = 0, e0 = 0, novr = 0, want = 1;   // want: rounds to enqueue before the next look
+  bool complete = false, bound = false;
+  unsigned h[(1 + kToyChunks) * kToyStat];
+  while (!complete) {
+    const int64_t r = std::min<int64_t>(want, kMaxRounds);
+    const bool grow = r > c->toy_rounds;
+    if (kpsi_status st = toy_buffers(c, std::max(r, c->toy_rounds), t)) return st;
+    unsigned* rec = t.stat;
+    hipError_t e = hipMemsetAsync(rec, 0, sizeof h, c->stream);
+    if (e == hipSuccess && (grow || !bound)) e = launch_toy_bound<Sh>(a, c->stream);
+    bound = true;
+    t.kept = kept;
+    int chunks = 0;
+    int len[kToyChunks];   // rounds of each chunk
+    for (int64_t left = want, at = e0; left > 0 && chunks < kToyChunks && e == hipSuccess; ++chunks) {
+      t.rounds = len[chunks] = (int)std::min(left, r);
+      t.e0 = at;
+      t.stat = rec + (1 + chunks) * kToyStat;
+      // two wavefronts per SIMD of one round's proposals, up to four of a longer chunk's
+      t.per_wave = t.rounds > 1 ? 1024 : 512;
+      e = launch_toys<Sh>(a, n_cu, c->stream);
+      at += t.rounds * B;
+      left -= t.rounds;
+    }
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(h, rec, (1 + chunks) * kToyStat * sizeof(unsigned), hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return fail(c, KPSI_E_HIP, "generator: %s", hipGetErrorString(e));
+    for (int i = 0; i < chunks && !complete; ++i) {
+      const unsigned* x = h + (1 + i) * kToyStat;
+      for (int k = 0; k < len[i] && !complete; ++k) {
+        for (int g = 0; g < 1 << (kRoundBits - kGroupBits); ++g) kept += x[kToyCounts + (k << (kRoundBits - kGroupBits)) + g];
+        novr += x[kToyOver + k];
+        e0 += B;
+        complete = kept >= n;
+        if (!complete && e0 > budget) {
+          *n_prop = e0;
+          *n_over = novr;
+          return fail(c, KPSI_E_ARG, "proposal budget exhausted");
+        }
+      }
+      if (complete) {
+        uint64_t last;
+        std::memcpy(&last, x + kToyLast, sizeof last);
+        e0 = (int64_t)last + 1;
+      }
+    }
+    // rounds the rest needs at the yield so far, and a few more (two standard deviations; twice as many
+    // as before while there is no yield)
+    if (!complete) {
+      const double rest = (double)(n - kept), per = (double)kept / (double)(e0 / B);
+      const double w = kept > 0 ? std::ceil((rest + 2.0 * std::sqrt(rest)) / per) : 2.0 * (double)want;
+      want = (int64_t)std::min(w, (double)(kMaxRounds * kToyChunks));
+    }
+  }
+  *n_prop = e0;
+  *n_over = novr;
+  return KPSI_OK;
+}
+
 }  // namespace
 
 // ================================================================== C ABI
@@ -1140,6 +1250,7 @@ kpsi_status kpsi_destroy(kpsi_ctx* c) {
   }
   if (c->eps) hipFree(c->eps);
   if (c->mlp_w2h) hipFree(c->mlp_w2h);
+  if (c->toy_buf) hipFree(c->toy_buf);
   if (c->eps_f64) hipFree(c->eps_f64);
   if (c->norm_w) hipFree(c->norm_w);
   if (c->wcol) hipFree(c->wcol);
@@ -1830,8 +1941,7 @@ kpsi_status kpsi_invariants(kpsi_ctx* c, kpsi_set set, double* out) {
   a.cols = cols;
   a.ld = ld;
   a.n = s.n;
-  a.mB = c->kin.m_b; a.mJ = c->kin.m_jpsi; a.mK = c->kin.m_k; a.mPi = c->kin.m_pi;
-  a.rB = c->kin.r_b; a.rR = c->kin.r_r;
+  a.kin = kin_of(c);
   a.with_z = 1;
   a.diag = diag;
   hipError_t e = launch_invariants<double>(a, c->stream);
@@ -1853,9 +1963,8 @@ kpsi_status kpsi_generate_phsp(kpsi_ctx* c, uint64_t seed, int64_t n, double wma
   if (hipMalloc(&flag, n * sizeof(int)) != hipSuccess) return fail(c, KPSI_E_OOM, "generator flags");
   GenArgs g{};
   g.seed = seed; g.e0 = 0; g.n = n; g.wmax = wmax;
-  g.mB = c->kin.m_b; g.mJ = c->kin.m_jpsi; g.mK = c->kin.m_k; g.mPi = c->kin.m_pi;
+  g.kin = kin_of(c);
   g.out[0] = m; g.out[1] = ck; g.out[2] = cj; g.out[3] = phi;
-  g.spare = nullptr;
   g.flag = flag;
   hipError_t e = launch_phsp(g, c->stream);
   // every event must have been produced within the trial budget
@@ -1886,112 +1995,8 @@ kpsi_status kpsi_generate_model(kpsi_ctx* c, const double* params, uint64_t seed
     return fail(c, KPSI_E_ARG, "bad generator arguments");
   if (!c->has_model) return fail(c, KPSI_E_STATE, "no model set");
   hipSetDevice(c->device);
-  const int64_t B = 1 << 20;
-  const int64_t ld = B;
-  double *obs = nullptr, *spare = nullptr, *S = nullptr, *cols = nullptr;
-  int *valid = nullptr, *flag = nullptr, *over = nullptr, *pos = nullptr, *opos = nullptr;
-  void* tmp = nullptr;
-  size_t tb = 0;
-  auto cleanup = [&]() {
-    for (void* p : {(void*)obs, (void*)spare, (void*)S, (void*)cols, (void*)valid, (void*)flag, (void*)over,
-                    (void*)pos, (void*)opos, tmp})
-      if (p) hipFree(p);
-  };
-  if (hipMalloc(&obs, 4 * B * sizeof(double)) || hipMalloc(&spare, B * sizeof(double)) ||
-      hipMalloc(&S, B * sizeof(double)) || hipMalloc(&cols, (size_t)ld * NCOL_MAX * sizeof(double)) ||
-      hipMalloc(&valid, B * sizeof(int)) || hipMalloc(&flag, B * sizeof(int)) || hipMalloc(&over, B * sizeof(int)) ||
-      hipMalloc(&pos, B * sizeof(int)) || hipMalloc(&opos, B * sizeof(int))) {
-    cleanup();
-    return fail(c, KPSI_E_OOM, "generator buffers");
-  }
-  exclusive_scan_int(flag, pos, B, nullptr, &tb, c->stream);
-  if (hipMalloc(&tmp, tb)) { cleanup(); return fail(c, KPSI_E_OOM, "scan scratch"); }
-  const double delta = 1.0 - std::pow(3.0, -0.25);
-  int64_t kept = 0, e0 = 0, novr = 0;
-  kpsi_status st = KPSI_OK;
-  std::vector<int> hpos, hflag;
-  while (kept < n) {
-    GenArgs g{};
-    g.seed = seed; g.e0 = e0; g.n = B; g.wmax = wmax;
-    g.mB = c->kin.m_b; g.mJ = c->kin.m_jpsi; g.mK = c->kin.m_k; g.mPi = c->kin.m_pi;
-    for (int j = 0; j < 4; ++j) g.out[j] = obs + j * B;
-    g.spare = spare;
-    g.flag = valid;
-    hipError_t e = launch_phsp(g, c->stream);
-    InvArgs<double> ia{};
-    for (int j = 0; j < 4; ++j) ia.obs[j] = obs + j * B;
-    ia.cols = cols; ia.ld = ld; ia.n = B;
-    ia.mB = c->kin.m_b; ia.mJ = c->kin.m_jpsi; ia.mK = c->kin.m_k; ia.mPi = c->kin.m_pi;
-    ia.rB = c->kin.r_b; ia.rR = c->kin.r_r;
-    ia.with_z = c->has_z ? 1 : 0;
-    ia.zfree = c->zfree ? 1 : 0;
-    if (e == hipSuccess) e = launch_invariants<double>(ia, c->stream);
-    if (e != hipSuccess) { st = fail(c, KPSI_E_HIP, "generator: %s", hipGetErrorString(e)); break; }
-    // density of the proposals through the FP64 amplitude kernel
-    {
-      auto dens = [&](auto shtag) -> hipError_t {
-        using Sh = decltype(shtag);
-        AmpArgs<double, Sh> a{};
-        a.cols[0] = cols; a.ld[0] = ld; a.n[0] = B;
-        a.cols[1] = cols; a.ld[1] = ld; a.n[1] = 0;
-        a.s_out[0] = S; a.s_out[1] = nullptr;
-        a.eps = nullptr;
-        pack<double, Sh>(c, params, a);
-        a.step[0] = (uint64_t)4 << 32;
-        a.nb_data = (int)((B + 4 * BLOCK - 1) / (4 * BLOCK));
-        a.partial = nullptr;
-        return launch_amp<double, Sh>(a, MODE_DENSITY, a.nb_data, c->stream);
-      };
-      e = c->shape == 0 ? dens(ShapeSmall{}) : dens(ShapeFull{});
-    }
-    AcceptArgs aa{};
-    for (int j = 0; j < 4; ++j) aa.obs[j] = obs + j * B;
-    aa.S = S; aa.spare = spare; aa.valid = valid;
-    aa.acc_on = acc_coef ? 1 : 0;
-    for (int j = 0; j < 12; ++j) aa.coef[j] = acc_coef ? acc_coef[j] : 0.0;
-    aa.delta = delta;
-    aa.lo = c->kin.m_k + c->kin.m_pi; aa.hi = c->kin.m_b - c->kin.m_jpsi;
-    aa.smax = smax; aa.n = B; aa.flag = flag; aa.over = over;
-    if (e == hipSuccess) e = launch_accept(aa, c->stream);
-    if (e == hipSuccess) e = exclusive_scan_int(flag, pos, B, tmp, &tb, c->stream);
-    if (e == hipSuccess) e = exclusive_scan_int(over, opos, B, tmp, &tb, c->stream);
-    CompactArgs ca{};
-    for (int j = 0; j < 4; ++j) { ca.obs[j] = obs + j * B; }
-    ca.out[0] = m; ca.out[1] = ck; ca.out[2] = cj; ca.out[3] = phi;
-    ca.flag = flag; ca.pos = pos; ca.n = B; ca.base = kept; ca.limit = n;
-    if (e == hipSuccess) e = launch_compact(ca, c->stream);
-    int tail[4] = {0, 0, 0, 0};
-    if (e == hipSuccess) e = hipMemcpyAsync(&tail[0], pos + B - 1, sizeof(int), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&tail[1], flag + B - 1, sizeof(int), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&tail[2], opos + B - 1, sizeof(int), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&tail[3], over + B - 1, sizeof(int), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) { st = fail(c, KPSI_E_HIP, "generator: %s", hipGetErrorString(e)); break; }
-    const int64_t acc = tail[0] + tail[1];
-    novr += tail[2] + tail[3];
-    if (kept + acc >= n) {
-      // locate the proposal that completes the sample
-      hpos.resize(B);
-      hflag.resize(B);
-      e = hipMemcpy(hpos.data(), pos, B * sizeof(int), hipMemcpyDeviceToHost);
-      if (e == hipSuccess) e = hipMemcpy(hflag.data(), flag, B * sizeof(int), hipMemcpyDeviceToHost);
-      if (e != hipSuccess) { st = fail(c, KPSI_E_HIP, "generator: %s", hipGetErrorString(e)); break; }
-      const int64_t need = n - kept;
-      int64_t last = B - 1;
-      for (int64_t i = 0; i < B; ++i)
-        if (hflag[i] && hpos[i] == need - 1) { last = i; break; }
-      e0 += last + 1;
-      kept = n;
-      break;
-    }
-    kept += acc;
-    e0 += B;
-    if (e0 > ((int64_t)1 << 40)) { st = fail(c, KPSI_E_ARG, "proposal budget exhausted"); break; }
-  }
-  cleanup();
-  *n_prop = e0;
-  *n_over = novr;
-  return st;
+  if (c->shape == 0) return generate_toys<ShapeSmall>(c, params, seed, n, wmax, smax, acc_coef, m, ck, cj, phi, n_prop, n_over);
+  return generate_toys<ShapeFull>(c, params, seed, n, wmax, smax, acc_coef, m, ck, cj, phi, n_prop, n_over);
 }
 
 kpsi_status kpsi_time_kernel(kpsi_ctx* c, const double* params, int grad, int reps, double* ms_per_launch) {
