@@ -41,16 +41,7 @@ template <typename T> __device__ __forceinline__ T ldoff(const T* base, uint32_t
   else return *p;
 }
 
-// Opaque copy of a pointer to uniform kernel-argument data.  Re-deriving it inside the
-// event loop keeps the compiler from hoisting every per-resonance constant out of the
-// loop into vector registers: the constants are re-read with scalar loads instead.
-template <typename P> using kconst_ptr = __attribute__((address_space(4))) const P*;
 template <typename P> using lds_ptr = __attribute__((address_space(3))) P*;   // LDS (32-bit address)
-template <typename P> __device__ __forceinline__ kconst_ptr<P> kernarg_laundered() {
-  kconst_ptr<P> p = (kconst_ptr<P>)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
-  return p;
-}
 
 // FP64: x added to this thread's own LDS slot by an LDS add without a returned value, so nothing
 // waits for the slot.  (The FP32 kernel reads, adds and writes: the LDS add of a float runs at a

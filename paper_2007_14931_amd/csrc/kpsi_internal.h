@@ -25,17 +25,10 @@ __host__ __device__ constexpr int64_t col_at(int k, int64_t e, int64_t ld) {
 
 enum { MODE_DENSITY = 0, MODE_NLL = 1, MODE_GRAD = 2, MODE_TOYS = 3 };
 
-// Per-resonance constants of an interference-matrix build (host-computed in double, stored as T).
-//   den(m) = M2 - m^2 - i P g(m),  A(m) = K n(m) / den(m)
-template <typename T> struct RC {
-  T M2, P, K;
+// Per-resonance constants of an interference-matrix build: D(m) = M2 - m^2 - i P g(m).
+template <typename T> struct alignas(4 * sizeof(T)) RC {
+  T M2, P;
   T M2lo;             // M^2 - M2 (FP32 constants: the rounding remainder of M^2; FP64: 0)
-  T pad0[6];          // (spacing for which the compiler keeps the constants out of spilled registers)
-  T kap, twoM, dP, PoG;   // d ln K/dM, 2M, dP/dM, P/Gamma0
-  int flt;            // floating slot or -1
-  T pad1[2];
-  int lass;           // 1: LASS S-wave (spin-0 K* only), 0: Breit-Wigner
-  T lai, lhb;         // LASS 1/a and b/2: q cot(delta_B) = lai + lhb q^2
 };
 
 // Per-resonance constants of the per-event kernel: eight values, so that one scalar load (32 bytes
@@ -197,12 +190,16 @@ template <typename T, class Sh> struct ImArgs {
   const T* eps;         // per-event efficiency or null
   double* partial;      // block partials of the Gram tiles, in 32-byte records (four values)
   int ncols;            // real columns in use (even; at most the kernel's padded width)
-  int skip_last;        // 1: the last diagonal 16 x 16 tile has derivative columns only; skip it
+  int skip_first;       // 1: the first 16 x 16 tile has derivative columns only; skip it
   int cnt[6];
-  int dcol[NFL];        // first derivative component of floating slot f
-  T rR, rB, invMB;
-  RC<T> ks[Sh::NK > 0 ? Sh::NK : 1];
-  RC<T> zs[Sh::NZ > 0 ? Sh::NZ : 1];
+  // complex columns: first p, m column; first u column; first derivative columns of floating slot f
+  // among the p, m and Z columns' and among the u columns'
+  int baseA, baseB, dA[NFL], dB[NFL];
+  unsigned flt, flt1;   // bit k: K* slot k (NK + z: Z slot z) has a floating lineshape; is that of floating slot 1
+  T rR2, rB2;           // squared barrier radii
+  RC<T> rc[Sh::NK + Sh::NZ];   // K* slots, then Z slots
+  int lass;             // bit k: K* slot k is a LASS S-wave
+  T lai[Sh::NK], lhb[Sh::NK];   // LASS 1/a and b/2: q cot(delta_B) = lai + lhb q^2
   int zfree;            // one Z with independent H'_{+1}, H'_{-1}: three Z components (0, +1, -1)
 };
 

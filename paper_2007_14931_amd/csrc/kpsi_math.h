@@ -2,7 +2,7 @@
 // hardware reciprocal and reciprocal square root (refined by Newton steps in FP64), the
 // normalised Blatt-Weisskopf polynomials, and the small-d functions d^J_{00}, d^J_{10} of the
 // K* helicity angle (Eq. 4).  One copy, so both kernels evaluate the same lineshape and
-// angular polynomials.
+// angular polynomials.  Also the opaque kernel-argument pointer both use in their event loops.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -104,6 +104,16 @@ template <int J, typename T> __device__ __forceinline__ T d10(T c, T s) {
   else if constexpr (J == 3) return -s * (T(15) * c * c - T(3)) * T(0.14433756729740644113);
   else if constexpr (J == 4) return -s * c * (T(35) * c * c - T(15)) * T(0.11180339887498948482);
   else return T(0);
+}
+
+// Opaque copy of a pointer to uniform kernel-argument data.  Re-deriving it inside the
+// event loop keeps the compiler from hoisting every per-resonance constant out of the
+// loop into vector registers: the constants are re-read with scalar loads instead.
+template <typename P> using kconst_ptr = __attribute__((address_space(4))) const P*;
+template <typename P> __device__ __forceinline__ kconst_ptr<P> kernarg_laundered() {
+  kconst_ptr<P> p = (kconst_ptr<P>)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
 }
 
 // First K* slot of spin J in a compiled kernel shape (slots are ordered by spin).

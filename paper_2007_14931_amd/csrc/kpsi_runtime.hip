@@ -335,20 +335,20 @@ template <typename T, class Sh> void pack_im(const kpsi_ctx* c, const double* pa
   for (size_t i = 0; i < c->res.size(); ++i) {
     const kpsi_resonance& r = c->res[i];
     const LsConst lc = lineshape_consts(c->kin, r, par[ncr + 2 * i], par[ncr + 2 * i + 1]);
-    RC<T>& rc = r.chain == 0 ? a.ks[c->slot[i]] : a.zs[c->slot[i]];
-    rc.M2 = (T)lc.M2; rc.P = (T)lc.P; rc.K = (T)lc.K;
+    const int slot = (r.chain == 0 ? 0 : Sh::NK) + c->slot[i];
+    RC<T>& rc = a.rc[slot];
+    rc.M2 = (T)lc.M2; rc.P = (T)lc.P;
     rc.M2lo = (T)(lc.M2 - (double)rc.M2);
-    rc.kap = (T)lc.kap; rc.twoM = (T)lc.twoM; rc.dP = (T)lc.dP; rc.PoG = (T)lc.PoG;
-    rc.flt = c->fslot[i];
-    rc.lass = r.shape == 1 ? 1 : 0;
-    rc.lai = r.shape == 1 ? (T)(1.0 / r.lass_a) : T(0);
-    rc.lhb = r.shape == 1 ? (T)(0.5 * r.lass_b) : T(0);
+    if (r.shape == 1) {
+      a.lass |= 1 << slot;
+      a.lai[slot] = (T)(1.0 / r.lass_a);
+      a.lhb[slot] = (T)(0.5 * r.lass_b);
+    }
   }
   a.zfree = c->zfree ? 1 : 0;
   for (int j = 0; j < 6; ++j) a.cnt[j] = c->cnt[j];
-  a.rR = (T)c->kin.r_r;
-  a.rB = (T)c->kin.r_b;
-  a.invMB = (T)(1.0 / c->kin.m_b);
+  a.rR2 = (T)(c->kin.r_r * c->kin.r_r);
+  a.rB2 = (T)(c->kin.r_b * c->kin.r_b);
 }
 
 // Accumulator offset of the couplings of table resonance i inside the block record.
@@ -625,23 +625,80 @@ template <typename T, class Sh>
 kpsi_status gram_build_t(kpsi_ctx* c, const double* par, bool with_eps, bool with_deriv, Gram& g) {
   const DevSet& d = c->set[1];
   const int ncomp = n_components(c->shape);
-  int nderiv = 0;
-  int dcol[NFL] = {0, 0};
-  if (with_deriv) {
-    for (size_t i = 0; i < c->res.size(); ++i) {
-      if (c->fslot[i] < 0) continue;
-      int k0, nk;
-      components_of(c, i, &k0, &nk);
-      dcol[c->fslot[i]] = ncomp + nderiv;
-      nderiv += 2 * nk;
-    }
+  // helicity components and their lineshape derivatives as weighted sums of the kernel's columns:
+  // lambda = +-1 of a K* is m +- p, free lambda' = +-1 of a Z the sum +- the difference, each times K
+  // and the constant factors; dA/dM = kappa A - 2M E + dP/dM F, dA/dGamma0 = P/Gamma0 F
+  struct Of {
+    int n = 0, col[6];
+    double w[6];
+    void add(int c, double x) { col[n] = c; w[n++] = x; }
+  };
+  constexpr int kMaxComp = 48;
+  Of of[kMaxComp];
+  int nda = 0, ndb = 0, nderiv = 0, nz = 0;   // derivative columns (p, m, Z; u), derivative components, Z columns
+  int dcol[NFL] = {0, 0}, dA[NFL] = {0, 0}, dB[NFL] = {0, 0};
+  for (size_t i = 0; i < c->res.size(); ++i) {
+    const kpsi_resonance& r = c->res[i];
+    if (r.chain == 1) nz += ncoup(r);
+    const int f = with_deriv ? c->fslot[i] : -1;
+    if (f < 0) continue;
+    int k0, nk;
+    components_of(c, i, &k0, &nk);
+    dcol[f] = ncomp + nderiv;
+    nderiv += 2 * nk;
+    dA[f] = nda;
+    dB[f] = ndb;
+    nda += r.chain == 1 ? 2 * nk : (r.spin > 0 ? 4 : 0);
+    ndb += r.chain == 1 ? 0 : 2;
   }
-  const int ncx = ncomp + nderiv;
+  const int n0 = Sh::N[0];
+  const int baseA = nda, baseB = nda + 2 * (Sh::NK - n0) + nz;
+  for (int f = 0; f < NFL; ++f) dB[f] += baseB + Sh::NK;
+  const int ncx = baseB + Sh::NK + ndb;
+  for (size_t i = 0; i < c->res.size(); ++i) {
+    const kpsi_resonance& r = c->res[i];
+    int k0, nk;
+    components_of(c, i, &k0, &nk);
+    const int ncr = c->nparams - 2 * (int)c->res.size();
+    const LsConst lc = lineshape_consts(c->kin, r, par[ncr + 2 * i], par[ncr + 2 * i + 1]);
+    const CoupScale cs = coup_scale(c->kin, r);
+    // x times the lineshape columns at `a` (the first p, m or Z column) and `u` into the components k ..
+    auto put = [&](int k, int a, int u, double x) {
+      const double e0 = lc.K * cs.e0 * x, e1 = lc.K * cs.e1 * x, eh = lc.K * M_SQRT1_2 * x;
+      if (r.chain == 0) {
+        of[r.spin > 0 ? k + 1 : k].add(u, e0);
+        if (r.spin > 0) {
+          of[k].add(a + 1, e1);
+          of[k].add(a, -e1);
+          of[k + 2].add(a + 1, e1);
+          of[k + 2].add(a, e1);
+        }
+        return;
+      }
+      of[k].add(a, e0);
+      of[k + 1].add(a + 1, nk == 3 ? eh : e1);
+      if (nk == 3) {
+        of[k + 1].add(a + 2, eh);
+        of[k + 2].add(a + 1, eh);
+        of[k + 2].add(a + 2, -eh);
+      }
+    };
+    const int sl = c->slot[i];
+    const int a0 = r.chain == 1 ? baseA + 2 * (Sh::NK - n0) + 2 * sl : baseA + 2 * (sl - n0), u0 = baseB + sl;
+    put(k0, a0, u0, 1.0);
+    const int f = with_deriv ? c->fslot[i] : -1;
+    if (f < 0) continue;
+    const int aF = dA[f] + (r.chain == 1 ? nk : 2);   // columns of F, behind those of E
+    put(dcol[f], a0, u0, lc.kap);
+    put(dcol[f], dA[f], dB[f], -lc.twoM);
+    put(dcol[f], aF, dB[f] + 1, lc.dP);
+    put(dcol[f] + nk, aF, dB[f] + 1, lc.PoG);
+  }
   const int ncols = 2 * ncx;
   const int C = ncols <= 16 ? 16 : ncols <= 32 ? 32 : ncols <= 64 ? 64 : ncols <= 80 ? 80 : 0;
   if (!C) return fail(c, KPSI_E_UNSUPPORTED, "interference matrix of %d columns exceeds the compiled 80", ncols);
   const int NT = C / 16, NTILE = NT * (NT + 1) / 2, nv = NTILE * 256;
-  const int64_t ntiles = (d.n + 31) / 32;
+  const int64_t ntiles = (d.n + 63) / 64;
   // one resident round of one-wavefront blocks (their LDS rows limit them per compute unit)
   const int bpc = imatrix_blocks_per_cu<T, Sh>(ncols);
   const int64_t cap = (int64_t)(c->n_cu > 0 ? c->n_cu : 256) * (bpc > 0 ? bpc : 4);
@@ -669,11 +726,17 @@ kpsi_status gram_build_t(kpsi_ctx* c, const double* par, bool with_eps, bool wit
   a.eps = with_eps ? (const T*)c->eps : (const T*)c->wcol;   // wcol: importance weights or null
   a.partial = c->cache_partial;
   a.ncols = ncols;
-  a.skip_last = (NT > 1 && 16 * (NT - 1) >= 2 * ncomp) ? 1 : 0;
-  for (int f = 0; f < NFL; ++f) a.dcol[f] = dcol[f];
-  if (!with_deriv) {   // no derivative columns: every lineshape counts as fixed in this matrix
-    for (int k = 0; k < (Sh::NK > 0 ? Sh::NK : 1); ++k) a.ks[k].flt = -1;
-    for (int k = 0; k < (Sh::NZ > 0 ? Sh::NZ : 1); ++k) a.zs[k].flt = -1;
+  a.skip_first = 2 * nda >= 16 ? 1 : 0;
+  a.baseA = baseA;
+  a.baseB = baseB;
+  for (int f = 0; f < NFL; ++f) { a.dA[f] = dA[f]; a.dB[f] = dB[f]; }
+  static_assert(NFL == 2 && Sh::NK + Sh::NZ <= 32, "one mask bit per slot");
+  for (size_t i = 0; i < c->res.size(); ++i) {
+    const int f = with_deriv ? c->fslot[i] : -1;
+    if (f < 0) continue;
+    const unsigned bit = 1u << ((c->res[i].chain == 0 ? 0 : Sh::NK) + c->slot[i]);
+    a.flt |= bit;
+    if (f == 1) a.flt1 |= bit;
   }
   hipEvent_t e0 = c->ev0, e1 = c->ev1;
   hipEventRecord(e0, c->stream);
@@ -701,21 +764,26 @@ kpsi_status gram_build_t(kpsi_ctx* c, const double* par, bool with_eps, bool wit
           G[(size_t)row * C + col] = v;
           G[(size_t)col * C + row] = v;
         }
-  // complex blocks: sum B_k conj(B_l) = (G[2k][2l] + G[2k+1][2l+1]) + i (G[2k+1][2l] - G[2k][2l+1])
-  auto cre = [&](int k, int l) { return G[(size_t)(2 * k) * C + 2 * l] + G[(size_t)(2 * k + 1) * C + 2 * l + 1]; };
-  auto cim = [&](int k, int l) { return G[(size_t)(2 * k + 1) * C + 2 * l] - G[(size_t)(2 * k) * C + 2 * l + 1]; };
+  // complex blocks of the columns: sum B_k conj(B_l) = (G[2k][2l] + G[2k+1][2l+1]) + i (G[2k+1][2l] -
+  // G[2k][2l+1]); of two components, over their columns (of derivatives with components only)
+  auto block = [&](const Of& x, const Of& y, double* out2) {
+    double re = 0.0, im = 0.0;
+    for (int i = 0; i < x.n; ++i)
+      for (int j = 0; j < y.n; ++j) {
+        const double w = x.w[i] * y.w[j];
+        const double *gr = &G[(size_t)(2 * x.col[i]) * C + 2 * y.col[j]], *gi = gr + C;
+        re += w * (gr[0] + gi[1]);
+        im += w * (gi[0] - gr[1]);
+      }
+    out2[0] = re;
+    out2[1] = im;
+  };
   g.I.assign(2 * (size_t)ncomp * ncomp, 0.0);
-  for (int k = 0; k < ncomp; ++k)
-    for (int l = 0; l < ncomp; ++l) {
-      g.I[2 * ((size_t)k * ncomp + l)] = cre(k, l);
-      g.I[2 * ((size_t)k * ncomp + l) + 1] = cim(k, l);
-    }
   g.D.assign(2 * (size_t)nderiv * ncomp, 0.0);
+  for (int k = 0; k < ncomp; ++k)
+    for (int l = 0; l < ncomp; ++l) block(of[k], of[l], &g.I[2 * ((size_t)k * ncomp + l)]);
   for (int dd = 0; dd < nderiv; ++dd)
-    for (int l = 0; l < ncomp; ++l) {
-      g.D[2 * ((size_t)dd * ncomp + l)] = cre(ncomp + dd, l);
-      g.D[2 * ((size_t)dd * ncomp + l) + 1] = cim(ncomp + dd, l);
-    }
+    for (int l = 0; l < ncomp; ++l) block(of[ncomp + dd], of[l], &g.D[2 * ((size_t)dd * ncomp + l)]);
   g.ncomp = ncomp;
   g.nderiv = nderiv;
   for (int f = 0; f < NFL; ++f) g.dcol[f] = dcol[f];
