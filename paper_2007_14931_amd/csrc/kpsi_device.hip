@@ -191,8 +191,14 @@ __global__ __launch_bounds__(256) void invariants_kernel(InvArgs<T> a) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= a.n) return;
   double c[18];
-  invariants(a.kin, a.obs[0][e], a.obs[1][e], a.obs[2][e], a.obs[3][e], a.with_z, a.zfree, c,
-             a.diag ? a.diag + 5 * e : nullptr);
+  const double m = a.obs[0][e], ck = a.obs[1][e], cj = a.obs[2][e], ph = a.obs[3][e];
+  if (a.bad) {
+    const double tol = 1e-12;
+    const bool ok = m >= a.lo - tol && m <= a.hi + tol && fabs(ck) <= 1.0 + tol && fabs(cj) <= 1.0 + tol &&
+                    fabs(ph) <= 3.14159265358979323846 + tol;
+    if (!ok) *a.bad = 1u;   // (the same value from whichever events: no atomic operation)
+  }
+  invariants(a.kin, m, ck, cj, ph, a.with_z, a.zfree, c, a.diag ? a.diag + 5 * e : nullptr);
 #pragma unroll
   for (int k = 0; k < 18; ++k) {
     const bool z = k == 9 || k > 10;   // a Z column

@@ -151,6 +151,8 @@ template <typename T> struct InvArgs {
   int with_z;
   int zfree;              // with_z and free Z helicities: columns 14-17 hold the separate factors
   double* diag;           // optional (n, 5) output: m_Jpsi pi, cos theta_Z, cos theta~, phi~, alpha
+  unsigned* bad;          // optional: set to 1 by an event outside the physical region, m in [lo, hi]
+  double lo, hi;
 };
 
 struct HistArgs {

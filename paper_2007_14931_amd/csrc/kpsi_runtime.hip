@@ -96,7 +96,7 @@ struct kpsi_ctx {
   double* partial = nullptr;
   size_t partial_cap = 0;       // in doubles
   double* red = nullptr;        // device view of red_host
-  double* red_host = nullptr;   // [3][NACC], mapped pinned host memory (fine-grained, so the
+  double* red_host = nullptr;   // [3][NACC] and the flag of the event check, mapped pinned host memory (fine-grained, so the
                                 // reduction's stores reach it as they are made): data,
                                 // normalisation, and the normalisation read with phi reversed
                                 // (flavour tags).  A call marks the values its reduction writes
@@ -478,7 +478,9 @@ Kin kin_of(const kpsi_ctx* c) {
   return Kin{c->kin.m_b, c->kin.m_jpsi, c->kin.m_k, c->kin.m_pi, c->kin.r_b};
 }
 
-kpsi_status derive_columns(kpsi_ctx* c, int s) {
+// The event columns of set s.  With `check`, each event is also held against the physical region in the
+// same pass; events outside leave the set empty.
+kpsi_status derive_columns(kpsi_ctx* c, int s, bool check = false) {
   DevSet& d = c->set[s];
   if (d.n == 0 || !c->has_model) return KPSI_OK;
   const int ncol = NCOL_KSTAR + (c->has_z ? NCOL_Z : 0) + (c->zfree ? NCOL_ZFREE : 0);
@@ -492,6 +494,9 @@ kpsi_status derive_columns(kpsi_ctx* c, int s) {
     d.cols_cap = bytes;
   }
   d.ld = ld;
+  const double lo = c->kin.m_k + c->kin.m_pi, hi = c->kin.m_b - c->kin.m_jpsi;
+  volatile unsigned* bad = reinterpret_cast<unsigned*>(c->red_host + 3 * NACC);
+  *bad = 0;
   auto go = [&](auto tag) -> hipError_t {
     using T = decltype(tag);
     InvArgs<T> a{};
@@ -503,21 +508,22 @@ kpsi_status derive_columns(kpsi_ctx* c, int s) {
     a.with_z = c->has_z ? 1 : 0;
     a.zfree = c->zfree ? 1 : 0;
     a.diag = nullptr;
+    a.bad = check ? reinterpret_cast<unsigned*>(c->red + 3 * NACC) : nullptr;
+    a.lo = lo;
+    a.hi = hi;
     return launch_invariants<T>(a, c->stream);
   };
   hipError_t e = c->prec == KPSI_FP32 ? go(float{}) : go(double{});
-  if (e != hipSuccess) return fail(c, KPSI_E_HIP, "invariants kernel: %s", hipGetErrorString(e));
+  if (e == hipSuccess && check) e = hipStreamSynchronize(c->stream);
+  if (e != hipSuccess) {
+    if (check) d.n = 0;
+    return fail(c, KPSI_E_HIP, "invariants kernel: %s", hipGetErrorString(e));
+  }
+  if (check && *bad) {
+    d.n = 0;
+    return fail(c, KPSI_E_ARG, "event outside the physical region (m in [%.6f, %.6f], |cos| <= 1, |phi| <= pi)", lo, hi);
+  }
   return KPSI_OK;
-}
-
-__global__ void validate_kernel(const double* m, const double* ck, const double* cj, const double* ph, int64_t n,
-                                double lo, double hi, unsigned int* bad) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double tol = 1e-12;
-  const bool ok = (m[i] >= lo - tol) && (m[i] <= hi + tol) && (fabs(ck[i]) <= 1.0 + tol) &&
-                  (fabs(cj[i]) <= 1.0 + tol) && (fabs(ph[i]) <= 3.14159265358979323846 + tol);
-  if (!ok) atomicOr(bad, 1u);
 }
 
 template <typename T> __global__ void to_t_kernel(const double* in, T* out, int64_t n) {
@@ -542,24 +548,6 @@ kpsi_status product_column(kpsi_ctx* c, const double* a, const double* b, void**
   if (er != hipSuccess) { hipFree(e); return fail(c, KPSI_E_HIP, "column product: %s", hipGetErrorString(er)); }
   if (*col) hipFree(*col);
   *col = e;
-  return KPSI_OK;
-}
-
-kpsi_status validate(kpsi_ctx* c, int64_t n, const double* const* obs) {
-  if (n == 0) return KPSI_OK;
-  unsigned int* bad = nullptr;
-  HIPCHECK(c, hipMalloc(&bad, sizeof(unsigned int)));
-  hipMemsetAsync(bad, 0, sizeof(unsigned int), c->stream);
-  const double lo = c->kin.m_k + c->kin.m_pi, hi = c->kin.m_b - c->kin.m_jpsi;
-  hipLaunchKernelGGL(validate_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, obs[0], obs[1],
-                     obs[2], obs[3], n, lo, hi, bad);
-  unsigned int h = 0;
-  hipMemcpyAsync(&h, bad, sizeof h, hipMemcpyDeviceToHost, c->stream);
-  hipError_t e = hipStreamSynchronize(c->stream);
-  hipFree(bad);
-  if (e != hipSuccess) return fail(c, KPSI_E_HIP, "validation: %s", hipGetErrorString(e));
-  if (h) return fail(c, KPSI_E_ARG, "event outside the physical region (m in [%.6f, %.6f], |cos| <= 1, |phi| <= pi)",
-                     lo, hi);
   return KPSI_OK;
 }
 
@@ -1291,11 +1279,11 @@ kpsi_status kpsi_create(int device, void* stream, kpsi_precision prec, kpsi_ctx*
   }
   // fine-grained where the system has it (each value is seen as the reduction stores it);
   // otherwise the values appear when the reduction kernel ends, and the poll still works
-  if (hipHostMalloc(&c->red_host, 3 * NACC * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=
+  if (hipHostMalloc(&c->red_host, (3 * NACC + 1) * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=
       hipSuccess) {
     (void)hipGetLastError();
     c->red_host = nullptr;
-    if (hipHostMalloc(&c->red_host, 3 * NACC * sizeof(double), hipHostMallocMapped) != hipSuccess) c->red_host = nullptr;
+    if (hipHostMalloc(&c->red_host, (3 * NACC + 1) * sizeof(double), hipHostMallocMapped) != hipSuccess) c->red_host = nullptr;
   }
   if (!c->red_host || hipHostGetDevicePointer((void**)&c->red, c->red_host, 0) != hipSuccess ||
       hipMalloc(&c->red_dev, 3 * NACC * sizeof(double)) != hipSuccess) {
@@ -1595,6 +1583,18 @@ static void drop_norm_columns(kpsi_ctx* c) {
   c->norm_w_host.clear();
 }
 
+// The n events at the set's observables become the set: checked and their columns derived in one pass.
+static kpsi_status take_events(kpsi_ctx* c, kpsi_set set, int64_t n) {
+  c->set[set].n = n;
+  if (kpsi_status st = derive_columns(c, set, true)) {
+    c->set[set].n = 0;
+    return st;
+  }
+  if (set == KPSI_NORM) drop_norm_columns(c);
+  if (set == KPSI_NORM) invalidate_cache(c);
+  return KPSI_OK;
+}
+
 kpsi_status kpsi_load_events(kpsi_ctx* c, kpsi_set set, int64_t n, const double* m, const double* ck,
                              const double* cj, const double* phi) {
   kpsi_status st = load_common(c, set, n);
@@ -1611,15 +1611,7 @@ kpsi_status kpsi_load_events(kpsi_ctx* c, kpsi_set set, int64_t n, const double*
     d.obs[j] = d.owned + (size_t)j * n;
     HIPCHECK(c, hipMemcpyAsync((void*)d.obs[j], src[j], n * sizeof(double), hipMemcpyHostToDevice, c->stream));
   }
-  st = validate(c, n, d.obs);
-  if (st) return st;
-  d.n = n;
-  if (set == KPSI_NORM) drop_norm_columns(c);
-  if (set == KPSI_NORM) invalidate_cache(c);
-  st = derive_columns(c, set);
-  if (st) return st;
-  HIPCHECK(c, hipStreamSynchronize(c->stream));
-  return KPSI_OK;
+  return take_events(c, set, n);
 }
 
 kpsi_status kpsi_load_events_device(kpsi_ctx* c, kpsi_set set, int64_t n, const double* m, const double* ck,
@@ -1633,16 +1625,8 @@ kpsi_status kpsi_load_events_device(kpsi_ctx* c, kpsi_set set, int64_t n, const 
   d.owned = nullptr;
   d.n = 0;
   const double* src[4] = {m, ck, cj, phi};
-  st = validate(c, n, src);
-  if (st) return st;
   for (int j = 0; j < 4; ++j) d.obs[j] = src[j];
-  d.n = n;
-  if (set == KPSI_NORM) drop_norm_columns(c);
-  if (set == KPSI_NORM) invalidate_cache(c);
-  st = derive_columns(c, set);
-  if (st) return st;
-  HIPCHECK(c, hipStreamSynchronize(c->stream));
-  return KPSI_OK;
+  return take_events(c, set, n);
 }
 
 // The per-event column the kernels read: efficiency times importance weight (null when both are 1).
