@@ -412,10 +412,12 @@ template <class Sh> __host__ __device__ constexpr int acc_base(int J) {   // acc
 // most 128 or 256 registers; its spin-1..3 accumulators live in LDS to make room (36 values x
 // 256 threads: 36 KB per block in FP32, 4 blocks per compute unit; 72 KB in FP64, 2 blocks).
 // The FP64 likelihood-only and density kernels of the large shape ask for 4 (128 registers).
-template <typename T, class Sh, int MODE> struct AmpWaves {
+// The FP32 likelihood-only one without tags asks for 8 (64
+// registers): it waits for memory more than it issues (33.6 against 36.9 us for 3e6 events).
+template <typename T, class Sh, int MODE, bool CC> struct AmpWaves {
   static constexpr bool lds = MODE == MODE_GRAD && Sh::LDS_HI > Sh::LDS_LO;
   static constexpr bool f32 = std::is_same<T, float>::value;
-  static constexpr int v = MODE == MODE_TOYS ? 2 : (lds ? (f32 ? 4 : 2) : (!f32 && Sh::NK > 1 ? 4 : 1));
+  static constexpr int v = MODE == MODE_TOYS ? 2 : (lds ? (f32 ? 4 : 2) : Sh::NK == 1 ? 1 : !f32 ? 4 : CC ? 1 : 8);
 };
 // CC: flavour-tagged events (text after Eq. 12).  Data events carry a tag q = +-1 and are read
 // with phi -> q phi, plus the other flavour with the mistag weight; the normalisation events run
@@ -423,7 +425,7 @@ template <typename T, class Sh, int MODE> struct AmpWaves {
 // ZF: one Z whose H'_{+1} and H'_{-1} are independent couplings (no Eq. 11 relation); its
 // lambda' = -1 accumulators use the record slots of the second Z.
 template <typename T, class Sh, int MODE, bool CC, bool ZF>
-__global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(const AmpArgs<T, Sh> a) {
+__global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kernel(const typename AmpArgsOf<T, Sh, MODE>::type a) {
   constexpr int NK = Sh::NK;
   static_assert(!ZF || Sh::NZ >= 2, "free Z helicities use the second Z's record slots");
   constexpr int NZ = ZF ? 1 : Sh::NZ;   // Z slots evaluated
@@ -437,7 +439,8 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
   const int src = set == 0 ? 0 : 1;   // event set read by this block
   const int64_t blk = (int64_t)blockIdx.x - (set == 0 ? 0 : (set == 1 ? a.nb_data : a.nb_data + a.nb_mc));
   const uint32_t tl = TOYS ? blockIdx.x % kToyLists : 0;   // toys: this block's list
-  const int64_t n = TOYS ? (int64_t)a.toys.stat[kToyListed + 16 * tl] : a.n[src];
+  int64_t n = a.n[src];
+  if constexpr (TOYS) n = (int64_t)a.toys.stat[kToyListed + 16 * tl];
   const T* __restrict__ col = a.cols[src];
   const int64_t ld = a.ld[src];
   const int64_t e0 = TOYS ? 0 : (int64_t)(((uint64_t)blk * a.step[src]) >> 32) * 256;
@@ -519,13 +522,15 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
   using V4 = T __attribute__((ext_vector_type(4)));
   const V4* __restrict__ gb = (const V4*)col + e0;   // column group 0 at this block's first event
   const uint32_t n_blk = (uint32_t)(e1 > e0 ? e1 - e0 : 0);
-  // Column groups of this thread's event.  The FP64 gradient kernel (two wavefronts per SIMD)
-  // fetches the next event's as soon as the current ones are used up, before the accumulation
-  // (a clamped index past the last event: no branch); 108 against 111 us for 3e6 events.  The other
-  // kernels load them where the event begins: the live registers cost the FP32 gradient kernel
-  // more than the latency (51.5 against 50.5 us), and the likelihood-only one reads at the
-  // memory's rate either way (66 against 65 us).
+  // Column groups of this thread's event.  The FP64 gradient kernel of the large shape (two wavefronts
+  // per SIMD) fetches the next event's as soon as the current ones are used up, before the
+  // accumulation (a clamped index past the last event: no branch); 108 against 111 us for 3e6 events.
+  // The others load them where the event begins, and the Z columns where the Z chain does: the live
+  // registers cost the FP32 gradient kernel more than the latency (51.5 against 50.5 us) and the
+  // likelihood-only ones wavefronts (FP32: 37 against 35 us), and the small shape reads at the
+  // memory's rate (FP64 gradient: 57 against 53 us).
   constexpr int NG = NZ > 0 ? (ZF ? 5 : 4) : 3;
+  constexpr bool PRE = GRAD && std::is_same_v<T, double> && NK > 1;
   V4 grp[NG];
   uint32_t prop = 0;       // toys: this thread's proposal and the number of its accept-reject test
   double spare = 0.0, eps_true = 1.0;
@@ -546,24 +551,28 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
     }
     const uint32_t ob4 = i * (uint32_t)sizeof(V4);
 #pragma unroll
-    for (int k = 0; k < NG; ++k)
+    for (int k = 0; k < (PRE ? NG : 3); ++k)
       if (k < 3 || a.cnt[5] > 0) grp[k] = ldoff(gb + k * ld, ob4);
   };
-  constexpr bool PRE = GRAD && std::is_same_v<T, double>;
   if (PRE && threadIdx.x < n_blk) fetch(threadIdx.x);
+  // (Issue-bound kernels only: where memory is waited for, FP32 likelihood and small shape, the fixed
+  // order cost 2 us of 23.)
   // Wavefronts further from their block's end issue first.  Left to the hardware, the oldest ready
   // wavefront issues first, so of the blocks sharing a compute unit (all with the same number of
   // events) one ends early and the last runs with idle issue slots: on average 3.5 of 4 (FP32) and
   // 1.7 of 2 (FP64) wavefronts per SIMD were left.  Lowering a wavefront's priority as it nears its end
   // lets the others catch up.
-  __builtin_amdgcn_s_setprio(3);
+  constexpr bool PRIO = NK > 1 && (GRAD || std::is_same_v<T, double>) && !TOYS;
+  if constexpr (PRIO) __builtin_amdgcn_s_setprio(3);
   uint32_t left = (n_blk + 255) / 256;   // passes of this block still to do
   for (uint32_t i = TOYS ? blockIdx.x / kToyLists * 256 + threadIdx.x : threadIdx.x; i < n_blk;
        i += TOYS ? gridDim.x / kToyLists * 256 : 256) {
-    if (left == 6) __builtin_amdgcn_s_setprio(2);
-    else if (left == 3) __builtin_amdgcn_s_setprio(1);
-    else if (left == 1) __builtin_amdgcn_s_setprio(0);
-    --left;
+    if constexpr (PRIO) {
+      if (left == 6) __builtin_amdgcn_s_setprio(2);
+      else if (left == 3) __builtin_amdgcn_s_setprio(1);
+      else if (left == 1) __builtin_amdgcn_s_setprio(0);
+      --left;
+    }
     const int64_t e = e0 + i;
     const uint32_t ob = i * (uint32_t)sizeof(T);
     const auto& ka = *kernarg_laundered<AmpArgs<T, Sh>>();
@@ -749,6 +758,10 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
     Cx<T> T0k{T(0), T(0)}, T1k{T(0), T(0)}, T2k{T(0), T(0)};   // Z coupling sums, kept for a second reading
     if constexpr (NZ > 0) {
       if (a.cnt[5] > 0) {
+        if constexpr (!PRE && !TOYS) {
+#pragma unroll
+          for (int k = 3; k < NG; ++k) grp[k] = ldoff(gb + k * ld, i * (uint32_t)sizeof(V4));
+        }
         const T mz2 = grp[2].y;
         gzv = grp[2].w;
         // The xi = -1 factors are (-Re, Im) of the xi = +1 ones (columns 12-15), so Im enters X and
@@ -853,12 +866,17 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
         if (!(S > pos_floor<T>()) || !(S < T(INFINITY))) nbad += 1.f;
         w = rcp_(S);
       }
-      // ln of the product of the terms: mantissa product in [1/2, 1) and exponent sum; one
-      // logarithm per thread after the loop (a rounding of 2^-53 per event, below that of a
-      // logarithm per event and its sum; 4-5 instructions in place of 8 in FP32 and 100 in FP64)
-      const double pr = mprod * (double)arg;
-      mprod = __builtin_amdgcn_frexp_mant(pr);
-      mexp += __builtin_amdgcn_frexp_exp(pr);
+      // ln of the product of the terms, kept as the product of their mantissas (each in [1/2, 1): at
+      // most 1024 passes, so it stays representable) and the sum of their exponents; one logarithm per
+      // thread after the loop (a rounding of 2^-53 per event, below that of a logarithm per event
+      // and its sum)
+      if constexpr (std::is_same_v<T, float>) {
+        mprod *= (double)__builtin_amdgcn_frexp_mantf(arg);
+        mexp += __builtin_amdgcn_frexp_expf(arg);
+      } else {
+        mprod *= __builtin_amdgcn_frexp_mant(arg);
+        mexp += __builtin_amdgcn_frexp_exp(arg);
+      }
     } else {
       const T eps = a.eps ? ldoff(a.eps + e0, ob) : T(1);
       const double x = (double)(eps * S);
@@ -1055,10 +1073,21 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE>::v)) void amp_kernel(co
 
   if (set == 0) {
     // ln(mprod 2^mexp) as the pair ms - mc: mexp ln2 in two parts, the first exact (29 bits times
-    // at most 24) so that the pair carries the full product
+    // at most 24) so that the pair carries the full product.  FP32: the logarithm of the mantissa is
+    // the hardware's (an error of 1e-7 per thread, where each event's was), corrected for what its
+    // argument leaves out; the double precision one cost 1.5 us of the 35 of 3e6 events.
     constexpr double L2H = 0x1.62e42ff000000p-1, L2L = -0x1.718432a1b0e26p-35;
+    mexp += __builtin_amdgcn_frexp_exp(mprod);
+    mprod = __builtin_amdgcn_frexp_mant(mprod);
+    double ln;
+    if constexpr (std::is_same_v<T, float>) {
+      const float hi = (float)mprod;
+      ln = (double)(__builtin_amdgcn_logf(hi) * 0.693147180559945309f + (float)(mprod - (double)hi) * rcp_(hi));
+    } else {
+      ln = log(mprod);
+    }
     ms = (double)mexp * L2H;
-    mc = -((double)mexp * L2L + log(mprod));
+    mc = -((double)mexp * L2L + ln);
   }
   // ---- block reduction: wave transpose-butterfly, then the 4 waves in order
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1272,7 +1301,7 @@ __global__ __launch_bounds__(256) void phsp_kernel(GenArgs a) {
 //   |ang0| <= ang0(1),   |sin ang1| <= 2 ang1(1) / (J + 1)         (Legendre; Bernstein's inequality)
 // The Z angular factors are at most n_Z / sqrt2 in size.  The intervals overlap by 1e-9 of the range
 // and the bound is raised by 1e-6, which covers every rounding.
-template <class Sh> __global__ __launch_bounds__(kBins) void bound_kernel(const AmpArgs<double, Sh> a) {
+template <class Sh> __global__ __launch_bounds__(kBins) void bound_kernel(const ToyAmpArgs<Sh> a) {
   const ToyArgs& ty = a.toys;
   const Kin& k = ty.kin;
   auto span = [&](double lo, double hi, double& x1, double& x2) {
@@ -1576,14 +1605,14 @@ hipError_t launch_phsp(const GenArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 // One chunk of toys: the proposals, the densities of the listed ones, and the accepted events.
-template <class Sh> hipError_t launch_toys(const AmpArgs<double, Sh>& a, int n_cu, hipStream_t st) {
+template <class Sh> hipError_t launch_toys(const ToyAmpArgs<Sh>& a, int n_cu, hipStream_t st) {
   const ToyArgs& t = a.toys;
   const int64_t n = (int64_t)t.rounds << kRoundBits;
   const int groups = (int)(n >> kGroupBits);
   if (t.rounds < 1 || t.rounds > kMaxRounds || t.per_wave < 64 || t.per_wave > kPerWave || n % (4 * kToyLists * t.per_wave))
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(propose_kernel, dim3((unsigned)(n / (4 * t.per_wave))), dim3(256), 0, st, t);
-  AmpArgs<double, Sh> b = a;
+  ToyAmpArgs<Sh> b = a;
   b.nb_data = (2 * n_cu + kToyLists - 1) / kToyLists * kToyLists;   // whole blocks per list
   if constexpr (Sh::NZ >= 2) {
     if (a.zfree) {
@@ -1600,13 +1629,13 @@ template <class Sh> hipError_t launch_toys(const AmpArgs<double, Sh>& a, int n_c
   hipLaunchKernelGGL(collect_kernel, dim3(groups), dim3(256), 0, st, t);
   return hipGetLastError();
 }
-template <class Sh> hipError_t launch_toy_bound(const AmpArgs<double, Sh>& a, hipStream_t st) {
+template <class Sh> hipError_t launch_toy_bound(const ToyAmpArgs<Sh>& a, hipStream_t st) {
   hipLaunchKernelGGL(bound_kernel<Sh>, dim3(1), dim3(kBins), 0, st, a);
   return hipGetLastError();
 }
-template hipError_t launch_toys<ShapeSmall>(const AmpArgs<double, ShapeSmall>&, int, hipStream_t);
-template hipError_t launch_toys<ShapeFull>(const AmpArgs<double, ShapeFull>&, int, hipStream_t);
-template hipError_t launch_toy_bound<ShapeSmall>(const AmpArgs<double, ShapeSmall>&, hipStream_t);
-template hipError_t launch_toy_bound<ShapeFull>(const AmpArgs<double, ShapeFull>&, hipStream_t);
+template hipError_t launch_toys<ShapeSmall>(const ToyAmpArgs<ShapeSmall>&, int, hipStream_t);
+template hipError_t launch_toys<ShapeFull>(const ToyAmpArgs<ShapeFull>&, int, hipStream_t);
+template hipError_t launch_toy_bound<ShapeSmall>(const ToyAmpArgs<ShapeSmall>&, hipStream_t);
+template hipError_t launch_toy_bound<ShapeFull>(const ToyAmpArgs<ShapeFull>&, hipStream_t);
 
 }  // namespace kpsi

@@ -138,8 +138,14 @@ template <typename T, class Sh> struct AmpArgs {
   // instantiation that reads the extra angular columns; its lambda' = -1 accumulators take the
   // record slots of the (then unused) second Z.
   int zfree;
-  ToyArgs toys;         // MODE_TOYS only
 };
+// The per-event kernel's arguments in MODE_TOYS.  (Apart, so that the other modes' launches do not
+// carry them.)
+template <class Sh> struct ToyAmpArgs : AmpArgs<double, Sh> {
+  ToyArgs toys;
+};
+template <typename T, class Sh, int MODE> struct AmpArgsOf { using type = AmpArgs<T, Sh>; };
+template <typename T, class Sh> struct AmpArgsOf<T, Sh, MODE_TOYS> { using type = ToyAmpArgs<Sh>; };
 // Record slot of sum_i w_i S_i over the data events of the mixture (gradient mode).
 template <class Sh> constexpr int ws_slot() { return 3 + Sh::NKACC + 4 * Sh::NZ + 2 * NFL; }
 
@@ -269,8 +275,8 @@ hipError_t launch_reduce_final(const double* partial, int nb_data, int nb_mc, in
 hipError_t launch_hist_lookup(const HistArgs& a, hipStream_t st);
 hipError_t launch_template(const TplArgs& a, hipStream_t st);
 hipError_t launch_phsp(const GenArgs& a, hipStream_t st);
-template <class Sh> hipError_t launch_toy_bound(const AmpArgs<double, Sh>& a, hipStream_t st);
-template <class Sh> hipError_t launch_toys(const AmpArgs<double, Sh>& a, int n_cu, hipStream_t st);
+template <class Sh> hipError_t launch_toy_bound(const ToyAmpArgs<Sh>& a, hipStream_t st);
+template <class Sh> hipError_t launch_toys(const ToyAmpArgs<Sh>& a, int n_cu, hipStream_t st);
 hipError_t exclusive_scan_int(const int* in, int* out, int64_t n, void* tmp, size_t* tmp_bytes, hipStream_t st);
 
 // Record an error message on a context (the host runtime's kpsi_last_error) and return s.
