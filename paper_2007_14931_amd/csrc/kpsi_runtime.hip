@@ -2280,20 +2280,20 @@ kpsi_status kpsi_mlp_train(kpsi_ctx* c, float* params, int64_t n, const double* 
   const int nbmax = c->n_cu > 0 ? c->n_cu : 256;
   const int64_t B = o->batch;
   const int64_t nbatch = (n + B - 1) / B;
-  float *dp = nullptr, *mm = nullptr, *vv = nullptr, *part = nullptr;
-  double* dloss = nullptr;   // mean loss of each batch
-  auto cleanup = [&]() {
-    for (void* p : {(void*)dp, (void*)mm, (void*)vv, (void*)part, (void*)dloss}) if (p) hipFree(p);
-  };
-  if (hipMalloc(&dp, MLP_NP * sizeof(float)) || hipMalloc(&mm, MLP_NP * sizeof(float)) ||
-      hipMalloc(&vv, MLP_NP * sizeof(float)) || hipMalloc(&part, (size_t)(MLP_NP + 1) * nbmax * sizeof(float)) ||
-      hipMalloc(&dloss, nbatch * sizeof(double))) {
-    cleanup();
+  // one allocation: mean losses of the batches, parameters, moments, block records (five allocations,
+  // two fills and two copies back took 20 us more per call)
+  constexpr size_t NPA = 4608;   // parameters, padded to whole 256-byte lines
+  static_assert(NPA >= (size_t)4545 && NPA % 64 == 0, "parameter stride");
+  const size_t nl = ((size_t)nbatch + 31) / 32 * 32;
+  unsigned char* buf = nullptr;
+  if (hipMalloc(&buf, nl * sizeof(double) + (3 * NPA + (size_t)(MLP_NP + 1) * nbmax) * sizeof(float)) != hipSuccess)
     return fail(c, KPSI_E_OOM, "network buffers");
-  }
+  auto cleanup = [&]() { hipFree(buf); };
+  double* const dloss = reinterpret_cast<double*>(buf);
+  float* const dp = reinterpret_cast<float*>(dloss + nl);
+  float *const mm = dp + NPA, *const vv = mm + NPA, *const part = vv + NPA;
   hipError_t e = hipMemcpyAsync(dp, params, MLP_NP * sizeof(float), hipMemcpyHostToDevice, c->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(mm, 0, MLP_NP * sizeof(float), c->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(vv, 0, MLP_NP * sizeof(float), c->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(mm, 0, 2 * NPA * sizeof(float), c->stream);
   AdamArgs ad{};
   ad.p = dp; ad.m = mm; ad.v = vv;
   ad.lr = (float)o->lr; ad.b1 = (float)o->beta1; ad.b2 = (float)o->beta2; ad.eps = (float)o->eps;
@@ -2310,16 +2310,19 @@ kpsi_status kpsi_mlp_train(kpsi_ctx* c, float* params, int64_t n, const double* 
                           current);
     }
   }
-  // the losses of the last epoch's batches
-  std::vector<double> hl(o->epochs > 0 ? nbatch : 0);
-  if (e == hipSuccess && !hl.empty())
-    e = hipMemcpyAsync(hl.data(), dloss, hl.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(params, dp, MLP_NP * sizeof(float), hipMemcpyDeviceToHost, c->stream);
+  // the losses of the last epoch's batches and the parameters
+  std::vector<unsigned char> h(nl * sizeof(double) + MLP_NP * sizeof(float));
+  if (e == hipSuccess) e = hipMemcpyAsync(h.data(), buf, h.size(), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   cleanup();
   if (e != hipSuccess) return fail(c, KPSI_E_HIP, "network training: %s", hipGetErrorString(e));
+  std::memcpy(params, h.data() + nl * sizeof(double), MLP_NP * sizeof(float));
   double sum = 0.0;
-  for (size_t b = 0; b < hl.size(); ++b) sum += hl[b] * (double)std::min<int64_t>(B, n - (int64_t)b * B);
+  for (int64_t b = 0; b < (o->epochs > 0 ? nbatch : 0); ++b) {
+    double lb;
+    std::memcpy(&lb, h.data() + b * sizeof(double), sizeof lb);
+    sum += lb * (double)std::min<int64_t>(B, n - b * B);
+  }
   if (loss) *loss = sum / (double)n;
   return KPSI_OK;
 }
