@@ -447,8 +447,9 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
   const int64_t e2 = TOYS ? n : (int64_t)(((uint64_t)(blk + 1) * a.step[src]) >> 32) * 256;
   const int64_t e1 = (blk + 1 < (src == 0 ? a.nb_data : a.nb_mc) && e2 < n) ? e2 : n;
 
-  double ms = 0.0, mc = 0.0;   // Kahan pair
-  double mprod = 1.0;          // data: product of the terms as mprod 2^mexp
+  // normalisation: Kahan pair; data: product of the terms as ms 2^mexp until the loop is done (one
+  // variable for both: the FP32 likelihood kernel has no register to spare)
+  double ms = set == 0 ? 1.0 : 0.0, mc = 0.0;
   int mexp = 0;
   float nbad = 0.f;   // events with a non-positive or non-finite density (exact count; the call then
                       // fails, so what they add to the sums does not matter)
@@ -871,10 +872,10 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
       // thread after the loop (a rounding of 2^-53 per event, below that of a logarithm per event
       // and its sum)
       if constexpr (std::is_same_v<T, float>) {
-        mprod *= (double)__builtin_amdgcn_frexp_mantf(arg);
+        ms *= (double)__builtin_amdgcn_frexp_mantf(arg);
         mexp += __builtin_amdgcn_frexp_expf(arg);
       } else {
-        mprod *= __builtin_amdgcn_frexp_mant(arg);
+        ms *= __builtin_amdgcn_frexp_mant(arg);
         mexp += __builtin_amdgcn_frexp_exp(arg);
       }
     } else {
@@ -1072,13 +1073,13 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
   if constexpr (MODE == MODE_DENSITY || TOYS) return;
 
   if (set == 0) {
-    // ln(mprod 2^mexp) as the pair ms - mc: mexp ln2 in two parts, the first exact (29 bits times
+    // ln(ms 2^mexp) as the pair ms - mc: mexp ln2 in two parts, the first exact (29 bits times
     // at most 24) so that the pair carries the full product.  FP32: the logarithm of the mantissa is
     // the hardware's (an error of 1e-7 per thread, where each event's was), corrected for what its
     // argument leaves out; the double precision one cost 1.5 us of the 35 of 3e6 events.
     constexpr double L2H = 0x1.62e42ff000000p-1, L2L = -0x1.718432a1b0e26p-35;
-    mexp += __builtin_amdgcn_frexp_exp(mprod);
-    mprod = __builtin_amdgcn_frexp_mant(mprod);
+    mexp += __builtin_amdgcn_frexp_exp(ms);
+    const double mprod = __builtin_amdgcn_frexp_mant(ms);
     double ln;
     if constexpr (std::is_same_v<T, float>) {
       const float hi = (float)mprod;
