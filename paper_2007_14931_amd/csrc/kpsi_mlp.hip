@@ -3,8 +3,8 @@
 // The 64x64 layer (forward, weight gradient and input gradient) runs on BF16 matrix cores
 // (v_mfma_f32_16x16x32_bf16: 16x16 outputs, 32-deep products, 8 operands per lane) with FP32
 // accumulation; the 4-wide input layer and the output layer run on the vector ALUs in FP32.
-// Master weights are FP32; a small kernel writes the BF16 copies of the 64x64 layer in both
-// layouts once per parameter update, and blocks stage them into LDS with 16-byte copies.
+// Master weights are FP32; the Adam step also writes the BF16 copies of the 64x64 layer in both
+// layouts, which the gradient kernel loads into registers as operands.
 //
 // Parameter layout (4545 floats): W1[64][4], b1[64], W2[64][64] (row = output), b2[64],
 // w3[64], b3.  Network input: u = (2 (m - lo)/(hi - lo) - 1, cos theta_K*, cos theta_J/psi,
