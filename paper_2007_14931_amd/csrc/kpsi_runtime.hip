@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "kpsi.h"
+#include "kpsi_grid.h"
 #include "kpsi_internal.h"
 #include "kpsi_math.h"
 
@@ -425,68 +426,17 @@ kpsi_status ensure_partial(kpsi_ctx* c, size_t nblocks) {
   return KPSI_OK;
 }
 
-// Blocks of the per-event kernel over the data set and over each of nrec normalisation records, and
-// the passes of 256 events each block takes (AmpArgs::step).
-//
-// The grid is one resident round (compute units x resident blocks per unit for this kernel), or the
-// fewest whole rounds in which no block exceeds 64 passes: every round is full, and a block's
-// passes are the average rounded down or up, spread evenly, so compute units end together.  (With
-// equal whole passes per block, at most 64, the 3e7 events of the largest fit ran a second round
-// that was 79% full: 534 against 517 us of kernel in FP32; with flavour tags 5e6 readings take
-// 75.6 against 75.0 us, and 3e6 events the same 44.4 us either way.)
-// At most `limit` blocks (the callers' partial rows).
-struct Grid {
-  int nbd = 0, nbm = 0;
-  uint64_t sd = 0, sm = 0;
-};
-int64_t passes(int64_t n) { return (n + BLOCK - 1) / BLOCK; }
-// Blocks of the grid at `ept` passes each.
-int64_t blocks_at(int64_t ept, int64_t nd, int64_t nm, int nrec) {
-  return (passes(nd) + ept - 1) / ept + nrec * ((passes(nm) + ept - 1) / ept);
-}
-template <typename T, class Sh>
-Grid pick_grid(kpsi_ctx* c, int mode, int64_t nd, int64_t nm, int nrec, int64_t limit) {
-  const int64_t td = passes(nd), tm = passes(nm), total = td + nrec * tm;
-  Grid g;
-  if (total <= 0) return g;
-  if (c->ept_override > 0) {
-    const int64_t ept = c->ept_override;
-    g.nbd = (int)((td + ept - 1) / ept);
-    g.nbm = (int)((tm + ept - 1) / ept);
-    g.sd = g.sm = (uint64_t)ept << 32;
-    return g;
-  }
+// Grid rule of the per-event kernel in a mode (pick_grid): its resident blocks, and equal whole passes in
+// the FP32 kernels of the small shape, which read at the memory's rate and do better so where one round
+// holds them: 23.4 against 25.3 us (gradient) and 22.0 against 22.7 (likelihood) for 3e6 events.  In FP64
+// it is the other way round (53.8 against 51.3), and the large shape does not mind.
+static_assert(kPassEvents == BLOCK, "a pass is one event per thread");
+template <typename T, class Sh> GridRule grid_rule(kpsi_ctx* c, int mode) {
   const bool cc = c->cc_on && mode != MODE_DENSITY;
   int& bpc = c->blocks_per_cu[c->shape][mode][(cc ? 1 : 0) + (c->zfree ? 2 : 0)];
   if (bpc < 0) bpc = amp_blocks_per_cu<T, Sh>(mode, cc, c->zfree);
-  const int64_t cap = (int64_t)(c->n_cu > 0 ? c->n_cu : 256) * (bpc > 0 ? bpc : 3);
-  const int64_t rounds = (total + 64 * cap - 1) / (64 * cap);
-  const int64_t slots = std::min(limit, std::min(total, rounds * cap));
-  // The FP32 kernels of the small shape read at the memory's rate, and there blocks of equal whole passes
-  // do better where one round holds them: 23.4 against 25.3 us (gradient) and 22.0 against 22.7
-  // (likelihood) for 3e6 events.  In FP64 it is the other way round (53.8 against 51.3), and the
-  // large shape does not mind.
-  if (Sh::NK == 1 && std::is_same_v<T, float> && rounds == 1) {
-    const int64_t most = std::min(cap, limit);
-    int64_t ept = (total + most - 1) / most;
-    while (ept < 64 && blocks_at(ept, nd, nm, nrec) > most) ++ept;
-    if (blocks_at(ept, nd, nm, nrec) <= most) {
-      g.nbd = (int)((td + ept - 1) / ept);
-      g.nbm = (int)((tm + ept - 1) / ept);
-      g.sd = g.sm = (uint64_t)ept << 32;
-      return g;
-    }
-  }
-  // slots in proportion to the passes, at least one block where there are events
-  int64_t nbd = td > 0 ? std::max<int64_t>(1, (slots * td + total / 2) / total) : 0;
-  if (tm > 0) nbd = std::min(nbd, std::max<int64_t>(td > 0 ? 1 : 0, slots - nrec));
-  nbd = std::min(nbd, td);
-  const int64_t nbm = tm > 0 ? std::min(tm, std::max<int64_t>(1, (slots - nbd) / nrec)) : 0;
-  g.nbd = (int)nbd;
-  g.nbm = (int)nbm;
-  g.sd = nbd > 0 ? ((uint64_t)td << 32) / (uint64_t)nbd : 0;
-  g.sm = nbm > 0 ? ((uint64_t)tm << 32) / (uint64_t)nbm : 0;
-  return g;
+  return GridRule{(int64_t)(c->n_cu > 0 ? c->n_cu : 256) * (bpc > 0 ? bpc : 3),
+                  Sh::NK == 1 && std::is_same_v<T, float>, c->ept_override};
 }
 
 Kin kin_of(const kpsi_ctx* c) {
@@ -1045,26 +995,15 @@ kpsi_status run_amp(kpsi_ctx* c, int mode, const double* par, int which /*-1: bo
     a.keep = (T)(1.0 - c->mistag);
   }
   const int64_t limit = fixed ? (int64_t)(fixed_cap / NACC) : INT64_MAX;
-  if (fixed) {
-    // refused at the block counts of 64 passes per block (or the passes the caller set), which the
-    // automatic grid never exceeds
-    const int64_t rows = blocks_at(c->ept_override > 0 ? c->ept_override : 64, nd, nm, nmsets);
-    if (rows > limit)
-      return fail(c, KPSI_E_ARG, "%lld block partials of %d doubles exceed the static scratch of %zu doubles "
-                  "(at most %lld blocks)", (long long)rows, NACC, fixed_cap, (long long)limit);
-  }
-  Grid grid;
-  if (!mix) {
-    grid = pick_grid<T, Sh>(c, mode, nd, nm, nmsets, limit);
-  } else {
-    // Eq. 14: the data terms need the normalisation total, so the normalisation events run in
-    // a launch of their own first, and the data launch sums their block partials (unless the
-    // normalisation record comes from the interference matrix and is already in red_dev)
-    const Grid gm = pick_grid<T, Sh>(c, mode, 0, nm, nmsets, limit);
-    grid = pick_grid<T, Sh>(c, mode, nd, 0, 1, std::max<int64_t>(1, limit - nmsets * gm.nbm));
-    grid.nbm = gm.nbm;
-    grid.sm = gm.sm;
-  }
+  const GridRule rule = grid_rule<T, Sh>(c, mode);
+  const int64_t rows = grid_rows(rule, nd, nm, nmsets);
+  if (rows > limit)
+    return fail(c, KPSI_E_ARG, "%lld block partials of %d doubles exceed the static scratch of %zu doubles "
+                "(at most %lld blocks)", (long long)rows, NACC, fixed_cap, (long long)limit);
+  const Grid grid = mix ? pick_grid_mixture(rule, nd, nm, nmsets, limit) : pick_grid(rule, nd, nm, nmsets, limit);
+  if (!grid_holds(grid, nd, nm, nmsets, limit))
+    return fail(c, KPSI_E_ARG, "no grid of at most %lld blocks for %lld data and %lld normalisation events",
+                (long long)limit, (long long)nd, (long long)nm);
   const int nbd = grid.nbd, nbm = grid.nbm;
   double* part = c->partial;
   if (mode != MODE_DENSITY) {
