@@ -443,9 +443,9 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
   if constexpr (TOYS) n = (int64_t)a.toys.stat[kToyListed + 16 * tl];
   const T* __restrict__ col = a.cols[src];
   const int64_t ld = a.ld[src];
-  const int64_t e0 = TOYS ? 0 : (int64_t)(((uint64_t)blk * a.step[src]) >> 32) * 256;
-  const int64_t e2 = TOYS ? n : (int64_t)(((uint64_t)(blk + 1) * a.step[src]) >> 32) * 256;
-  const int64_t e1 = (blk + 1 < (src == 0 ? a.nb_data : a.nb_mc) && e2 < n) ? e2 : n;
+  auto first = [&](int64_t b) { return (b * a.per[src] + (b < a.more[src] ? b : a.more[src])) * 256; };
+  const int64_t e0 = TOYS ? 0 : first(blk), e2 = TOYS ? n : first(blk + 1);
+  const int64_t e1 = e2 < n ? e2 : n;
 
   // normalisation: Kahan pair; data: product of the terms as ms 2^mexp until the loop is done (one
   // variable for both: the FP32 likelihood kernel has no register to spare)

@@ -10,15 +10,17 @@ constexpr int64_t kPassEvents = 256;    // events of a pass: one per thread of a
 constexpr int64_t kRowPasses = 64;      // passes per block at which a call's rows are admitted
 constexpr int64_t kMostPasses = 1024;   // passes per block that the kernel's product of terms holds
 
-// Blocks of the per-event kernel over the data set and over each normalisation record, and the passes of
-// each block times 2^32 (AmpArgs::step).
+// Blocks of the per-event kernel over the data set and over each normalisation record: nb blocks of
+// `per` passes, the first `more` of them of one more.
+struct Blocks {
+  int nb = 0, per = 0, more = 0;
+};
 struct Grid {
-  int nbd = 0, nbm = 0;
-  uint64_t sd = 0, sm = 0;
+  Blocks d, m;
 };
 struct GridRule {
   int64_t cap;   // blocks resident at once
-  bool whole;    // equal whole passes per block where one round holds them
+  int few;       // up to this many passes per block, no more blocks than these take
   int ept;       // passes per block set by the caller, or 0
 };
 
@@ -33,39 +35,43 @@ inline int64_t grid_rows(const GridRule& r, int64_t nd, int64_t nm, int nrec) {
   return blocks_at(r.ept > 0 ? r.ept : kRowPasses, nd, nm, nrec);
 }
 
-// The grid is one resident round, or the fewest whole rounds that take about 64 passes per block:
-// every round is full, and the passes are spread evenly over the blocks of a set, so compute units end
-// together.  (With equal whole passes per block, at most 64, the 3e7 events of the largest fit ran a
-// second round that was 79% full: 534 against 517 us of kernel in FP32; with flavour tags 5e6
-// readings take 75.6 against 75.0 us, and 3e6 events the same 44.4 us either way.)
+// The grid is one resident round, or the fewest whole rounds in which no block exceeds kRowPasses
+// passes.  P is the fewest passes per block at which both sets fit these slots.  Every slot is taken, P or
+// fewer passes a block, the longer blocks of a set first: blocks go to the compute units in turn, so
+// each unit gets as many of the longer ones as any other, to within one per set.
+//   - Fewer blocks (P whole passes each, P = 2 and 3) do not shorten the longest one and leave slots idle:
+//     FP64 likelihood of the large shape on 1024 slots, 1177 passes 21.2 against 19.4 us, 1638 passes 23.1
+//     against 21.8 a call; FP32 gradient, 1638 passes 22.2 against 21.3.  The other way round it is at
+//     most 2% (FP32, 2867 passes on 2048 slots: 21.6 against 21.9), but for the kernels with a `few`.
+//   - With the longer blocks spread evenly over the set, those whose numbers differ by the count of the
+//     units meet on one unit where the spread's period divides it: 1300 passes 22.8 against 20.7 us
+//     (21.9 in blocks of two), 2060 passes 27.2 against 25.2.
+//   - With equal whole passes per block, the 3e7 events of the largest fit run a second round that is
+//     79% full: 534 against 517 us of kernel in FP32.
 inline Grid pick_grid(const GridRule& r, int64_t nd, int64_t nm, int nrec, int64_t limit) {
   const int64_t td = grid_passes(nd), tm = grid_passes(nm), total = td + nrec * tm;
   Grid g;
   if (total <= 0) return g;
-  auto equal = [&](int64_t ept) {
-    g.nbd = (int)((td + ept - 1) / ept);
-    g.nbm = (int)((tm + ept - 1) / ept);
-    g.sd = g.sm = (uint64_t)ept << 32;
+  auto ceil_div = [](int64_t t, int64_t p) { return (t + p - 1) / p; };
+  auto equal = [&](int64_t p) {   // whole passes, the last block of a set the rest
+    g.d = Blocks{(int)ceil_div(td, p), (int)p, 0};
+    g.m = Blocks{(int)ceil_div(tm, p), (int)p, 0};
     return g;
   };
+  auto spread = [](int64_t t, int64_t nb) { return nb > 0 ? Blocks{(int)nb, (int)(t / nb), (int)(t % nb)} : Blocks{}; };
   if (r.ept > 0) return equal(r.ept);
-  const int64_t rounds = (total + kRowPasses * r.cap - 1) / (kRowPasses * r.cap);
-  const int64_t slots = std::min(limit, std::min(total, rounds * r.cap));
-  if (r.whole && rounds == 1) {
-    const int64_t most = std::min(r.cap, limit);
-    int64_t ept = (total + most - 1) / most;
-    while (ept < kRowPasses && blocks_at(ept, nd, nm, nrec) > most) ++ept;
-    if (blocks_at(ept, nd, nm, nrec) <= most) return equal(ept);
-  }
-  // slots in proportion to the passes, at least one block where there are events
-  int64_t nbd = td > 0 ? std::max<int64_t>(1, (slots * td + total / 2) / total) : 0;
-  if (tm > 0) nbd = std::min(nbd, std::max<int64_t>(td > 0 ? 1 : 0, slots - nrec));
-  nbd = std::min(nbd, td);
-  const int64_t nbm = tm > 0 ? std::min(tm, std::max<int64_t>(1, (slots - nbd) / nrec)) : 0;
-  g.nbd = (int)nbd;
-  g.nbm = (int)nbm;
-  g.sd = nbd > 0 ? ((uint64_t)td << 32) / (uint64_t)nbd : 0;
-  g.sm = nbm > 0 ? ((uint64_t)tm << 32) / (uint64_t)nbm : 0;
+  int64_t rounds = ceil_div(total, kRowPasses * r.cap), slots, P;
+  do {   // (a second time where the sets do not divide well: 65 passes in the fewest rounds)
+    slots = std::min(limit, rounds++ * r.cap);
+    P = ceil_div(total, slots);
+    while (P <= kRowPasses && blocks_at(P, nd, nm, nrec) > slots) ++P;
+  } while (P > kRowPasses && slots < limit);
+  if (P <= r.few && slots <= r.cap) return equal(P);
+  // slots in proportion to the passes, at least as many for each set as P passes per block take
+  const int64_t bd = ceil_div(td, P), bm = ceil_div(tm, P);
+  const int64_t nbd = std::min(td, std::max(bd, std::min((slots * td + total / 2) / total, slots - nrec * bm)));
+  g.d = spread(td, nbd);
+  g.m = spread(tm, std::min(tm, (slots - nbd) / nrec));
   return g;
 }
 
@@ -74,21 +80,14 @@ inline Grid pick_grid(const GridRule& r, int64_t nd, int64_t nm, int nrec, int64
 // picked: whole rounds of it may take all that `limit` leaves.
 inline Grid pick_grid_mixture(const GridRule& r, int64_t nd, int64_t nm, int nrec, int64_t limit) {
   const Grid gm = pick_grid(r, 0, nm, nrec, limit - grid_rows(r, nd, 0, 1));
-  Grid g = pick_grid(r, nd, 0, 1, limit - (int64_t)nrec * gm.nbm);
-  g.nbm = gm.nbm;
-  g.sm = gm.sm;
+  Grid g = pick_grid(r, nd, 0, 1, limit - (int64_t)nrec * gm.m.nb);
+  g.m = gm.m;
   return g;
 }
 
 // Whether a grid keeps the bounds its launch relies on: rows of the partials, passes of a block.
-inline bool grid_holds(const Grid& g, int64_t nd, int64_t nm, int nrec, int64_t limit) {
-  auto most = [](int64_t t, int64_t nb, uint64_t step) {   // passes of the longest block
-    if (nb <= 0) return t;
-    const int64_t last = t - (int64_t)(((uint64_t)(nb - 1) * step) >> 32);
-    return std::max(last, nb > 1 ? (int64_t)((step + 0xffffffffull) >> 32) : 0);
-  };
-  return g.nbd + (int64_t)nrec * g.nbm <= limit && most(grid_passes(nd), g.nbd, g.sd) <= kMostPasses &&
-         most(grid_passes(nm), g.nbm, g.sm) <= kMostPasses;
+inline bool grid_holds(const Grid& g, int nrec, int64_t limit) {
+  return g.d.nb + (int64_t)nrec * g.m.nb <= limit && std::max(g.d.per + (g.d.more > 0), g.m.per + (g.m.more > 0)) <= kMostPasses;
 }
 
 }  // namespace kpsi

@@ -105,8 +105,7 @@ template <typename T, class Sh> struct AmpArgs {
   int poff;             // block offset of this launch in the partial rows
   double* s_out[2];     // density mode: per-event S of each set
   int nb_data;          // blocks of the data set; the rest cover the normalisation set
-  uint64_t step[2];     // passes (of 256 events) per block of each set, times 2^32: block b takes the
-                        // passes [b step, (b + 1) step) / 2^32, the last block the rest
+  int per[2], more[2];  // passes (of 256 events) per block of each set; its first `more` blocks take one more
   int cnt[6];           // slots in use per spin 0..4 and Z
   T rR2, rB2;           // squared barrier radii
   AC<T> cs[Sh::NK + Sh::NZ];   // K* slots, then Z slots

@@ -426,17 +426,20 @@ kpsi_status ensure_partial(kpsi_ctx* c, size_t nblocks) {
   return KPSI_OK;
 }
 
-// Grid rule of the per-event kernel in a mode (pick_grid): its resident blocks, and equal whole passes in
-// the FP32 kernels of the small shape, which read at the memory's rate and do better so where one round
-// holds them: 23.4 against 25.3 us (gradient) and 22.0 against 22.7 (likelihood) for 3e6 events.  In FP64
-// it is the other way round (53.8 against 51.3), and the large shape does not mind.
+// Grid rule of the per-event kernel in a mode (pick_grid): its resident blocks, and the passes per block up
+// to which no more blocks are started than these take.  The kernels of the small shape have little work in
+// a pass beside the start and the reduction of a block.  In FP32, blocks of equal whole passes are
+// faster or within 1% wherever one round holds them (calls with gradient: 2060 passes 15.6 against 17.9 us, 2867
+// 18.0 against 18.9, 11719 33.3 against 33.6); of the FP64 kernels, the gradient's at two passes
+// (1500 passes 17.9 against 19.1 us, 2060 21.3 against 21.1; at three 23.9 against 24.7 and 26.9 against
+// 25.7).
 static_assert(kPassEvents == BLOCK, "a pass is one event per thread");
 template <typename T, class Sh> GridRule grid_rule(kpsi_ctx* c, int mode) {
   const bool cc = c->cc_on && mode != MODE_DENSITY;
   int& bpc = c->blocks_per_cu[c->shape][mode][(cc ? 1 : 0) + (c->zfree ? 2 : 0)];
   if (bpc < 0) bpc = amp_blocks_per_cu<T, Sh>(mode, cc, c->zfree);
-  return GridRule{(int64_t)(c->n_cu > 0 ? c->n_cu : 256) * (bpc > 0 ? bpc : 3),
-                  Sh::NK == 1 && std::is_same_v<T, float>, c->ept_override};
+  const int few = Sh::NK > 1 ? 0 : std::is_same_v<T, float> ? (int)kRowPasses : mode == MODE_GRAD ? 2 : 0;
+  return GridRule{(int64_t)(c->n_cu > 0 ? c->n_cu : 256) * (bpc > 0 ? bpc : 3), few, c->ept_override};
 }
 
 Kin kin_of(const kpsi_ctx* c) {
@@ -1001,10 +1004,10 @@ kpsi_status run_amp(kpsi_ctx* c, int mode, const double* par, int which /*-1: bo
     return fail(c, KPSI_E_ARG, "%lld block partials of %d doubles exceed the static scratch of %zu doubles "
                 "(at most %lld blocks)", (long long)rows, NACC, fixed_cap, (long long)limit);
   const Grid grid = mix ? pick_grid_mixture(rule, nd, nm, nmsets, limit) : pick_grid(rule, nd, nm, nmsets, limit);
-  if (!grid_holds(grid, nd, nm, nmsets, limit))
+  if (!grid_holds(grid, nmsets, limit))
     return fail(c, KPSI_E_ARG, "no grid of at most %lld blocks for %lld data and %lld normalisation events",
                 (long long)limit, (long long)nd, (long long)nm);
-  const int nbd = grid.nbd, nbm = grid.nbm;
+  const int nbd = grid.d.nb, nbm = grid.m.nb;
   double* part = c->partial;
   if (mode != MODE_DENSITY) {
     if (fixed) {
@@ -1015,8 +1018,10 @@ kpsi_status run_amp(kpsi_ctx* c, int mode, const double* par, int which /*-1: bo
       part = c->partial;
     }
   }
-  a.step[0] = grid.sd;
-  a.step[1] = grid.sm;
+  a.per[0] = grid.d.per;
+  a.per[1] = grid.m.per;
+  a.more[0] = grid.d.more;
+  a.more[1] = grid.m.more;
   a.partial = part;
   a.pstride = nbd + nmsets * nbm;
   a.nb_mc = nbm;
