@@ -13,6 +13,7 @@
 #include <stdint.h>
 
 #include "kpsi_internal.h"
+#include "kpsi_silu.h"
 
 namespace kpsi {
 
@@ -31,32 +32,15 @@ __device__ __forceinline__ unsigned short bf16(float f) {
   u += 0x7fffu + ((u >> 16) & 1u);
   return (unsigned short)(u >> 16);
 }
-// silu with a correctly rounded quotient.  With y the correctly rounded 1/d (the hardware's value,
-// one Newton step), one correction of q = z y gives the IEEE quotient: the steps of the division
-// without its scaling of extreme operands, which d >= 1 needs only where it is huge.  There it is
-// held at 2^100 (z < -69: the result is below 1e-28 in size either way).
+// The denominator is held at 2^100 (z < -69).
 __device__ __forceinline__ float sig_den(float z) { return fminf(1.0f + __expf(-z), 0x1p100f); }
-__device__ __forceinline__ float silu_rn(float z) {
-  const float d = sig_den(z), y0 = __builtin_amdgcn_rcpf(d);
-  const float y = __builtin_fmaf(__builtin_fmaf(-d, y0, 1.0f), y0, y0);
-  const float q = z * y;
-  return __builtin_fmaf(__builtin_fmaf(-d, q, z), y, q);
+__device__ __forceinline__ float silu(float z) {
+  const float d = sig_den(z);
+  return silu_of(z, d, __builtin_amdgcn_rcpf(d));
 }
-// silu and silu' = s (1 + z (1 - s)) with the correctly rounded sigmoid s = 1/d
 __device__ __forceinline__ void silu_both(float z, float& sl, float& ds) {
-  const float d = sig_den(z), y0 = __builtin_amdgcn_rcpf(d);
-  const float y = __builtin_fmaf(__builtin_fmaf(-d, y0, 1.0f), y0, y0);
-  const float s = __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
-  const float q = z * s;
-  sl = __builtin_fmaf(__builtin_fmaf(-d, q, z), s, q);
-  ds = s * __builtin_fmaf(z, 1.0f - s, 1.0f);
-}
-// silu where the value is rounded to BF16 at once: without the Newton step the quotient is
-// correctly rounded but for about one value in 2^20, by one FP32 unit in the last place.
-__device__ __forceinline__ float silu_bf(float z) {
-  const float d = sig_den(z), y = __builtin_amdgcn_rcpf(d);
-  const float q = z * y;
-  return __builtin_fmaf(__builtin_fmaf(-d, q, z), y, q);
+  const float d = sig_den(z);
+  silu_both_of(z, d, __builtin_amdgcn_rcpf(d), sl, ds);
 }
 // Sum over the 16 lanes of a row, in every lane (quad permutations, then the mirrored half rows and
 // rows: their lanes hold equal values by then).
@@ -428,7 +412,8 @@ __global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict
 // layer for event l % 16 of a group of 16 and the features 32 kk + 8 (l / 16) + j, which is the
 // layout in which the matrix cores read them as the A operand, and the weights of all layers stay
 // in registers over the events of the wavefront.  Bound by the vector instructions of the 128
-// sigmoids per event: 148 us per call for 2e6 events.  (335 us with the layers passed through LDS
+// sigmoids per event: 153 us per call for 2e6 events (4 of them for the Newton step of the first layer's
+// reciprocals, without which one quotient in about 2^20 is not correctly rounded).  (335 us with the layers passed through LDS
 // by a workgroup per 64 events, a barrier between them, whole IEEE divisions and the double
 // exponential of four events per 16 lanes evaluated in each of them.)
 __global__ __launch_bounds__(256, 2) void mlp_eval_kernel(MlpArgs a) {
@@ -471,7 +456,7 @@ __global__ __launch_bounds__(256, 2) void mlp_eval_kernel(MlpArgs a) {
       for (int k = 0; k < 4; ++k) um[k] = __shfl(u[k], 16 * mt + l16, 64);
       bf8_t h[2];
 #pragma unroll
-      for (int c = 0; c < 16; ++c) h[c >> 3][c & 7] = (__bf16)silu_bf(w1.z(c, um));
+      for (int c = 0; c < 16; ++c) h[c >> 3][c & 7] = (__bf16)silu(w1.z(c, um));
       float z3p[4] = {0.f, 0.f, 0.f, 0.f};   // events 4 lg + r of the group
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) {
@@ -479,7 +464,7 @@ __global__ __launch_bounds__(256, 2) void mlp_eval_kernel(MlpArgs a) {
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) z2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h[kk], w2[nt][kk], z2, 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) z3p[r] += w3[nt] * silu_rn(z2[r] + b2[nt]);
+        for (int r = 0; r < 4; ++r) z3p[r] += w3[nt] * silu(z2[r] + b2[nt]);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) z3p[r] = row_sum(z3p[r]);
