@@ -32,14 +32,12 @@ __device__ __forceinline__ unsigned short bf16(float f) {
   u += 0x7fffu + ((u >> 16) & 1u);
   return (unsigned short)(u >> 16);
 }
-// The denominator is held at 2^100 (z < -69).
-__device__ __forceinline__ float sig_den(float z) { return fminf(1.0f + __expf(-z), 0x1p100f); }
 __device__ __forceinline__ float silu(float z) {
-  const float d = sig_den(z);
+  const float d = 1.0f + __expf(-z);
   return silu_of(z, d, __builtin_amdgcn_rcpf(d));
 }
 __device__ __forceinline__ void silu_both(float z, float& sl, float& ds) {
-  const float d = sig_den(z);
+  const float d = 1.0f + __expf(-z);
   silu_both_of(z, d, __builtin_amdgcn_rcpf(d), sl, ds);
 }
 // Sum over the 16 lanes of a row, in every lane (quad permutations, then the mirrored half rows and

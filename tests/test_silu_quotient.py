@@ -1,5 +1,6 @@
 """silu(z) = z / (1 + exp(-z)) in the network kernels (kpsi_silu.h) against the IEEE division, on the CPU:
-the quotient is that of the division for every estimate of the reciprocal within one unit in the last place."""
+the quotient is that of the division for every estimate of the reciprocal within one unit in the last
+place, and saturated units, infinities and NaN give what the division gives."""
 import ctypes
 import os
 import subprocess
@@ -72,3 +73,21 @@ def test_quotient_is_the_ieee_quotient(silu, ulp):
     assert _same(sl, z / d) and _same(sl2, z / d)
     want = s.astype(np.float64) * (1 + z.astype(np.float64) * (F(1) - s).astype(np.float64))
     assert np.max(np.abs(ds - want)[:n]) <= 2.0**-23   # (z and d of a unit)
+
+
+def test_saturated_units_and_special_values(silu):
+    with np.errstate(all="ignore"):
+        z = np.concatenate([np.linspace(-140, 140, 2801), -np.logspace(2, 38, 400), np.logspace(2, 38, 400),
+                            [np.inf, -np.inf, np.nan, 0.0, -0.0]]).astype(F)
+        d = (F(1) + np.exp(-z)).astype(F)
+        y0 = (F(1) / d).astype(F)
+        y0[np.abs(y0) < F(2.0**-126)] = 0   # a denormal estimate is returned as zero
+        sl, sl2, ds = silu(z, d, y0)
+        want, s = z / d, F(1) / d
+        want_ds = s * (F(1) + z * (F(1) - s))
+    edge = (d > F(2.0**126)) & np.isfinite(d)
+    assert _same(sl[~edge], want[~edge]) and _same(sl2[~edge], want[~edge])
+    assert np.all(np.abs(sl[edge] - want[edge]) <= 2e-36) and np.all(np.abs(sl2[edge] - want[edge]) <= 2e-36)
+    assert np.array_equal(np.isnan(ds), np.isnan(want_ds))
+    ok = ~np.isnan(ds)
+    assert np.all(np.abs(ds[ok] - want_ds[ok]) <= 2.0**-22 * np.maximum(1, np.abs(want_ds[ok])))
