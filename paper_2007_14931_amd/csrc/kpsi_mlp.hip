@@ -242,10 +242,12 @@ __global__ __launch_bounds__(256, 1) void mlp_grad_kernel(MlpArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) z3p[r] = row_sum(z3p[r]);
     const float zlo = (l16 & 1) ? z3p[1] : z3p[0], zhi = (l16 & 1) ? z3p[3] : z3p[2];
-    const float p = 1.0f / (1.0f + __expf(-(((l16 & 2) ? zhi : zlo) + b3)));
-    const float pc = fminf(fmaxf(p, 1e-12f), 1.0f - 1e-12f);
+    const float z3 = ((l16 & 2) ? zhi : zlo) + b3;
+    const float p = 1.0f / (1.0f + __expf(-z3)), d_not = 1.0f + __expf(z3);
+    const float p_not = quotient(1.0f, d_not, newton_rcp(d_not, __builtin_amdgcn_rcpf(d_not)));
     const float dz = ok ? p - yl : 0.0f;
-    const float term = ok ? -(yl * __logf(pc) + (1.0f - yl) * __logf(1.0f - pc)) : 0.0f;
+    // (p_not and not 1 - p, which is 0 for z3 > 17: its logarithm is then -inf, and times a label's 0 no number)
+    const float term = ok ? -(yl * __logf(fmaxf(p, 1e-12f)) + (1.0f - yl) * __logf(fmaxf(p_not, 1e-12f))) : 0.0f;
     const float dz3[4] = {dpp<0x00>(dz), dpp<0x55>(dz), dpp<0xAA>(dz), dpp<0xFF>(dz)};
     const float tr[4] = {dpp<0x00>(term), dpp<0x55>(term), dpp<0xAA>(term), dpp<0xFF>(term)};
 #pragma unroll

@@ -61,3 +61,18 @@ def test_units_far_below_zero_are_off(z):
     assert not g2[5::9].any() and not g[4416:4480][5::9].any() and not g[4480:4544][5::9].any()
     keep = np.setdiff1d(np.arange(64), np.arange(3, 64, 7))
     assert np.array_equal(g[256:320][keep], h[256:320][keep])
+
+
+# outputs at and beyond where 1 - p is 0 in single precision (a logit of 17), and where the loss is clamped
+# at a probability of 1e-12 (27.6), for events of either label
+@pytest.mark.parametrize("b3", [-60.0, -30.0, -18.0, 18.0, 30.0, 60.0])
+def test_loss_of_confident_outputs(b3):
+    e, dev, lab, u, y = _case(81)
+    par = W.mlp_init(7)
+    par[4544] = b3
+    g, loss = e.mlp_grad(par, dev, lab)
+    ref_loss, _, ref_g = O.mlp(par.astype(np.float64), u, y.astype(np.float64), grad=True)
+    assert 0 < y.sum() < y.size and loss == pytest.approx(ref_loss, rel=2e-5)
+    assert np.linalg.norm(g - ref_g) <= 1e-3 * np.linalg.norm(ref_g)
+    after, train_loss = e.mlp_train(par, dev, lab, epochs=1, batch=128, lr=1e-4)
+    assert np.isfinite(train_loss) and np.all(np.isfinite(after))
