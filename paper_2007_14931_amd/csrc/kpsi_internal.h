@@ -137,6 +137,8 @@ template <typename T, class Sh> struct AmpArgs {
   // instantiation that reads the extra angular columns; its lambda' = -1 accumulators take the
   // record slots of the (then unused) second Z.
   int zfree;
+  T fh[NFL][3][2];      // couplings of the floating slots by helicity, as the kernel sums their weights: K* lambda = -1, 0, +1,
+                        // Z lambda' = 0, +-1 or, free helicities, 0, +1, -1
 };
 // The per-event kernel's arguments in MODE_TOYS.  (Apart, so that the other modes' launches do not
 // carry them.)

@@ -249,15 +249,16 @@ LsConst lineshape_consts(const kpsi_kinematics& k, const kpsi_resonance& r, doub
 
 // Constant factors between a resonance's physical couplings K H and the per-event kernel's
 // couplings h: e0 and e1 for its lambda = 0 and lambda = +-1 terms (the constants of the angular
-// functions and the 1/M_B of each power of p_B; Z: the sqrt2 of the rotated muon amplitudes, and
-// 1/sqrt2 more where two free helicity couplings combine).
+// functions and the 1/M_B of each power of p_B; Z: the sqrt2 of the rotated muon amplitudes, halved
+// where two free helicity couplings combine).
 //   K*, spin >= 1: h[0] = e1 (H_+ - H_-)/sqrt2, h[1] = e0 H_0, h[2] = e1 (H_+ + H_-)/sqrt2
 //   K*, spin 0:    h[1] = e0 H_0
 //   Z:             h[0] = sqrt2 H'_0, h[1] = sqrt2 H'_{+-1}
 //   Z, free:       h[0] = sqrt2 H'_0, h[1] = (H'_+1 + H'_-1)/sqrt2, h[2] = (H'_+1 - H'_-1)/sqrt2
+// The gradient's sums are by helicity again: those of lambda = +-1 carry the same e1.
 struct CoupScale { double e0, e1; };
 CoupScale coup_scale(const kpsi_kinematics& k, const kpsi_resonance& r) {
-  if (r.chain == 1) return {M_SQRT2, M_SQRT2};
+  if (r.chain == 1) return {M_SQRT2, r.hel_free ? M_SQRT1_2 : M_SQRT2};
   constexpr double E0[5] = {AngScale<0>::E0, AngScale<1>::E0, AngScale<2>::E0, AngScale<3>::E0, AngScale<4>::E0};
   constexpr double E1[5] = {AngScale<0>::E1, AngScale<1>::E1, AngScale<2>::E1, AngScale<3>::E1, AngScale<4>::E1};
   double f = 1.0;
@@ -276,14 +277,11 @@ void physical_couplings(const kpsi_resonance& r, double K, const double* p, doub
   }
 }
 
-// Per-event kernel constants of one resonance.
-template <typename T>
-void fill_ac(AC<T>& rc, const kpsi_kinematics& k, const kpsi_resonance& r, const LsConst& c, const double* p) {
+// Per-event kernel constants of one resonance, with the physical couplings h[2][3] and the scales s.
+template <typename T> void fill_ac(AC<T>& rc, const kpsi_resonance& r, const LsConst& c, const double h[2][3], const CoupScale& s) {
   rc.M2 = (T)c.M2;
   rc.P = (T)c.P;
-  const CoupScale s = coup_scale(k, r);
-  double h[2][3], g[2][3];
-  physical_couplings(r, c.K, p, h[0], h[1]);
+  double g[2][3];
   for (int i = 0; i < 2; ++i) {
     if (r.chain == 0) {
       g[i][0] = s.e1 * (h[i][2] - h[i][0]);
@@ -291,8 +289,8 @@ void fill_ac(AC<T>& rc, const kpsi_kinematics& k, const kpsi_resonance& r, const
       g[i][2] = s.e1 * (h[i][2] + h[i][0]);
     } else {
       g[i][0] = s.e0 * h[i][0];
-      g[i][1] = r.hel_free ? M_SQRT1_2 * (h[i][1] + h[i][2]) : s.e1 * h[i][1];
-      g[i][2] = r.hel_free ? M_SQRT1_2 * (h[i][1] - h[i][2]) : 0.0;
+      g[i][1] = s.e1 * (r.hel_free ? h[i][1] + h[i][2] : h[i][1]);
+      g[i][2] = r.hel_free ? s.e1 * (h[i][1] - h[i][2]) : 0.0;
     }
   }
   for (int l = 0; l < 3; ++l) {
@@ -300,6 +298,9 @@ void fill_ac(AC<T>& rc, const kpsi_kinematics& k, const kpsi_resonance& r, const
     rc.h[l][1] = (T)g[1][l];
   }
 }
+
+// Scale of the helicity term l (K* lambda = l - 1, Z lambda' = 0, +1, -1) of a resonance.
+double term_scale(const kpsi_resonance& r, const CoupScale& s, int l) { return l == (r.chain == 0 ? 1 : 0) ? s.e0 : s.e1; }
 
 // Pack the canonical parameter vector into the per-event kernel's arguments.
 template <typename T, class Sh> void pack(const kpsi_ctx* c, const double* par, AmpArgs<T, Sh>& a) {
@@ -315,14 +316,21 @@ template <typename T, class Sh> void pack(const kpsi_ctx* c, const double* par, 
     const kpsi_resonance& r = c->res[i];
     const LsConst lc = lineshape_consts(c->kin, r, par[ncr + 2 * i], par[ncr + 2 * i + 1]);
     const int slot = (r.chain == 0 ? 0 : Sh::NK) + c->slot[i];
-    fill_ac(a.cs[slot], c->kin, r, lc, par + c->coff[i]);
+    const CoupScale cs = coup_scale(c->kin, r);
+    double h[2][3];
+    physical_couplings(r, lc.K, par + c->coff[i], h[0], h[1]);
+    fill_ac(a.cs[slot], r, lc, h, cs);
     a.M2lo[slot] = (T)(lc.M2 - (double)a.cs[slot].M2);
     if (r.shape == 1) {
       a.lass |= 1 << slot;
       a.lai[slot] = (T)(1.0 / r.lass_a);
       a.lhb[slot] = (T)(0.5 * r.lass_b);
     }
-    if (c->fslot[i] >= 0) a.flt[c->fslot[i]] = slot;
+    const int f = c->fslot[i];
+    if (f < 0) continue;
+    a.flt[f] = slot;
+    for (int l = 0; l < 3; ++l)
+      for (int q = 0; q < 2; ++q) a.fh[f][l][q] = (T)(term_scale(r, cs, l) * h[q][l]);
   }
   a.zfree = c->zfree ? 1 : 0;
   for (int j = 0; j < 6; ++j) a.cnt[j] = c->cnt[j];
@@ -369,8 +377,8 @@ int shape_counts(int shape, int* N, int* NZ) {
   return 0;
 }
 
-// From the per-event kernel's gradient record (sums over its couplings h and the lineshape sums
-// of flt_sums) to the form the gradient is assembled from: d/dH' of the physical couplings
+// From the per-event kernel's gradient record (sums by helicity but for constant factors, and the
+// lineshape sums of flt_sums) to the form the gradient is assembled from: d/dH' of the physical couplings
 // H' = K H in their helicity order, and d/dM, d/dGamma0 per floating slot, in place.
 void finish_record(const kpsi_ctx* c, const double* par, double* rec) {
   int N[5], NZ;
@@ -382,29 +390,11 @@ void finish_record(const kpsi_ctx* c, const double* par, double* rec) {
     const kpsi_resonance& r = c->res[i];
     double* v = rec + acc_offset(c, i, N);
     const CoupScale s = coup_scale(c->kin, r);
-    const int nl = ncoup(r);
-    for (int q = 0; q < 2; ++q) {   // real and imaginary parts
-      if (r.chain == 0 && r.spin == 0) {
-        v[q] *= s.e0;
-      } else if (r.chain == 0) {
-        const double gp = s.e1 * v[q], gm = s.e1 * v[4 + q];
-        v[q] = gm - gp;        // lambda = -1
-        v[2 + q] *= s.e0;
-        v[4 + q] = gm + gp;    // lambda = +1
-      } else {
-        v[q] *= s.e0;
-        if (r.hel_free) {
-          const double gs = M_SQRT1_2 * v[2 + q], gd = M_SQRT1_2 * v[4 + q];
-          v[2 + q] = gs + gd;
-          v[4 + q] = gs - gd;
-        } else {
-          v[2 + q] *= s.e1;
-        }
-      }
-    }
+    const int nl = ncoup(r), l0 = r.chain == 0 && r.spin == 0 ? 1 : 0;
+    for (int l = 0; l < nl; ++l)
+      for (int q = 0; q < 2; ++q) v[2 * l + q] *= term_scale(r, s, l0 + l);   // real and imaginary parts
     if (c->fslot[i] < 0) continue;
     const LsConst lc = lineshape_consts(c->kin, r, par[ncr + 2 * i], par[ncr + 2 * i + 1]);
-    const int l0 = r.chain == 0 && r.spin == 0 ? 1 : 0;
     double hr[3], hi[3], sx = 0.0;   // sx = sum Re X = Re sum_lambda H'_lambda dS/dH'_lambda
     physical_couplings(r, lc.K, par + c->coff[i], hr, hi);
     for (int l = 0; l < nl; ++l) sx += hr[l0 + l] * v[2 * l] - hi[l0 + l] * v[2 * l + 1];
@@ -620,7 +610,7 @@ kpsi_status gram_build_t(kpsi_ctx* c, const double* par, bool with_eps, bool wit
     const CoupScale cs = coup_scale(c->kin, r);
     // x times the lineshape columns at `a` (the first p, m or Z column) and `u` into the components k ..
     auto put = [&](int k, int a, int u, double x) {
-      const double e0 = lc.K * cs.e0 * x, e1 = lc.K * cs.e1 * x, eh = lc.K * M_SQRT1_2 * x;
+      const double e0 = lc.K * cs.e0 * x, e1 = lc.K * cs.e1 * x;
       if (r.chain == 0) {
         of[r.spin > 0 ? k + 1 : k].add(u, e0);
         if (r.spin > 0) {
@@ -632,11 +622,11 @@ kpsi_status gram_build_t(kpsi_ctx* c, const double* par, bool with_eps, bool wit
         return;
       }
       of[k].add(a, e0);
-      of[k + 1].add(a + 1, nk == 3 ? eh : e1);
+      of[k + 1].add(a + 1, e1);
       if (nk == 3) {
-        of[k + 1].add(a + 2, eh);
-        of[k + 2].add(a + 1, eh);
-        of[k + 2].add(a + 2, -eh);
+        of[k + 1].add(a + 2, e1);
+        of[k + 2].add(a + 1, e1);
+        of[k + 2].add(a + 2, -e1);
       }
     };
     const int sl = c->slot[i];
