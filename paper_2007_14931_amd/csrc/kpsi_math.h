@@ -67,14 +67,15 @@ template <typename T> __device__ __forceinline__ T pole_gap_m(T M2, T M2lo, T m)
   else return fma_(-m, m, M2);
 }
 
-// The per-event kernel's angular functions: d^J_{00}(theta_K) = E0<J> ang0<J> and d^J_{10}(theta_K) =
-// E1<J> sin ang1<J>, with the constants folded into the couplings on the host.
+// The kernels' angular functions: d^J_{00}(theta_K) = E0<J> ang0<J> and d^J_{10}(theta_K) / sqrt2 = E1<J> sin
+// ang1<J>, with the constants folded into the couplings on the host.  (Each is one rounded number: as products
+// of rounded roots they would shift the lambda = +-1 terms of every event by up to 2^-52.)
 template <int J> struct AngScale;
 template <> struct AngScale<0> { static constexpr double E0 = 1.0, E1 = 0.0; };
-template <> struct AngScale<1> { static constexpr double E0 = 1.0, E1 = -0.70710678118654752440; };
-template <> struct AngScale<2> { static constexpr double E0 = 1.0, E1 = -1.22474487139158904910; };
-template <> struct AngScale<3> { static constexpr double E0 = 1.0, E1 = -0.43301270189221932338; };
-template <> struct AngScale<4> { static constexpr double E0 = 0.125, E1 = -0.55901699437494742410; };
+template <> struct AngScale<1> { static constexpr double E0 = 1.0, E1 = -0.5; };
+template <> struct AngScale<2> { static constexpr double E0 = 1.0, E1 = -0.86602540378443864676; };     // sqrt(3)/2
+template <> struct AngScale<3> { static constexpr double E0 = 1.0, E1 = -0.30618621784789726227; };     // sqrt(6)/8
+template <> struct AngScale<4> { static constexpr double E0 = 0.125, E1 = -0.39528470752104741649; };   // sqrt(10)/8
 template <int J, typename T> __device__ __forceinline__ T ang0(T c) {
   if constexpr (J == 0) return T(1);
   else if constexpr (J == 1) return c;

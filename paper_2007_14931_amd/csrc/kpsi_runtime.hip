@@ -258,12 +258,13 @@ LsConst lineshape_consts(const kpsi_kinematics& k, const kpsi_resonance& r, doub
 // The gradient's sums are by helicity again: those of lambda = +-1 carry the same e1.
 struct CoupScale { double e0, e1; };
 CoupScale coup_scale(const kpsi_kinematics& k, const kpsi_resonance& r) {
-  if (r.chain == 1) return {M_SQRT2, r.hel_free ? M_SQRT1_2 : M_SQRT2};
+  // (the Z columns carry the rounded 1/sqrt2: its reciprocal takes that rounding out, sqrt2 would double it)
+  if (r.chain == 1) return {1.0 / M_SQRT1_2, (r.hel_free ? 0.5 : 1.0) / M_SQRT1_2};
   constexpr double E0[5] = {AngScale<0>::E0, AngScale<1>::E0, AngScale<2>::E0, AngScale<3>::E0, AngScale<4>::E0};
   constexpr double E1[5] = {AngScale<0>::E1, AngScale<1>::E1, AngScale<2>::E1, AngScale<3>::E1, AngScale<4>::E1};
   double f = 1.0;
   for (int i = 0; i < lowest_lb(r); ++i) f /= k.m_b;
-  return {f * E0[r.spin], f * E1[r.spin] * M_SQRT1_2};
+  return {f * E0[r.spin], f * E1[r.spin]};
 }
 
 // Complex couplings times K of table resonance r at the parameters p: K*, spin >= 1 lambda = -1, 0,
