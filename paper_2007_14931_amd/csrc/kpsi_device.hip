@@ -22,7 +22,7 @@
 namespace kpsi {
 
 // ------------------------------------------------------------------ math helpers
-// rcp_, rsq_, fma_, the barrier polynomials and the d functions: kpsi_math.h
+// rcp_, rsq_, fma_, the barrier polynomials and the angular functions: kpsi_math.h
 // Smallest density a data event may have (exclusive): the FP32 path counts an event whose density
 // is below the smallest normal float as a bad event.
 template <typename T> __device__ __forceinline__ constexpr T pos_floor() {

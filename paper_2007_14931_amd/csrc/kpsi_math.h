@@ -1,8 +1,8 @@
 // Device arithmetic shared by the per-event kernel and the interference-matrix kernel: the
 // hardware reciprocal and reciprocal square root (refined by Newton steps in FP64), the
-// normalised Blatt-Weisskopf polynomials, and the small-d functions d^J_{00}, d^J_{10} of the
-// K* helicity angle (Eq. 4).  One copy, so both kernels evaluate the same lineshape and
-// angular polynomials.  Also the opaque kernel-argument pointer both use in their event loops.
+// normalised Blatt-Weisskopf polynomials, and the angular functions of the K* helicity angle
+// (Eq. 4: the small-d functions d^J_{00}, d^J_{10} without their constant factors).  One copy, so
+// both kernels evaluate the same lineshape and angular polynomials.  Also the opaque kernel-argument pointer both use in their event loops.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -88,23 +88,6 @@ template <int J, typename T> __device__ __forceinline__ T ang1(T c) {
   else if constexpr (J == 2) return c;
   else if constexpr (J == 3) return fma_(T(5) * c, c, T(-1));
   else return c * fma_(T(7) * c, c, T(-3));
-}
-
-// d^J_{00}(theta_K) and d^J_{10}(theta_K) (d^J_{-1,0} = -d^J_{10}) as polynomials in cos and sin.
-template <int J, typename T> __device__ __forceinline__ T d00(T c) {
-  if constexpr (J == 0) return T(1);
-  else if constexpr (J == 1) return c;
-  else if constexpr (J == 2) return T(1.5) * c * c - T(0.5);
-  else if constexpr (J == 3) return c * (T(2.5) * c * c - T(1.5));
-  else { T c2 = c * c; return (T(35) * c2 * c2 - T(30) * c2 + T(3)) * T(0.125); }
-}
-template <int J, typename T> __device__ __forceinline__ T d10(T c, T s) {
-  // -sin * P_J'(cos) / sqrt(J (J+1))
-  if constexpr (J == 1) return -s * T(0.70710678118654752440);
-  else if constexpr (J == 2) return -s * c * T(1.22474487139158904910);
-  else if constexpr (J == 3) return -s * (T(15) * c * c - T(3)) * T(0.14433756729740644113);
-  else if constexpr (J == 4) return -s * c * (T(35) * c * c - T(15)) * T(0.11180339887498948482);
-  else return T(0);
 }
 
 // Opaque copy of a pointer to uniform kernel-argument data.  Re-deriving it inside the
