@@ -526,6 +526,8 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
   // Column groups of this thread's event.  The FP64 gradient kernel of the large shape (two wavefronts
   // per SIMD) fetches the next event's as soon as the current ones are used up, before the
   // accumulation (a clamped index past the last event: no branch); 108 against 111 us for 3e6 events.
+  // With free helicities the last pass of a block branches over it: the kernel then needs no scratch
+  // (3e6 events 114.8 against 116.3 us, 48e3 events 20.8 against 21.5; without them 110.9 against 109.2).
   // The others load them where the event begins, and the Z columns where the Z chain does: the live
   // registers cost the FP32 gradient kernel more than the latency (51.5 against 50.5 us) and the
   // likelihood-only ones wavefronts (FP32: 37 against 35 us), and the small shape reads at the
@@ -610,10 +612,12 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
     // only arithmetic may cross, keeps it there.  Scalar loads return out of order, so every wait
     // is for all of them; loaded where they are used, each resonance waited for its own.  The four
     // wavefronts of FP32 hide those waits, and the fixed order costs more than it gives there
-    // (tagged step 90 against 85 us).
+    // (tagged step 90 against 85 us); so it does in the tagged FP64 gradient kernel, whose second
+    // reading leaves no registers for the order (3e6 events 187 against 179 us, 28e3 events 21.2 against
+    // 19.6, and no scratch).
     using C8 = T __attribute__((ext_vector_type(8)));
     const kconst_ptr<C8> cp = (kconst_ptr<C8>)&ka.cs[0];
-    constexpr bool AHEAD = std::is_same_v<T, double>;
+    constexpr bool AHEAD = std::is_same_v<T, double> && !(CC && GRAD);
     C8 ahead{};
     if constexpr (AHEAD) ahead = cp[0];
     auto constants = [&](int k) -> C8 {
@@ -968,7 +972,9 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
           }
         }
       }
-      if constexpr (PRE) fetch(i + 256 < n_blk ? i + 256 : i);
+      if constexpr (PRE) {
+        if (!ZF || left != 0) fetch(i + 256 < n_blk ? i + 256 : i);
+      }
       auto grad_spin = [&](auto Jc) {
         constexpr int J = decltype(Jc)::value;
         if constexpr (Sh::N[J] > 0) {
