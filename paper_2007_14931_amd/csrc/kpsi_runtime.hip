@@ -1173,7 +1173,11 @@ kpsi_status generate_toys(kpsi_ctx* c, const double* params, uint64_t seed, int6
     if (e == hipSuccess)
       e = hipMemcpyAsync(h, rec, (1 + chunks) * kToyStat * sizeof(unsigned), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) return fail(c, KPSI_E_HIP, "generator: %s", hipGetErrorString(e));
+    if (e != hipSuccess) {
+      *n_prop = e0;
+      *n_over = novr;
+      return fail(c, KPSI_E_HIP, "generator: %s", hipGetErrorString(e));
+    }
     for (int i = 0; i < chunks && !complete; ++i) {
       const unsigned* x = h + (1 + i) * kToyStat;
       for (int k = 0; k < len[i] && !complete; ++k) {
