@@ -896,24 +896,27 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
     if constexpr (GRAD) {
       // adjoint of S = |X|^2 + |Y|^2: bX = w conj(X), bY = w conj(Y); the weights of P, M and U_0
       // are W_P = cos phi bX + i sin phi cos th_J bY, W_M = i sin phi bX + cos phi cos th_J bY and
-      // W_0 = sin th_J bY, summed over the readings of the event
-      Cx<T> W0, WP, WM;
+      // W_0 = sin th_J bY.  Those of lambda = +-1, W_M +- W_P, are e^{+-i phi} (cos th_J bY +- bX): the sums
+      // are kept by helicity (as sums over P and M, the gradient of a small helicity beside a large one
+      // would be the difference of two sums of the large one's size).  Summed over the readings of the event.
+      Cx<T> W0, Wp, Wm;
       Cx<T> bX, bY, bX2{T(0), T(0)}, bY2{T(0), T(0)};
       auto adj_w = [&](auto first, T wt, T f, const Cx<T>& X_, const Cx<T>& Y_, Cx<T>& bX_, Cx<T>& bY_) {
         constexpr bool F = decltype(first)::value;
         bX_ = Cx<T>{wt * X_.re, -wt * X_.im};
         bY_ = Cx<T>{wt * Y_.re, -wt * Y_.im};
         const T sp = f * sph;
-        const Cx<T> y{cJ * bY_.re, cJ * bY_.im};
+        const Cx<T> s{fma_(cJ, bY_.re, bX_.re), fma_(cJ, bY_.im, bX_.im)};
+        const Cx<T> d{fma_(cJ, bY_.re, -bX_.re), fma_(cJ, bY_.im, -bX_.im)};
         if constexpr (F) {
-          WP = Cx<T>{fma_(cph, bX_.re, -sp * y.im), fma_(cph, bX_.im, sp * y.re)};
-          WM = Cx<T>{fma_(cph, y.re, -sp * bX_.im), fma_(cph, y.im, sp * bX_.re)};
+          Wp = Cx<T>{fma_(cph, s.re, -sp * s.im), fma_(cph, s.im, sp * s.re)};
+          Wm = Cx<T>{fma_(cph, d.re, sp * d.im), fma_(cph, d.im, -sp * d.re)};
           W0 = Cx<T>{sJ * bY_.re, sJ * bY_.im};
         } else {
-          WP.re = fma_(cph, bX_.re, fma_(-sp, y.im, WP.re));
-          WP.im = fma_(cph, bX_.im, fma_(sp, y.re, WP.im));
-          WM.re = fma_(cph, y.re, fma_(-sp, bX_.im, WM.re));
-          WM.im = fma_(cph, y.im, fma_(sp, bX_.re, WM.im));
+          Wp.re = fma_(cph, s.re, fma_(-sp, s.im, Wp.re));
+          Wp.im = fma_(cph, s.im, fma_(sp, s.re, Wp.im));
+          Wm.re = fma_(cph, d.re, fma_(sp, d.im, Wm.re));
+          Wm.im = fma_(cph, d.im, fma_(-sp, d.re, Wm.im));
           W0.re = fma_(sJ, bY_.re, W0.re);
           W0.im = fma_(sJ, bY_.im, W0.im);
         }
@@ -948,10 +951,7 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
           if (two) wz(std::false_type{}, -f1, bX2, bY2);
         }
       };
-      // V_{J lambda}: the angular functions times the weights, for lambda = +-1 of M +- P.  (The sums are kept by
-      // helicity: as sums over P and M, the gradient of a small helicity beside a large one would be the
-      // difference of two sums of the large one's size.)
-      Cx<T> Wp, Wm;
+      // V_{J lambda}: the angular functions times the weights
       auto V_of = [&](auto Jc, Cx<T>& Vm, Cx<T>& V0, Cx<T>& Vp) {
         constexpr int J = decltype(Jc)::value;
         V0 = Cx<T>{dd0[J] * W0.re, dd0[J] * W0.im};
@@ -960,8 +960,6 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
           Vp = Cx<T>{dd1[J] * Wp.re, dd1[J] * Wp.im};
         }
       };
-      Wp = Cx<T>{WM.re + WP.re, WM.im + WP.im};
-      Wm = Cx<T>{WM.re - WP.re, WM.im - WP.im};
       if constexpr (NZ > 0) {
         if (a.cnt[5] > 0) {
           z_weights();
