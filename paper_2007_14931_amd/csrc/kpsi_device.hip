@@ -690,15 +690,14 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
     do_spin(std::integral_constant<int, 3>{});
     do_spin(std::integral_constant<int, 4>{});
 
-    // ---- angular sums (Eq. 4) in the transversity basis.  With the helicity sums U_+- and U_0 of
-    // Eq. 4, P = (U_+ + U_-)/sqrt2 and M = (U_+ - U_-)/sqrt2 come from the coupling combinations
-    // h[0], h[2] directly (d^J_{-10} = -d^J_{10}), and the muon amplitudes a_+-1 rotated to
-    // X = (a_+ + a_-)/sqrt2, Y = (a_+ - a_-)/sqrt2 (S = |X|^2 + |Y|^2) are
-    //   X = cos phi P + i sin phi M + Z terms
-    //   Y = cos th_J (cos phi M + i sin phi P) + sin th_J U_0 + Z terms:
-    // every factor is real or imaginary, so each step is half a complex product, in the adjoint
-    // too.  The helicity form took about 25% more instructions for this part and twice as many in
-    // the Z chain.
+    // ---- angular sums (Eq. 4) and the muon amplitudes rotated to X = (a_+ + a_-)/sqrt2, Y = (a_+ - a_-)/sqrt2
+    // (S = |X|^2 + |Y|^2): with the helicity sums U_+- and U_0,
+    //   X = e^{i phi} U_+ - e^{-i phi} U_- + Z terms
+    //   Y = cos th_J (e^{i phi} U_+ + e^{-i phi} U_-) + sin th_J U_0 + Z terms
+    // (d^J_{-10} = -d^J_{10}; the constants are in the couplings): fewer instructions than a_+-1
+    // themselves, by about 25% in this part and half in the Z chain, whose factors are real or imaginary.
+    // The couplings stay by helicity: as rounded sums and differences, a small one beside a large one would
+    // be off by the large one's rounding in every event.
     // (n_J times the angular functions; the n_J of spins absent from the model are zero)
     T dd0[5], dd1[5];
     auto do_ang = [&](auto Jc) {
@@ -711,17 +710,17 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
     do_ang(std::integral_constant<int, 2>{});
     do_ang(std::integral_constant<int, 3>{});
     do_ang(std::integral_constant<int, 4>{});
-    Cx<T> U0{T(0), T(0)}, UP{T(0), T(0)}, UM{T(0), T(0)};
+    Cx<T> U0{T(0), T(0)}, Um{T(0), T(0)}, Up{T(0), T(0)};
 #pragma unroll
     for (int J = 0; J < 5; ++J) {
       if (Sh::N[J] == 0) continue;
       U0.re = fma_(dd0[J], Tl[J][1].re, U0.re);
       U0.im = fma_(dd0[J], Tl[J][1].im, U0.im);
       if (J > 0) {
-        UP.re = fma_(dd1[J], Tl[J][0].re, UP.re);
-        UP.im = fma_(dd1[J], Tl[J][0].im, UP.im);
-        UM.re = fma_(dd1[J], Tl[J][2].re, UM.re);
-        UM.im = fma_(dd1[J], Tl[J][2].im, UM.im);
+        Um.re = fma_(dd1[J], Tl[J][0].re, Um.re);
+        Um.im = fma_(dd1[J], Tl[J][0].im, Um.im);
+        Up.re = fma_(dd1[J], Tl[J][2].re, Up.re);
+        Up.im = fma_(dd1[J], Tl[J][2].im, Up.im);
       }
     }
     // Amplitudes X, Y of the event read with phi -> f phi.  f = -1 is the charge-conjugate decay:
@@ -729,8 +728,9 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
     // the Z angular factors.
     auto kstar_at = [&](T f, Cx<T>& X_, Cx<T>& Y_) {
       const T sp = f * sph;
-      X_ = Cx<T>{fma_(cph, UP.re, -sp * UM.im), fma_(cph, UP.im, sp * UM.re)};
-      const Cx<T> y{fma_(cph, UM.re, -sp * UP.im), fma_(cph, UM.im, sp * UP.re)};
+      const Cx<T> p{fma_(cph, Up.re, -sp * Up.im), fma_(cph, Up.im, sp * Up.re)};   // e^{i phi} U_+
+      X_ = Cx<T>{fma_(-cph, Um.re, fma_(-sp, Um.im, p.re)), fma_(-cph, Um.im, fma_(sp, Um.re, p.im))};
+      const Cx<T> y{fma_(cph, Um.re, fma_(sp, Um.im, p.re)), fma_(cph, Um.im, fma_(-sp, Um.re, p.im))};
       Y_ = Cx<T>{fma_(cJ, y.re, sJ * U0.re), fma_(cJ, y.im, sJ * U0.im)};
     };
     // Z chain: X += i z0i T0 + i z1i T1 (+ z2r T2), Y += z0r T0 + z1r T1 (+ i z2i T2), T2 with free
@@ -799,6 +799,11 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
             cmac(T1, rc[4], rc[5], AZ[z].re, AZ[z].im);
             if constexpr (ZF) cmac(T2, rc[6], rc[7], AZ[z].re, AZ[z].im);
           }
+        }
+        if constexpr (ZF) {   // sum and difference of lambda' = +1 and -1
+          const Cx<T> p = T1, m = T2;
+          T1 = Cx<T>{p.re + m.re, p.im + m.im};
+          T2 = Cx<T>{p.re - m.re, p.im - m.im};
         }
         z_add(f1, T0, T1, T2, X, Y);
         if constexpr (CC) {
@@ -894,11 +899,10 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
     }
 
     if constexpr (GRAD) {
-      // adjoint of S = |X|^2 + |Y|^2: bX = w conj(X), bY = w conj(Y); the weights of P, M and U_0
-      // are W_P = cos phi bX + i sin phi cos th_J bY, W_M = i sin phi bX + cos phi cos th_J bY and
-      // W_0 = sin th_J bY.  Those of lambda = +-1, W_M +- W_P, are e^{+-i phi} (cos th_J bY +- bX): the sums
-      // are kept by helicity (as sums over P and M, the gradient of a small helicity beside a large one
-      // would be the difference of two sums of the large one's size).  Summed over the readings of the event.
+      // adjoint of S = |X|^2 + |Y|^2: bX = w conj(X), bY = w conj(Y); the weights of U_+-, e^{+-i phi}
+      // (cos th_J bY +- bX), and of U_0, sin th_J bY, summed over the readings of the event.  (By helicity: as
+      // sums over the weights of U_+ +- U_-, the gradient of a small helicity beside a large one would be the
+      // difference of two sums of the large one's size.)
       Cx<T> W0, Wp, Wm;
       Cx<T> bX, bY, bX2{T(0), T(0)}, bY2{T(0), T(0)};
       auto adj_w = [&](auto first, T wt, T f, const Cx<T>& X_, const Cx<T>& Y_, Cx<T>& bX_, Cx<T>& bY_) {
@@ -1041,8 +1045,8 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
       // factor are picked by uniform branches (the slot numbers are re-read each event, so the
       // comparisons are not hoisted into scalar registers the loop needs), then one piece of code
       // sums them.
-      auto flt_slot = [&](int f, int slot, T& sR, T& sI) {
-        const auto& h = ka.fh[f];
+      auto flt_slot = [&](int slot, T& sR, T& sI) {
+        const auto& h = ka.cs[slot].h;
         Cx<T> B{T(0), T(0)}, Q{T(0), T(0)};
         T g = T(0);
         auto pick = [&](auto Jc) {
@@ -1080,8 +1084,8 @@ __global__ __launch_bounds__(256, (AmpWaves<T, Sh, MODE, CC>::v)) void amp_kerne
       };
       const int fs0 = ka.flt[0], fs1 = ka.flt[1];   // (the first is filled first)
       if (fs0 >= 0) {
-        flt_slot(0, fs0, gM0, gG0);
-        if (fs1 >= 0) flt_slot(1, fs1, gM1, gG1);
+        flt_slot(fs0, gM0, gG0);
+        if (fs1 >= 0) flt_slot(fs1, gM1, gG1);
       }
     }
   }
@@ -1334,6 +1338,10 @@ template <class Sh> __global__ __launch_bounds__(kBins) void bound_kernel(const 
     return 1.0 / sqrt(d * d + w * w);
   };
   auto mag = [](const double* h) { return sqrt(h[0] * h[0] + h[1] * h[1]); };
+  auto mag2 = [](const double* h, const double* g, double s) {   // |h + s g|
+    const double x = h[0] + s * g[0], y = h[1] + s * g[1];
+    return sqrt(x * x + y * y);
+  };
   // ---- Z chain: the bound over bin threadIdx.x of m_Jpsi pi, then the largest of the block
   __shared__ double zred[kBins / 64];
   double z = 0.0;
@@ -1344,7 +1352,7 @@ template <class Sh> __global__ __launch_bounds__(kBins) void bound_kernel(const 
     const double nZ = (pz / k.mB) / sqrt(1.0 + k.rB * pz * k.rB * pz);
     for (int i = 0; i < a.cnt[5]; ++i) {
       const AC<double>& rc = a.cs[Sh::NK + i];
-      const double h = mag(rc.h[0]) + mag(rc.h[1]) + (a.zfree ? mag(rc.h[2]) : 0.0);
+      const double h = mag(rc.h[0]) + (a.zfree ? mag2(rc.h[1], rc.h[2], 1.0) + mag2(rc.h[1], rc.h[2], -1.0) : mag(rc.h[1]));
       if (h > 0.0) z += h * prop(rc.M2, rc.P, m1 * m1, m2 * m2, g1) * nZ * 0.70710678118654752440;
     }
   }
@@ -1369,7 +1377,8 @@ template <class Sh> __global__ __launch_bounds__(kBins) void bound_kernel(const 
     for (int j = 0; j < Sh::N[J]; ++j) {
       const int sl = slot_base<Sh>(J) + j;
       const AC<double>& rc = a.cs[sl];
-      const double h0 = J > 0 ? mag(rc.h[0]) : 0.0, h1 = mag(rc.h[1]), h2 = J > 0 ? mag(rc.h[2]) : 0.0;
+      const double h1 = mag(rc.h[1]);   // the couplings of U_0, and of U_+ - U_- and U_+ + U_-
+      const double h0 = J > 0 ? mag2(rc.h[2], rc.h[0], -1.0) : 0.0, h2 = J > 0 ? mag2(rc.h[2], rc.h[0], 1.0) : 0.0;
       if (h0 == 0.0 && h1 == 0.0 && h2 == 0.0) continue;
       double A = prop(rc.M2, rc.P, m1 * m1, m2 * m2, gJ);
       if (J == 0 && (a.lass & (1 << sl))) {

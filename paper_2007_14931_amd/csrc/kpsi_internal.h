@@ -32,11 +32,8 @@ template <typename T> struct alignas(4 * sizeof(T)) RC {
 };
 
 // Per-resonance constants of the per-event kernel: eight values, so that one scalar load (32 bytes
-// in FP32, 64 in FP64) brings a resonance.  The couplings are those of the transversity basis the
-// kernel sums in (pack):
-//   K* of spin >= 1: h[0] ~ H_+ - H_-, h[1] ~ H_0, h[2] ~ H_+ + H_-;  spin 0: h[1] ~ H_0
-//   Z: h[0] ~ H'_0, h[1] ~ H'_{+-1} (Eq. 11), or, free helicities, h[1] ~ H'_+1 + H'_-1 and
-//   h[2] ~ H'_+1 - H'_-1
+// in FP32, 64 in FP64) brings a resonance.  The couplings by helicity,
+//   K*: lambda = -1, 0, +1 (spin 0: h[1] alone);  Z: lambda' = 0, +-1 (Eq. 11) or, free helicities, 0, +1, -1
 // each times K and the constant factors of its angular and barrier functions (CoupScale).
 template <typename T> struct alignas(8 * sizeof(T)) AC {
   T M2, P;
@@ -137,8 +134,6 @@ template <typename T, class Sh> struct AmpArgs {
   // instantiation that reads the extra angular columns; its lambda' = -1 accumulators take the
   // record slots of the (then unused) second Z.
   int zfree;
-  T fh[NFL][3][2];      // couplings of the floating slots by helicity, as the kernel sums their weights: K* lambda = -1, 0, +1,
-                        // Z lambda' = 0, +-1 or, free helicities, 0, +1, -1
 };
 // The per-event kernel's arguments in MODE_TOYS.  (Apart, so that the other modes' launches do not
 // carry them.)

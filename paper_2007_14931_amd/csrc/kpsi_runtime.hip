@@ -248,14 +248,9 @@ LsConst lineshape_consts(const kpsi_kinematics& k, const kpsi_resonance& r, doub
 }
 
 // Constant factors between a resonance's physical couplings K H and the per-event kernel's
-// couplings h: e0 and e1 for its lambda = 0 and lambda = +-1 terms (the constants of the angular
-// functions and the 1/M_B of each power of p_B; Z: the sqrt2 of the rotated muon amplitudes, halved
-// where two free helicity couplings combine).
-//   K*, spin >= 1: h[0] = e1 (H_+ - H_-)/sqrt2, h[1] = e0 H_0, h[2] = e1 (H_+ + H_-)/sqrt2
-//   K*, spin 0:    h[1] = e0 H_0
-//   Z:             h[0] = sqrt2 H'_0, h[1] = sqrt2 H'_{+-1}
-//   Z, free:       h[0] = sqrt2 H'_0, h[1] = (H'_+1 + H'_-1)/sqrt2, h[2] = (H'_+1 - H'_-1)/sqrt2
-// The gradient's sums are by helicity again: those of lambda = +-1 carry the same e1.
+// couplings h: e0 for its lambda = 0 and e1 for its lambda = +-1 terms (the constants of the angular
+// functions, the 1/sqrt2 of the rotated muon amplitudes and the 1/M_B of each power of p_B; Z: the sqrt2 of
+// the rotated muon amplitudes, halved where two free helicity couplings combine).
 struct CoupScale { double e0, e1; };
 CoupScale coup_scale(const kpsi_kinematics& k, const kpsi_resonance& r) {
   // (the Z columns carry the rounded 1/sqrt2: its reciprocal takes that rounding out, sqrt2 would double it)
@@ -278,30 +273,20 @@ void physical_couplings(const kpsi_resonance& r, double K, const double* p, doub
   }
 }
 
-// Per-event kernel constants of one resonance, with the physical couplings h[2][3] and the scales s.
-template <typename T> void fill_ac(AC<T>& rc, const kpsi_resonance& r, const LsConst& c, const double h[2][3], const CoupScale& s) {
-  rc.M2 = (T)c.M2;
-  rc.P = (T)c.P;
-  double g[2][3];
-  for (int i = 0; i < 2; ++i) {
-    if (r.chain == 0) {
-      g[i][0] = s.e1 * (h[i][2] - h[i][0]);
-      g[i][1] = s.e0 * h[i][1];
-      g[i][2] = s.e1 * (h[i][2] + h[i][0]);
-    } else {
-      g[i][0] = s.e0 * h[i][0];
-      g[i][1] = s.e1 * (r.hel_free ? h[i][1] + h[i][2] : h[i][1]);
-      g[i][2] = r.hel_free ? s.e1 * (h[i][1] - h[i][2]) : 0.0;
-    }
-  }
-  for (int l = 0; l < 3; ++l) {
-    rc.h[l][0] = (T)g[0][l];
-    rc.h[l][1] = (T)g[1][l];
-  }
-}
-
 // Scale of the helicity term l (K* lambda = l - 1, Z lambda' = 0, +1, -1) of a resonance.
 double term_scale(const kpsi_resonance& r, const CoupScale& s, int l) { return l == (r.chain == 0 ? 1 : 0) ? s.e0 : s.e1; }
+
+// Per-event kernel constants of one resonance with the couplings p.
+template <typename T>
+void fill_ac(AC<T>& rc, const kpsi_kinematics& k, const kpsi_resonance& r, const LsConst& c, const double* p) {
+  rc.M2 = (T)c.M2;
+  rc.P = (T)c.P;
+  const CoupScale s = coup_scale(k, r);
+  double h[2][3];
+  physical_couplings(r, c.K, p, h[0], h[1]);
+  for (int l = 0; l < 3; ++l)
+    for (int q = 0; q < 2; ++q) rc.h[l][q] = (T)(term_scale(r, s, l) * h[q][l]);
+}
 
 // Pack the canonical parameter vector into the per-event kernel's arguments.
 template <typename T, class Sh> void pack(const kpsi_ctx* c, const double* par, AmpArgs<T, Sh>& a) {
@@ -317,21 +302,14 @@ template <typename T, class Sh> void pack(const kpsi_ctx* c, const double* par, 
     const kpsi_resonance& r = c->res[i];
     const LsConst lc = lineshape_consts(c->kin, r, par[ncr + 2 * i], par[ncr + 2 * i + 1]);
     const int slot = (r.chain == 0 ? 0 : Sh::NK) + c->slot[i];
-    const CoupScale cs = coup_scale(c->kin, r);
-    double h[2][3];
-    physical_couplings(r, lc.K, par + c->coff[i], h[0], h[1]);
-    fill_ac(a.cs[slot], r, lc, h, cs);
+    fill_ac(a.cs[slot], c->kin, r, lc, par + c->coff[i]);
     a.M2lo[slot] = (T)(lc.M2 - (double)a.cs[slot].M2);
     if (r.shape == 1) {
       a.lass |= 1 << slot;
       a.lai[slot] = (T)(1.0 / r.lass_a);
       a.lhb[slot] = (T)(0.5 * r.lass_b);
     }
-    const int f = c->fslot[i];
-    if (f < 0) continue;
-    a.flt[f] = slot;
-    for (int l = 0; l < 3; ++l)
-      for (int q = 0; q < 2; ++q) a.fh[f][l][q] = (T)(term_scale(r, cs, l) * h[q][l]);
+    if (c->fslot[i] >= 0) a.flt[c->fslot[i]] = slot;
   }
   a.zfree = c->zfree ? 1 : 0;
   for (int j = 0; j < 6; ++j) a.cnt[j] = c->cnt[j];
