@@ -436,7 +436,8 @@ kpsi_status kpsi_mlp_eval(kpsi_ctx* ctx, const float* params, int64_t n, const d
 kpsi_status kpsi_set_efficiency_mlp(kpsi_ctx* ctx, const float* params);
 
 /* Launch tuning: events handled by each thread of the per-event kernel (1..1024), or 0
- * for the automatic choice (about 2048 blocks over the two sets). */
+ * for the automatic choice: whole rounds of the blocks that the device holds at once, and at most 64
+ * events per thread. */
 kpsi_status kpsi_set_events_per_thread(kpsi_ctx* ctx, int ept);
 
 /* Message of the last error on ctx (or of the last failed kpsi_create when ctx is NULL). */

@@ -48,11 +48,15 @@ typedef float f4_t __attribute__((ext_vector_type(4)));
 // Column order (complex): derivatives of p, m and Z columns; p and m of each K* slot; Z; u of each K*
 // slot; derivatives of u.
 //
-// Bound by instruction issue: the FP32 and FP64 matrix instructions occupy the vector units (another
-// wavefront's vector instructions do not overlap with them), so their 304 times 32 cycles per 64
-// events of the full model and the other instructions add up.  2e6 events in FP32: 326 us in the
-// helicity form (448 matrix instructions per 64 events, two evaluations of every lineshape), now
-// 257 us, and the result is 5 times closer to double precision (no rounded constant is left in it).
+// What bounds it (counters, 2e6 events of the full model in FP32): the FP32 and FP64 matrix instructions
+// occupy the vector units (another wavefront's vector instructions do not overlap with them); their 304
+// times 32 cycles per 64 events are 48% of the kernel's cycles, the other vector instructions 18%.  In the last
+// third neither issues: the two wavefronts of a SIMD wait for LDS operands, for the columns, and for the 64
+// to 80 bytes per lane of accumulators that the FP32 kernel of 80 columns keeps in scratch (41 to 55
+// registers; with one wavefront per SIMD and no scratch it took 338 against 320 us).  2e6 events in FP32:
+// 326 us in the helicity form (448 matrix instructions per 64 events, two evaluations of every
+// lineshape), now 250 to 260 us, and the result is 5 times closer to double precision (no rounded constant
+// is left in it).
 // ZF: one Z whose H'_{+1} and H'_{-1} are independent couplings: three Z columns.
 template <typename T, class Sh, int C, bool ZF>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 1)))

@@ -412,10 +412,10 @@ __global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict
 // layer for event l % 16 of a group of 16 and the features 32 kk + 8 (l / 16) + j, which is the
 // layout in which the matrix cores read them as the A operand, and the weights of all layers stay
 // in registers over the events of the wavefront.  Bound by the vector instructions of the 128
-// sigmoids per event: 153 us per call for 2e6 events (4 of them for the Newton step of the first layer's
-// reciprocals, without which one quotient in about 2^20 is not correctly rounded).  (335 us with the layers passed through LDS
-// by a workgroup per 64 events, a barrier between them, whole IEEE divisions and the double
-// exponential of four events per 16 lanes evaluated in each of them.)
+// sigmoids per event: 140 us of kernel, 153 us per call for 2e6 events.  (4% of that are the Newton steps
+// of the first layer's reciprocals, without which one quotient in about 2^20 is not correctly rounded.  335 us
+// per call with the layers passed through LDS by a workgroup per 64 events, a barrier between them, whole
+// IEEE divisions and the double exponential of four events per 16 lanes evaluated in each of them.)
 __global__ __launch_bounds__(256, 2) void mlp_eval_kernel(MlpArgs a) {
   using namespace nn;
   const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
